@@ -375,10 +375,10 @@ __host__ __device__ inline void adjoint_point_setup(const EventC& ec, const AdjE
 
 // A trigonometric polynomial of SiteC::jk and its second hour-angle
 // derivative from the same partial sums: with a1 = c1 cos H + c2 sin H and
-// a2 = c3 cos 2H + c4 sin 2H, y = c0 + a1 + a2 and y'' = -(a1 + 4 a2).
+// a2 = c3 cos 2H + c4 sin H cos H, y = c0 + a1 + a2 and y'' = -(a1 + 4 a2).
 __host__ __device__ inline void trig_val_dHH(const double c[5], const SiteTrig& sp, double& y, double& yhh) {
   const double a1 = fma(c[2], sp.sH, c[1] * sp.cH);
-  const double a2 = fma(c[4], sp.s2H, c[3] * sp.c2H);
+  const double a2 = fma(c[4], sp.sc, c[3] * sp.c2H);
   y = (a1 + a2) + c[0];
   yhh = -fma(4.0, a2, a1);
 }

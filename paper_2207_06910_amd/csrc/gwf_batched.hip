@@ -60,10 +60,10 @@ __global__ __launch_bounds__(64) void setup_kernel(SetupArgs a) {
 }
 
 template <int NPI, bool ROT, bool MIXED, bool TAB>
-__global__ __launch_bounds__(FisherDims<NPI>::TIDAL ? 2 * kBlock : kBlock) void items_kernel(ItemsArgs a) {
+__global__ __launch_bounds__(kBlock, 2) void items_kernel(ItemsArgs a) {
   using Dm = FisherDims<NPI>;
   constexpr int NACC = Dm::NACC;
-  __shared__ FisherLds L;
+  __shared__ FisherLds<NPI, 2> L;
   const int tid = threadIdx.x;
   const int n_site = a.n_site;
   // workgroup b takes item b (the plan orders its items longest first, and
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(FisherDims<NPI>::TIDAL ? 2 * kBlock : kBlock) void 
     double t = 0.0;
     // both forms: PN series as sums of products over shared powers and the
     // PSD power law once per point (in FP32 for the mixed form)
-    fisher_sums<NPI, ROT, MIXED, true, false, TAB>(ecg, scg, n_site, k0, k1, L, &t);
+    fisher_sums<NPI, 2, ROT, MIXED, true, false, TAB>(ecg, scg, n_site, k0, k1, L, &t);
     if (tid < NACC) out[tid] = t;
   }
 }

@@ -24,18 +24,14 @@
 
 namespace gwf {
 
-// Declared for 2 x kBlock lanes so that the register budget is that of two
-// wavefronts per SIMD (256 registers); launched with kBlock lanes, two
-// workgroups (about 63 KB of LDS each: 54 KB of FisherLds, the event's
-// 1.1 KB of constants and 6.9 KB for eight sites) then share a compute unit,
-// which hides the latency of the LDS constant reads and of the
+// Two workgroups per compute unit (256 registers; 45 KB of LDS each with
+// tides: 37 KB of FisherLds, the event's 1.1 KB of constants and 6.9 KB for
+// eight sites) hide the latency of the LDS constant reads and of the
 // transcendental sequences.
-// (The P = 11 instantiation keeps the one-wavefront budget: under the
-// two-wavefront cap it spills.)
 static_assert(64 + kMaxSites <= kBlock, "site set-up lanes in the second wavefront");
 
 template <int NPI_, bool ROT, bool EXPL, bool TAB>
-__global__ __launch_bounds__(FisherDims<NPI_>::TIDAL ? 2 * kBlock : kBlock) void fisher_kernel(FisherArgs a) {
+__global__ __launch_bounds__(kBlock, 2) void fisher_kernel(FisherArgs a) {
   using Dm = FisherDims<NPI_>;
   using PO = PhaseOnly<NPI_>;
   constexpr int P = Dm::P, NPI = Dm::NPI, NACC = Dm::NACC;
@@ -43,7 +39,7 @@ __global__ __launch_bounds__(FisherDims<NPI_>::TIDAL ? 2 * kBlock : kBlock) void
 
   __shared__ EventC ec;
   __shared__ SiteC sc[kMaxSites];
-  __shared__ FisherLds L;
+  __shared__ FisherLds<NPI, 1> L;
   __shared__ int32_t skip, bad;
 
   const int64_t e = a.base + blockIdx.x;
@@ -75,7 +71,7 @@ __global__ __launch_bounds__(FisherDims<NPI_>::TIDAL ? 2 * kBlock : kBlock) void
   }
 
   double t = 0.0;
-  fisher_sums<NPI, ROT, false, true, EXPL, TAB>(ec, sc, n_site, 0, ec.n, L, &t);
+  fisher_sums<NPI, 1, ROT, false, true, EXPL, TAB>(ec, sc, n_site, 0, ec.n, L, &t);
   if (tid < NACC) {
     int r, c;
     slot_position(tid, NPI, r, c);

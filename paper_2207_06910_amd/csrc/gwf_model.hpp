@@ -129,16 +129,16 @@ struct SiteC {
   double ct, slct, clst, sl, st;   // cos th, sin lat cos th, cos lat sin th, sin lat, sin th
   double cl;                   // cos lat
   double k1, k0, k1t, k0t;     // Delta = k1 cos H + k0;  dDelta/dth = k1t cos H + k0t
-  double lnx_off, ix_fac, x_fac;  // ln(f/f0) = 3 ln v + lnx_off; f0/f = ix_fac v^-3; f/f0 = x_fac v^3
+  double lnx_off, ix2_fac, x2_fac;  // ln(f/f0) = 3 ln v + lnx_off; (f0/f)^2 = ix2_fac v^-6; (f/f0)^2 = x2_fac v^6
   double xp_fac;               // (f/f0)^-4.14 = xp_fac v^-12.42
   double S0inv;                // 1/S0
-  // S0 times the PSD shape's coefficients (the root weight's form, see
-  // psd_root_weight), and sqrt(1/S0)
+  // S0 times the PSD shape's coefficients of v^-12.42, v^-6 and the rational
+  // part (the root weight's form, see psd_root_weight), and sqrt(1/S0)
   double xpS0, m5S0, k111S0, rS0inv;
   double alpha[2][4], beta[2][4], weff[2];  // effective interferometers (pattern maps)
   // the effective interferometers' F+, Fx and their theta derivatives as
   // trigonometric polynomials in the hour angle H: coefficients of
-  // (1, cos H, sin H, cos 2H, sin 2H), each scaled by sqrt(weff)
+  // (1, cos H, sin H, cos 2H, sin H cos H), each scaled by sqrt(weff)
   double jk[2][4][5];
   double arm_alpha[3][4], arm_beta[3][4];   // individual arms (SNR per interferometer)
   int32_t n_eff, n_arm;
@@ -501,13 +501,13 @@ struct TrigLin {
   double u, v, w;
 };
 
-// Adds k a b to out, the coefficients of (1, cos H, sin H, cos 2H, sin 2H).
+// Adds k a b to out, the coefficients of (1, cos H, sin H, cos 2H, sin H cos H).
 __host__ __device__ inline void trig_mul_add(const TrigLin& a, const TrigLin& b, double k, double out[5]) {
   out[0] += k * fma(a.u, b.u, 0.5 * fma(a.v, b.v, a.w * b.w));
   out[1] += k * fma(a.u, b.v, a.v * b.u);
   out[2] += k * fma(a.u, b.w, a.w * b.u);
   out[3] += k * 0.5 * fma(a.v, b.v, -a.w * b.w);
-  out[4] += k * 0.5 * fma(a.v, b.w, a.w * b.v);
+  out[4] += k * fma(a.v, b.w, a.w * b.v);
 }
 
 // The pattern vector P(H) of site_point and its theta derivative as
@@ -578,11 +578,12 @@ __host__ __device__ inline void site_setup(const double* p, const SiteDesc& sd, 
   sc.k0t = kREarthS * sl * st;
   sc.lnx_off = -log(piM) - log(sd.f0);
   sc.xp_fac = exp(-4.14 * sc.lnx_off);
-  sc.ix_fac = sd.f0 * piM;
-  sc.x_fac = 1.0 / sc.ix_fac;
+  const double ix_fac = sd.f0 * piM;          // f0/f = ix_fac v^-3
+  sc.ix2_fac = ix_fac * ix_fac;
+  sc.x2_fac = 1.0 / sc.ix2_fac;
   sc.S0inv = 1.0 / sd.S0;
   sc.xpS0 = sd.S0 * sc.xp_fac;
-  sc.m5S0 = -5.0 * sd.S0;
+  sc.m5S0 = -5.0 * sd.S0 * sc.ix2_fac;
   sc.k111S0 = 111.0 * sd.S0;
   sc.rS0inv = sqrt(sc.S0inv);
   sc.tab_f = sd.tab_f;
@@ -742,20 +743,27 @@ __host__ __device__ inline void vpow(double v, double L, VPow& w) {
   w.Lv = L * v;
 }
 
-// c0 + c1 v + ... + c7 v^7 as a sum of products with the powers, lowest
-// order first and c0 last.  Each fused multiply-add keeps the running sum as
+// c0 + c2 v^2 + ... + c7 v^7 as a sum of products with the powers, lowest
+// order first and c0 last (no series has a term c1 v: there is no 0.5PN
+// order); FIRST = 2 for a series without c0 as well, 3 for one that starts
+// at c3 v^3, where c0 and c2 are zero by construction too.  Each fused multiply-add keeps the running sum as
 // its addend, so per-event coefficients held in scalar registers enter every
 // step directly (a Horner recurrence makes the coefficient the addend, which
 // costs two register copies per step on this ISA).
+template <int FIRST = 0>
 __host__ __device__ inline double series7(const double c[8], const VPow& w) {
-  double h = c[1] * w.p1;
-  h = fma(c[2], w.p2, h);
-  h = fma(c[3], w.p3, h);
+  double h;
+  if (FIRST == 3) {
+    h = c[3] * w.p3;
+  } else {
+    h = c[2] * w.p2;
+    h = fma(c[3], w.p3, h);
+  }
   h = fma(c[4], w.p4, h);
   h = fma(c[5], w.p5, h);
   h = fma(c[6], w.p6, h);
   h = fma(c[7], w.p7, h);
-  return h + c[0];
+  return FIRST == 0 ? h + c[0] : h;
 }
 
 // The same polynomial by Horner's rule, which keeps fewer values live than
@@ -768,9 +776,9 @@ __host__ __device__ inline double horner7(const double c[8], double v) {
   for (int k = 6; k >= 0; --k) h = fma(h, v, c[k]);
   return h;
 }
-template <bool PSUM>
+template <bool PSUM, int FIRST = 0>
 __host__ __device__ inline double poly7(const double c[8], const VPow& w) {
-  return PSUM ? series7(c, w) : horner7(c, w.p1);
+  return PSUM ? series7<FIRST>(c, w) : horner7(c, w.p1);
 }
 
 // A phase series (PhaseSeries) at v: v^-5 (sum c_k v^k) + (l5 + l6 v) ln v
@@ -780,19 +788,29 @@ __host__ __device__ inline double eval_phase(const PhaseSeries& s, const VPow& w
   const double rest = fma(s.l6, w.Lv, fma(s.l5, w.L, fma(s.t12, w.p7, s.t10 * w.p5)));
   return fma(poly7<PSUM>(s.c, w), iv5, rest);
 }
-// The spin series, whose l6, t10 and t12 are zero by construction.
+// The Mc series, whose l5 is zero, the eta series, whose c0 is (at fixed Mc
+// the leading order does not depend on eta), and the spin series, which
+// start at 1.5PN and whose l6, t10 and t12 are zero, all by construction.
+__host__ __device__ inline double eval_phase_mc(const PhaseSeries& s, const VPow& w, double iv5) {
+  return fma(series7(s.c, w), iv5, fma(s.l6, w.Lv, fma(s.t12, w.p7, s.t10 * w.p5)));
+}
+__host__ __device__ inline double eval_phase_eta(const PhaseSeries& s, const VPow& w, double iv5) {
+  const double rest = fma(s.l6, w.Lv, fma(s.l5, w.L, fma(s.t12, w.p7, s.t10 * w.p5)));
+  return fma(series7<2>(s.c, w), iv5, rest);
+}
 template <bool PSUM = true>
 __host__ __device__ inline double eval_phase_spin(const PhaseSeries& s, const VPow& w, double iv5) {
-  return fma(poly7<PSUM>(s.c, w), iv5, s.l5 * w.L);
+  return fma(poly7<PSUM, 3>(s.c, w), iv5, s.l5 * w.L);
 }
 // The deformability series, which only have the tidal terms.
 __host__ __device__ inline double eval_phase_tidal(const PhaseSeries& s, const VPow& w) {
   return fma(s.t12, w.p7, s.t10 * w.p5);
 }
-// A tau*-type series at v: v^-8 (sum c_k v^k) + l6 ln v v^-2.
-template <bool PSUM = true>
+// A tau*-type series at v: v^-8 (sum c_k v^k) + l6 ln v v^-2 (FIRST = 2: the
+// eta series, whose c0 is zero as that of the phase).
+template <bool PSUM = true, int FIRST = 0>
 __host__ __device__ inline double eval_tau(const TauSeries& s, const VPow& w, double iv8, double iv2) {
-  return fma(poly7<PSUM>(s.c, w), iv8, s.l6 * (w.L * iv2));
+  return fma(poly7<PSUM, FIRST>(s.c, w), iv8, s.l6 * (w.L * iv2));
 }
 
 // Frequency-point quantities shared by all sites.
@@ -803,7 +821,7 @@ struct Point {
   double gMc, gEta;               // d(sidereal angle)/dMc, /deta
   double pMc, pEta;               // dPsi_PN/dMc, /deta
   double vpsd;                    // v^-12.42: the PSD's power law, shared by all sites
-  double v3, iv3;                 // v^3 and v^-3 (proportional to f and 1/f), shared by all sites
+  double v6, iv6;                 // v^6 and v^-6 (proportional to f^2 and f^-2), shared by all sites
   double ecv;                     // v^-5 (v_ref/v)^{19/3} (eccentric forms, else 0)
 };
 
@@ -816,14 +834,19 @@ struct Point {
 // 16384-point work item walked by 256 lanes, far inside the Fisher and SNR
 // tolerances, for three multiplications per point instead of two
 // exponentials and a reciprocal.
+__host__ __device__ inline void grid_values(const EventC& ec, int32_t k, double* val) {
+  const double L = fma((double)k, ec.dlnv, ec.lnv0);
+  val[0] = exp(L);
+  val[1] = exp(-L);
+  val[2] = exp(-12.42 * L);
+}
+
 struct GridWalk {
   double val[3];      // v, 1/v, v^-12.42 at the current point
   double ratio[3];
   __host__ __device__ inline void start(const EventC& ec, int32_t k, int32_t stride) {
-    const double L = fma((double)k, ec.dlnv, ec.lnv0), D = (double)stride * ec.dlnv;
-    val[0] = exp(L);
-    val[1] = exp(-L);
-    val[2] = exp(-12.42 * L);
+    const double D = (double)stride * ec.dlnv;
+    grid_values(ec, k, val);
     ratio[0] = exp(D);
     ratio[1] = exp(-D);
     ratio[2] = exp(-12.42 * D);
@@ -834,12 +857,7 @@ struct GridWalk {
     val[2] *= ratio[2];
   }
   // the values at point k evaluated directly again (ratios kept)
-  __host__ __device__ inline void anchor(const EventC& ec, int32_t k) {
-    const double L = fma((double)k, ec.dlnv, ec.lnv0);
-    val[0] = exp(L);
-    val[1] = exp(-L);
-    val[2] = exp(-12.42 * L);
-  }
+  __host__ __device__ inline void anchor(const EventC& ec, int32_t k) { grid_values(ec, k, val); }
 };
 
 // Number of phase-only Fisher parameters (Phic, chi1z, chi2z, then Lambda1,
@@ -856,14 +874,43 @@ struct PhaseOnly {
 // not at all, in FP64, or in FP32 (the mixed form's weight).
 enum PsdPow { kPsdNone = 0, kPsdF64 = 1, kPsdF32 = 2 };
 
+// Keeps the compiler from turning the uniform branch it stands in into
+// selects that every lane pays for.
+__host__ __device__ inline void keep_branch() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __asm__ volatile("");
+#endif
+}
+
+// The point's derivatives of the PN phase and of the sidereal angle with
+// respect to Mc and eta, from the v, 1/v and ln v of point_setup.
+template <bool ECC>
+__host__ __device__ inline void point_derivatives(const EventC& ec, bool rot, Point& q) {
+  const double iv2 = q.iv * q.iv, iv4 = iv2 * iv2, iv5 = iv4 * q.iv, iv8 = iv4 * iv4;
+  VPow pw;
+  vpow(q.v, q.L, pw);
+  q.gMc = rot ? eval_tau(ec.ts[kTsMc], pw, iv8, iv2) : 0.0;
+  q.gEta = rot ? eval_tau<true, 2>(ec.ts[kTsEta], pw, iv8, iv2) : 0.0;
+  q.pMc = eval_phase_mc(ec.ps[kPsMc], pw, iv5);
+  q.pEta = eval_phase_eta(ec.ps[kPsEta], pw, iv5);
+  q.ecv = 0.0;
+  if (ECC) {
+    q.ecv = iv5 * exp((19.0 / 3.0) * (ec.ecc_lnvr - q.L));
+    q.pMc = fma(ec.ecc_mc, q.ecv, q.pMc);
+  }
+}
+
 // PSUM: the evaluation form of the PN series (see horner7) and of the PSD's
 // power law (once per point when true, once per site otherwise).
 // EXPL: the point of an explicit grid (ec.fx) rather than of the log grid.
 // vrec (log grids only, NULL: evaluate directly): v, 1/v and v^-12.42 at the
 // point, carried by the caller from an earlier point (see GridWalk).
+// inner: the caller knows that k is neither end of the grid (a uniform value,
+// so that the end weights cost a wavefront inside the grid nothing).
 template <bool PSUM = true, bool EXPL = false, bool ECC = false>
 __host__ __device__ inline void point_setup(const EventC& ec, int32_t k, bool need_derivs, bool rot,
-                                            Point& q, int psd = kPsdF64, const double* vrec = nullptr) {
+                                            Point& q, int psd = kPsdF64, const double* vrec = nullptr,
+                                            bool inner = false) {
   double L, v, f, wf;               // wf: the trapezoid weight
   double rwe = 0.0;                 // log grid: sqrt(w KA4 / (pi M)) of the point's weight
   if (EXPL) {
@@ -877,21 +924,25 @@ __host__ __device__ inline void point_setup(const EventC& ec, int32_t k, bool ne
     f = (v * v * v) * ec.inv_piM;
     double w = ec.wint;
     rwe = ec.rwint;
-    if (k == 0) {
-      w = ec.wfirst;
-      rwe = ec.rwfirst;
-    }
-    if (k == ec.n - 1) {
-      w = ec.wlast;
-      rwe = ec.rwlast;
+    if (!inner) {
+      keep_branch();
+      if (k == 0) {
+        w = ec.wfirst;
+        rwe = ec.rwfirst;
+      }
+      if (k == ec.n - 1) {
+        w = ec.wlast;
+        rwe = ec.rwlast;
+      }
     }
     wf = w * f;
   }
   const double iv = (!EXPL && vrec) ? vrec[1] : recip(v);
   const double iv2 = iv * iv, iv4 = iv2 * iv2, iv5 = iv4 * iv, iv7 = iv5 * iv2, iv8 = iv4 * iv4;
   q.v = v; q.iv = iv; q.L = L; q.f = f;
-  q.v3 = v * v * v;
-  q.iv3 = iv2 * iv;
+  const double v3 = v * v * v;
+  q.v6 = v3 * v3;
+  q.iv6 = iv4 * iv2;
   q.tf = kTwoPi * f;
   q.w4A2 = wf * ec.KA4 * iv7;
   q.rw = EXPL ? sqrt(q.w4A2) : rwe * iv2;
@@ -908,17 +959,7 @@ __host__ __device__ inline void point_setup(const EventC& ec, int32_t k, bool ne
   vpow(v, L, pw);
   const double th = rot ? ec.thc + eval_tau<PSUM>(ec.ts[kTsTheta], pw, iv8, iv2) : ec.thc;
   sincos_moderate(th, &q.sth, &q.cth);
-  if (need_derivs) {
-    q.gMc = rot ? eval_tau<PSUM>(ec.ts[kTsMc], pw, iv8, iv2) : 0.0;
-    q.gEta = rot ? eval_tau<PSUM>(ec.ts[kTsEta], pw, iv8, iv2) : 0.0;
-    q.pMc = eval_phase<PSUM>(ec.ps[kPsMc], pw, iv5);
-    q.pEta = eval_phase<PSUM>(ec.ps[kPsEta], pw, iv5);
-  }
-  q.ecv = 0.0;
-  if (ECC) {
-    q.ecv = iv5 * exp((19.0 / 3.0) * (ec.ecc_lnvr - L));
-    if (need_derivs) q.pMc = fma(ec.ecc_mc, q.ecv, q.pMc);
-  }
+  if (need_derivs) point_derivatives<ECC>(ec, rot, q);
 }
 
 // The phase-only derivative coefficients of a point: c = (-1, dPsi/dchi1,
@@ -957,16 +998,14 @@ struct SitePoint {
 };
 
 template <bool PSUM = true>
-__host__ __device__ inline double psd_weight_of(double xp_fac, double lnx_off, double ix_fac,
-                                                double x_fac, double S0inv, const Point& q) {
+__host__ __device__ inline double psd_weight_of(double xp_fac, double lnx_off, double ix2_fac,
+                                                double x2_fac, double S0inv, const Point& q) {
   // S_n = S0 [x^-4.14 - 5 x^-2 + 111 (1 - x^2 + x^4/2)/(1 + x^2/2)], x = f/f0;
   // x^-4.14 = xp_fac v^-12.42 with the power of v evaluated once per point
   // (PSUM), or exp(-4.14 ln x) here
   const double xp = PSUM ? xp_fac * q.vpsd : exp(-4.14 * fma(3.0, q.L, lnx_off));
-  const double ix = ix_fac * q.iv3;                // f0/f
-  const double x = x_fac * q.v3;                   // f/f0
-  const double ix2 = ix * ix;
-  const double x2 = x * x;
+  const double ix2 = ix2_fac * q.iv6;              // (f0/f)^2
+  const double x2 = x2_fac * q.v6;                 // (f/f0)^2
   const double num = fma(0.5 * x2, x2, 1.0 - x2);
   const double den = fma(0.5, x2, 1.0);
   // shape = [(x^-4.14 - 5 x^-2) den + 111 num] / den
@@ -1004,7 +1043,7 @@ __host__ __device__ inline double table_weight(const double* __restrict__ tf, co
 template <bool PSUM = true, bool TAB = true>
 __host__ __device__ inline void psd_weight(const SiteC& sc, const Point& q, double& om) {
   if (TAB && sc.tab_kind) om = table_weight(sc.tab_f, sc.tab_S, sc.tab_n, sc.tab_kind, sc.S0inv, q.w4A2, q.f);
-  else om = psd_weight_of<PSUM>(sc.xp_fac, sc.lnx_off, sc.ix_fac, sc.x_fac, sc.S0inv, q);
+  else om = psd_weight_of<PSUM>(sc.xp_fac, sc.lnx_off, sc.ix2_fac, sc.x2_fac, sc.S0inv, q);
 }
 
 // The same weight with the PSD shape evaluated in FP32 (mixed form).  The
@@ -1025,8 +1064,7 @@ __host__ __device__ inline void psd_weight_f32(const SiteC& sc, const Point& q, 
     return;
   }
   const float xp = (float)(sc.xp_fac * q.vpsd);
-  const double x = sc.x_fac * q.v3, ix = sc.ix_fac * q.iv3;
-  const float x2 = (float)(x * x), ix2 = (float)(ix * ix);
+  const float x2 = (float)(sc.x2_fac * q.v6), ix2 = (float)(sc.ix2_fac * q.iv6);
   const float num = fmaf(0.5f * x2, x2, 1.0f - x2);
   const float den = fmaf(0.5f, x2, 1.0f);
   const float top = fmaf(fmaf(-5.0f, ix2, xp), den, 111.0f * num);
@@ -1049,13 +1087,10 @@ __host__ __device__ inline double psd_root_weight(const SiteC& sc, const Point& 
     psd_weight<PSUM, TAB>(sc, q, om);
     return sqrt(om);
   }
-  const double ix = sc.ix_fac * q.iv3;             // f0/f
-  const double x = sc.x_fac * q.v3;                // f/f0
-  const double ix2 = ix * ix;
-  const double x2 = x * x;
-  const double num = fma(0.5 * x2, x2, 1.0 - x2);
+  const double x2 = sc.x2_fac * q.v6;              // (f/f0)^2
+  const double num = fma(fma(0.5, x2, -1.0), x2, 1.0);
   const double den = fma(0.5, x2, 1.0);
-  const double topS = fma(fma(sc.m5S0, ix2, sc.xpS0 * q.vpsd), den, sc.k111S0 * num);
+  const double topS = fma(fma(sc.m5S0, q.iv6, sc.xpS0 * q.vpsd), den, sc.k111S0 * num);
   return (q.rw * den) * rsqrt_d(den * topS);
 }
 
@@ -1069,8 +1104,7 @@ __host__ __device__ inline double psd_root_weight_f32(const SiteC& sc, const Poi
   if (TAB && sc.tab_kind)
     return sqrt(table_weight(sc.tab_f, sc.tab_S, sc.tab_n, sc.tab_kind, sc.S0inv, q.w4A2, q.f));
   const float xp = (float)(sc.xp_fac * q.vpsd);
-  const double x = sc.x_fac * q.v3, ix = sc.ix_fac * q.iv3;
-  const float x2 = (float)(x * x), ix2 = (float)(ix * ix);
+  const float x2 = (float)(sc.x2_fac * q.v6), ix2 = (float)(sc.ix2_fac * q.iv6);
   const float num = fmaf(0.5f * x2, x2, 1.0f - x2);
   const float den = fmaf(0.5f, x2, 1.0f);
   const float top = fmaf(fmaf(-5.0f, ix2, xp), den, 111.0f * num);
@@ -1106,10 +1140,11 @@ __host__ __device__ inline void site_point(const SiteC& sc, const Point& q, bool
 
 // Site-level quantities of the Fisher kernels at one frequency for the
 // trigonometric form of the patterns (SiteC::jk): cos H, sin H, cos 2H,
-// sin 2H and the factors 2 cos 2H, -2 sin 2H of the H derivatives; the
-// arrival-time derivatives and the noise weight.
+// sin H cos H and the factor -4 sin H cos H of the cos 2H term's H derivative
+// (that of sin H cos H is cos 2H); the arrival-time derivatives and the noise
+// weight.
 struct SiteTrig {
-  double cH, sH, c2H, s2H, p2c, m2s;
+  double cH, sH, c2H, sc, m4;
   double dH, dT;      // dDelta/dH, dDelta/dtheta
   double om;          // 4 w A^2 / S_n(f)
 };
@@ -1121,9 +1156,8 @@ __host__ __device__ inline void site_trig(const SiteC& sc, const Point& q, SiteT
   sp.cH = cH;
   sp.sH = sH;
   sp.c2H = fma(cH, cH, -sH * sH);
-  sp.s2H = 2.0 * (sH * cH);
-  sp.p2c = 2.0 * sp.c2H;
-  sp.m2s = -2.0 * sp.s2H;
+  sp.sc = sH * cH;
+  sp.m4 = -4.0 * sp.sc;
   if (MIXED) psd_weight_f32<TAB>(sc, q, sp.om);
   else psd_weight<PSUM, TAB>(sc, q, sp.om);
   sp.dH = -sc.k1 * sH;
@@ -1136,9 +1170,9 @@ __host__ __device__ inline void site_trig(const SiteC& sc, const Point& q, SiteT
 // sin H themselves for the arrival-time derivatives.
 struct SiteTrigR {
   double cH, sH;
-  double r, rc, rs, rc2, rs2;   // r (1, cos H, sin H, cos 2H, sin 2H)
-  double p2c, m2s;              // r (2 cos 2H, -2 sin 2H)
-  double dH, dT;                // dDelta/dH, dDelta/dtheta
+  double r, rc, rs, rc2, rsc;   // r (1, cos H, sin H, cos 2H, sin H cos H)
+  double rm4;                   // -4 r sin H cos H
+  double u, w;                  // 2 pi f dDelta/dH, 2 pi f dDelta/dtheta
 };
 
 template <bool MIXED = false, bool PSUM = true, bool TAB = true>
@@ -1152,30 +1186,29 @@ __host__ __device__ inline void site_trig_root(const SiteC& sc, const Point& q, 
   sp.rc = r * cH;
   sp.rs = r * sH;
   sp.rc2 = fma(sp.rc, cH, -sp.rs * sH);
-  sp.rs2 = 2.0 * (sp.rs * cH);
-  sp.p2c = 2.0 * sp.rc2;
-  sp.m2s = -2.0 * sp.rs2;
-  sp.dH = -sc.k1 * sH;
-  sp.dT = fma(sc.k1t, cH, sc.k0t);
+  sp.rsc = sp.rs * cH;
+  sp.rm4 = -4.0 * sp.rsc;
+  sp.u = q.tf * (-sc.k1 * sH);
+  sp.w = fma(q.tf, sc.k1t * cH, q.tf * sc.k0t);
 }
 
 // r times a trigonometric polynomial of SiteC::jk, and r times its H
 // derivative (the constant term last, as in trig_val).
 __host__ __device__ inline double trig_val_r(const double c[5], const SiteTrigR& sp) {
-  return fma(c[0], sp.r, fma(c[4], sp.rs2, fma(c[3], sp.rc2, fma(c[2], sp.rs, c[1] * sp.rc))));
+  return fma(c[0], sp.r, fma(c[4], sp.rsc, fma(c[3], sp.rc2, fma(c[2], sp.rs, c[1] * sp.rc))));
 }
 __host__ __device__ inline double trig_dH_r(const double c[5], const SiteTrigR& sp) {
-  return fma(c[4], sp.p2c, fma(c[3], sp.m2s, fma(c[2], sp.rc, -c[1] * sp.rs)));
+  return fma(c[4], sp.rc2, fma(c[3], sp.rm4, fma(c[2], sp.rc, -c[1] * sp.rs)));
 }
 
 // A trigonometric polynomial of SiteC::jk at the point, and its H derivative.
 // The constant term is added last: the coefficients sit in scalar registers,
 // and as the first addend it would need copying into vector registers.
 __host__ __device__ inline double trig_val(const double c[5], const SiteTrig& sp) {
-  return fma(c[4], sp.s2H, fma(c[3], sp.c2H, fma(c[2], sp.sH, c[1] * sp.cH))) + c[0];
+  return fma(c[4], sp.sc, fma(c[3], sp.c2H, fma(c[2], sp.sH, c[1] * sp.cH))) + c[0];
 }
 __host__ __device__ inline double trig_dH(const double c[5], const SiteTrig& sp) {
-  return fma(c[4], sp.p2c, fma(c[3], sp.m2s, fma(c[2], sp.cH, -c[1] * sp.sH)));
+  return fma(c[4], sp.c2H, fma(c[3], sp.m4, fma(c[2], sp.cH, -c[1] * sp.sH)));
 }
 
 __host__ __device__ inline double dot4(const double a[4], const double b[4]) {
@@ -1235,96 +1268,260 @@ __host__ __device__ inline void derivative_vector(const AmpFactors& am, const Po
   Di[7] = fma(kOmegaE, QHi, Qr * ph.tc);
 }
 
-// ------------------------------------------------ one frequency point
-// The rows of dL, iota and psi are fixed per-event combinations of the
-// pattern values (F+, Fx) of each interferometer:
-//   D_dL = -Q/dL,  D_iota = (dc+ F+, dcx Fx),  D_psi = (2 c+ Fx, -2 cx F+),
-// with Q = (c+ F+, cx Fx) and (re, im) pairs.  So every Fisher entry in
-// those rows is a combination of the moments
-//   T_b = sum w (F+ Dr_b, F+ Di_b, Fx Dr_b, Fx Di_b)   for the other rows b
-//   S   = sum w (F+^2, F+ Fx, Fx^2),
-// and only the 5x5 block of (Mc, eta, theta, phi, tc) needs a rank-2 update
-// per interferometer.  The accumulator G[kGramAcc] holds that block's upper
-// triangle (15, row-major), then T (4 per row, in the order above), then S;
-// gram_finish turns it into the 8x8 block.
-constexpr int kGramAcc = 15 + 20 + 3;
-constexpr int kGramRows[5] = {0, 1, 3, 4, 7};   // Mc, eta, theta, phi, tc
+// Marks v and 1/v as unknown to the compiler, so that their powers are formed
+// again where they are needed next instead of being held in registers.
+__host__ __device__ inline void reread(double& v, double& iv) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __asm__("" : "+v"(v), "+v"(iv));
+#endif
+}
 
-// Adds the contribution of grid point k of an event to G[kGramAcc] (above)
-// and returns the point's phase-only quantities:
+// ------------------------------------------------ one frequency point
+// With Q = (c+ F+, cx Fx) and its hour-angle and theta derivatives Q_H, Q_t as
+// (re, im) pairs, u = 2 pi f dDelta/dH and w = 2 pi f dDelta/dtheta, put
+//   Z = Q_H + i u Q,   Y = Q_t + i w Q.
+// Then the derivative vectors of every interferometer are combinations of Q,
+// iQ, Z and Y with coefficients that no site or interferometer changes:
+//   D_Mc = dlnA Q + gMc Z + pMc iQ,   D_eta = gEta Z + pEta iQ,
+//   D_theta = Y,   D_phi = -Z,   D_tc = Omega Z + 2 pi f iQ,
+//   D_dL = -Q/dL,  D_iota = (dc+ F+, dcx Fx),  D_psi = (2 c+ Fx, -2 cx F+)
+// (the phase derivatives' shares of the delay sit in Z and Y).  So a point's
+// whole 8x8 block follows from 14 sums over its interferometers (NetSums): the
+// loop over them takes 17 multiply-adds each instead of the 63 of a rank-2
+// update of the five rows and their pattern moments, and the coefficients are
+// applied once per point.
+struct NetSums {
+  double spp, spx, sxx;                // F+^2, F+ Fx, Fx^2
+  double pzr, pzi, xzr, xzi;           // (F+, Fx) x (Re Z, Im Z)
+  double pyr, pyi, xyr, xyi;           // (F+, Fx) x (Re Y, Im Y)
+  double zz, yy, zy;                   // |Z|^2, |Y|^2, Re(Z Y^*)
+};
+
+// Adds one site's n_eff = 1 or 2 effective interferometers to the sums of NQ
+// points (of one event).  The patterns are trigonometric polynomials in H whose coefficients carry
+// sqrt(weff), and the basis carries the root weight r, so every product of
+// two of the values below is weighted by weff r^2.
+template <int NQ, bool MIXED = false, bool PSUM = true, bool TAB = true>
+__host__ __device__ inline void site_sums(const AmpFactors& am, const Point (&q)[NQ], const SiteC& st, int n_eff,
+                                          NetSums (&net)[NQ]) {
+  SiteTrigR sp[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) site_trig_root<MIXED, PSUM, TAB>(st, q[i], sp[i]);
+  int j = 0;
+  do {
+    const double(*c)[5] = st.jk[j];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      NetSums& n = net[i];
+      const double Fp = trig_val_r(c[0], sp[i]), Fx = trig_val_r(c[1], sp[i]);
+      const double Qr = am.cplus * Fp, Qi = am.ccross * Fx;
+      const double Zr = fma(am.cplus, trig_dH_r(c[0], sp[i]), -sp[i].u * Qi);
+      const double Zi = fma(am.ccross, trig_dH_r(c[1], sp[i]), sp[i].u * Qr);
+      const double Yr = fma(am.cplus, trig_val_r(c[2], sp[i]), -sp[i].w * Qi);
+      const double Yi = fma(am.ccross, trig_val_r(c[3], sp[i]), sp[i].w * Qr);
+      n.spp = fma(Fp, Fp, n.spp);
+      n.spx = fma(Fp, Fx, n.spx);
+      n.sxx = fma(Fx, Fx, n.sxx);
+      n.pzr = fma(Fp, Zr, n.pzr);
+      n.pzi = fma(Fp, Zi, n.pzi);
+      n.xzr = fma(Fx, Zr, n.xzr);
+      n.xzi = fma(Fx, Zi, n.xzi);
+      n.pyr = fma(Fp, Yr, n.pyr);
+      n.pyi = fma(Fp, Yi, n.pyi);
+      n.xyr = fma(Fx, Yr, n.xyr);
+      n.xyi = fma(Fx, Yi, n.xyi);
+      n.zz = fma(Zr, Zr, fma(Zi, Zi, n.zz));
+      n.yy = fma(Yr, Yr, fma(Yi, Yi, n.yy));
+      n.zy = fma(Zr, Yr, fma(Zi, Yi, n.zy));
+    }
+  } while (++j < n_eff);
+}
+
+// Slots of the accumulator G[kGramAcc]: the sums over points of
+//   the pattern products S, the products of (F+, Fx) with Z and with Y;
+//   2 pi f times W = |Q|^2, U_iota and U_psi;
+//   for b = Mc and eta, with D'_b = D_b - dlnA_b Q: U_b = Re(iQ D'_b^*),
+//   g_b Re(Q Z^*), Re(D_iota D'_b^*), Re(D_psi D'_b^*);
+//   the products of D'_Mc, D'_eta, Y, Z and 2 pi f iQ among each other.
+enum {
+  kGSpp = 0, kGSpx, kGSxx, kGPzr, kGPzi, kGXzr, kGXzi, kGPyr, kGPyi, kGXyr, kGXyi, kGTW, kGTI, kGTP,
+  kGMu, kGMd, kGMi, kGMp, kGEu, kGEd, kGEi, kGEp,
+  kGMM, kGME, kGEE, kGMY, kGEY, kGMZ, kGEZ, kGMt, kGEt, kGYY, kGZY, kGZZ, kGtY, kGtZ, kGtt,
+  kGramAcc
+};
+
+// Adds a point's sums n to G[kGramAcc] and returns its phase-only quantities:
 //   U[8]   U_b = sum_i w_i Re(i Q_i D_b,i^*)
-//   W      sum_i w_i |Q_i|^2 (the SNR^2 density)
-//   c[NPI] (-1, dPsi/dchi1, dPsi/dchi2[, dPsi/dLambda1, dPsi/dLambda2][, dPsi/de0]).
+//   W      sum_i w_i |Q_i|^2 (the SNR^2 density).
 // The phase-only derivative vectors are i Q c(f) with the same real c(f) at
 // every interferometer, so the blocks they span are
 //   Gamma_{b, 8+i} += U_b c_i,   Gamma_{8+i, 8+j} += W c_i c_j,
-// which the caller accumulates (see add_phase_blocks).  U and W of the rows
-// dL, iota, psi follow from the point's moments S as well: U_dL = 0
-// exactly, U_iota = (c+ dcx - cx dc+) S_+x, U_psi = -2 c+ cx (S_++ + S_xx),
-// W = c+^2 S_++ + cx^2 S_xx.
+// which the caller accumulates (see add_phase_blocks).
+template <bool ROT>
+__host__ __device__ inline void accumulate_sums(const EventC& ec, const Point& q, const NetSums& n, double* G,
+                                                double* U, double& W) {
+  const AmpFactors am = amp_factors(ec);
+  const double pm = q.pMc, pe = q.pEta, gm = q.gMc, ge = q.gEta, tf = q.tf;
+  G[kGSpp] += n.spp;
+  G[kGSpx] += n.spx;
+  G[kGSxx] += n.sxx;
+  G[kGPzr] += n.pzr;
+  G[kGPzi] += n.pzi;
+  G[kGXzr] += n.xzr;
+  G[kGXzi] += n.xzi;
+  G[kGPyr] += n.pyr;
+  G[kGPyi] += n.pyi;
+  G[kGXyr] += n.xyr;
+  G[kGXyi] += n.xyi;
+  G[kGYY] += n.yy;
+  G[kGZY] += n.zy;
+  G[kGZZ] += n.zz;
+  W = fma(ec.cp2, n.spp, ec.cx2 * n.sxx);
+  const double ui = ec.u_iota * n.spx, up = ec.u_psi * (n.spp + n.sxx);
+  const double iqz = fma(am.cplus, n.pzi, -am.ccross * n.xzr);    // Re(iQ Z^*)
+  const double iqy = fma(am.cplus, n.pyi, -am.ccross * n.xyr);    // Re(iQ Y^*)
+  const double tW = tf * W;
+  G[kGTW] += tW;
+  G[kGTI] = fma(tf, ui, G[kGTI]);
+  G[kGTP] = fma(tf, up, G[kGTP]);
+  G[kGtY] = fma(tf, iqy, G[kGtY]);
+  G[kGtZ] = fma(tf, iqz, G[kGtZ]);
+  G[kGtt] = fma(tf, tW, G[kGtt]);
+  double mu, eu, mz, ez;               // Re(iQ D'^*), Re(Z D'^*) of D'_Mc and D'_eta
+  if (ROT) {
+    const double qz = fma(am.cplus, n.pzr, am.ccross * n.xzi);             // Re(Q Z^*)
+    const double iz = fma(am.dcp, n.pzr, am.dcx * n.xzi);                  // Re(D_iota Z^*)
+    const double pz = 2.0 * fma(am.cplus, n.xzr, -am.ccross * n.pzi);      // Re(D_psi Z^*)
+    mu = fma(pm, W, gm * iqz);
+    eu = fma(pe, W, ge * iqz);
+    mz = fma(pm, iqz, gm * n.zz);
+    ez = fma(pe, iqz, ge * n.zz);
+    G[kGMd] = fma(gm, qz, G[kGMd]);
+    G[kGMi] = fma(pm, ui, fma(gm, iz, G[kGMi]));
+    G[kGMp] = fma(pm, up, fma(gm, pz, G[kGMp]));
+    G[kGEd] = fma(ge, qz, G[kGEd]);
+    G[kGEi] = fma(pe, ui, fma(ge, iz, G[kGEi]));
+    G[kGEp] = fma(pe, up, fma(ge, pz, G[kGEp]));
+    G[kGMM] = fma(pm, mu, fma(gm, mz, G[kGMM]));
+    G[kGME] = fma(pe, mu, fma(ge, mz, G[kGME]));
+    G[kGEE] = fma(pe, eu, fma(ge, ez, G[kGEE]));
+    G[kGMY] = fma(pm, iqy, fma(gm, n.zy, G[kGMY]));
+    G[kGEY] = fma(pe, iqy, fma(ge, n.zy, G[kGEY]));
+  } else {                             // the sidereal angle does not move: gMc = gEta = 0
+    mu = pm * W;
+    eu = pe * W;
+    mz = pm * iqz;
+    ez = pe * iqz;
+    G[kGMi] = fma(pm, ui, G[kGMi]);
+    G[kGMp] = fma(pm, up, G[kGMp]);
+    G[kGEi] = fma(pe, ui, G[kGEi]);
+    G[kGEp] = fma(pe, up, G[kGEp]);
+    G[kGMM] = fma(pm, mu, G[kGMM]);
+    G[kGME] = fma(pe, mu, G[kGME]);
+    G[kGEE] = fma(pe, eu, G[kGEE]);
+    G[kGMY] = fma(pm, iqy, G[kGMY]);
+    G[kGEY] = fma(pe, iqy, G[kGEY]);
+  }
+  G[kGMu] += mu;
+  G[kGEu] += eu;
+  G[kGMZ] += mz;
+  G[kGEZ] += ez;
+  G[kGMt] = fma(tf, mu, G[kGMt]);
+  G[kGEt] = fma(tf, eu, G[kGEt]);
+  U[0] = mu;
+  U[1] = eu;
+  U[2] = 0.0;
+  U[3] = iqy;
+  U[4] = -iqz;
+  U[5] = ui;
+  U[6] = up;
+  U[7] = fma(kOmegaE, iqz, tW);
+}
+
+// The sites of an event that have an interferometer on, in order: four bits
+// each, the site's number and (bit 3) whether it has two effective ones.
+struct ActiveSites {
+  uint32_t list;
+  int32_t n;
+};
+
+__host__ __device__ inline ActiveSites active_sites(const SiteC* sc, int n_site) {
+  ActiveSites a{0u, 0};
+  for (int s = 0; s < n_site; ++s)
+    if (sc[s].n_eff > 0) {
+      a.list |= ((uint32_t)s | (sc[s].n_eff > 1 ? 8u : 0u)) << (4 * a.n);
+      ++a.n;
+    }
+  return a;
+}
+
+// The sums over the network's interferometers at NQ points k, k + stride, ...
+// of an event (q, net), from the grid values vrec[NQ][3] of those points
+// (NULL: evaluated directly).  Points at or past kend stand for the point
+// kend - 1 (whose grid values the caller gives) and get zero weight; inner
+// says that no point is an end of the grid or past kend.  This part needs the
+// points' grid values and sidereal angle only; the phase and angle
+// derivatives follow it (finish_point), so that they and the sums are not
+// held at the same time as the sites' values.
+template <int NQ, int NPI, bool ROT, bool MIXED, bool PSUM, bool EXPL, bool TAB>
+__host__ __device__ inline void network_sums(const EventC& ec, const SiteC* sc, const ActiveSites& act, int32_t k,
+                                             int32_t stride, int32_t kend, bool inner, const double (*vrec)[3],
+                                             Point (&q)[NQ], NetSums (&net)[NQ]) {
+  const AmpFactors am = amp_factors(ec);
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    int32_t ki = k + i * stride;
+    if (!inner) {
+      keep_branch();
+      if (ki >= kend) ki = kend - 1;
+    }
+    point_setup<PSUM, EXPL, PhaseOnly<NPI>::ecc>(ec, ki, false, ROT, q[i], MIXED ? kPsdF32 : kPsdF64,
+                                                 vrec ? vrec[i] : nullptr, inner);
+    if (!inner) {
+      keep_branch();
+      if (k + i * stride >= kend) q[i].rw = q[i].w4A2 = 0.0;
+    }
+    net[i] = NetSums{};
+  }
+  if (act.n == 0) return;
+  // one loop without a way round its body: a site skipped inside the loop
+  // would have the compiler copy every sum where the two ways meet
+  uint32_t list = act.list;
+  int left = act.n;
+  do {
+    site_sums<NQ, MIXED, PSUM, TAB>(am, q, sc[list & 7u], 1 + (int)(list >> 3 & 1u), net);
+    list >>= 4;
+  } while (--left > 0);
+}
+
+// The rest of a point whose network sums are n: its derivatives, its share of
+// G[kGramAcc], U[8], W (accumulate_sums) and its phase-only coefficients
+// c[NPI] = (-1, dPsi/dchi1, dPsi/dchi2[, dPsi/dLambda1, dPsi/dLambda2]
+// [, dPsi/de0]).
+template <int NPI, bool ROT, bool PSUM>
+__host__ __device__ inline void finish_point(const EventC& ec, Point& q, const NetSums& n, double* G, double* U,
+                                             double& W, double* cph) {
+  reread(q.v, q.iv);
+  point_derivatives<PhaseOnly<NPI>::ecc>(ec, ROT, q);
+  accumulate_sums<ROT>(ec, q, n, G, U, W);
+  phase_only_coefficients<NPI, PSUM>(ec, q, cph);
+}
+
+// One grid point k of an event as a whole.
+template <int NPI, bool ROT, bool MIXED = false, bool PSUM = true, bool EXPL = false, bool TAB = true>
+__host__ __device__ inline void accumulate_point(const EventC& ec, const SiteC* sc, const ActiveSites& act,
+                                                 int32_t k, double* G, double* U, double& W,
+                                                 double* cph, const double (*vrec)[3] = nullptr) {
+  Point q[1];
+  NetSums n[1];
+  network_sums<1, NPI, ROT, MIXED, PSUM, EXPL, TAB>(ec, sc, act, k, 0, k + 1, false, vrec, q, n);
+  finish_point<NPI, ROT, PSUM>(ec, q[0], n[0], G, U, W, cph);
+}
 template <int NPI, bool ROT, bool MIXED = false, bool PSUM = true, bool EXPL = false, bool TAB = true>
 __host__ __device__ inline void accumulate_point(const EventC& ec, const SiteC* sc, int n_site,
                                                  int32_t k, double* G, double* U, double& W,
-                                                 double* cph, const double* vrec = nullptr) {
-  const AmpFactors am = amp_factors(ec);
-  Point q;
-  point_setup<PSUM, EXPL, PhaseOnly<NPI>::ecc>(ec, k, true, ROT, q, MIXED ? kPsdF32 : kPsdF64, vrec);
-  double UR[5], spp = 0.0, spx = 0.0, sxx = 0.0;
-#pragma unroll
-  for (int b = 0; b < 5; ++b) UR[b] = 0.0;
-  for (int s = 0; s < n_site; ++s) {
-    const SiteC& st = sc[s];
-    SiteTrigR sp;
-    site_trig_root<MIXED, PSUM, TAB>(st, q, sp);
-    const SitePhase ph = site_phase(q, sp.dH, sp.dT);
-    // at most two effective interferometers per site; the count is the same
-    // for every lane, so the second pass is skipped as a whole where unused.
-    // The patterns are trigonometric polynomials in H whose coefficients
-    // carry sqrt(weff), and the basis carries the root weight r, so Fp, Fx,
-    // the derivative vectors and Q below are r times their unweighted values
-    // and every product of two of them is weighted by w = weff r^2.
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (j >= st.n_eff) break;
-      const double(*c)[5] = st.jk[j];
-      const double Fp = trig_val_r(c[0], sp), Fx = trig_val_r(c[1], sp);
-      double Dr[8], Di[8];
-      derivative_vector(am, q, ph, Fp, Fx, trig_dH_r(c[0], sp), trig_dH_r(c[1], sp), trig_val_r(c[2], sp),
-                        trig_val_r(c[3], sp), Dr, Di);
-      const double Qr = am.cplus * Fp, Qi = am.ccross * Fx;
-      int g = 0;
-#pragma unroll
-      for (int a = 0; a < 5; ++a) {
-        const int r = kGramRows[a];
-        const double dr = Dr[r], di = Di[r];
-#pragma unroll
-        for (int b = a; b < 5; ++b) {
-          const int c = kGramRows[b];
-          G[g] = fma(dr, Dr[c], fma(di, Di[c], G[g]));
-          ++g;
-        }
-        G[15 + 4 * a + 0] = fma(Fp, dr, G[15 + 4 * a + 0]);
-        G[15 + 4 * a + 1] = fma(Fp, di, G[15 + 4 * a + 1]);
-        G[15 + 4 * a + 2] = fma(Fx, dr, G[15 + 4 * a + 2]);
-        G[15 + 4 * a + 3] = fma(Fx, di, G[15 + 4 * a + 3]);
-        // w Re(i Q D_r^*) = (r Qr)(r Di_r) - (r Qi)(r Dr_r)
-        UR[a] = fma(Qr, di, fma(-Qi, dr, UR[a]));
-      }
-      spp = fma(Fp, Fp, spp);
-      spx = fma(Fp, Fx, spx);
-      sxx = fma(Fx, Fx, sxx);
-    }
-  }
-  G[35] += spp;
-  G[36] += spx;
-  G[37] += sxx;
-#pragma unroll
-  for (int a = 0; a < 5; ++a) U[kGramRows[a]] = UR[a];
-  U[2] = 0.0;
-  U[5] = ec.u_iota * spx;
-  U[6] = ec.u_psi * (spp + sxx);
-  W = fma(ec.cp2, spp, ec.cx2 * sxx);
-  phase_only_coefficients<NPI, PSUM>(ec, q, cph);
+                                                 double* cph) {
+  accumulate_point<NPI, ROT, MIXED, PSUM, EXPL, TAB>(ec, sc, active_sites(sc, n_site), k, G, U, W, cph);
 }
 
 // The 8x8 upper-triangle block of (Mc, eta, dL, theta, phi, iota, psi, tc)
@@ -1333,24 +1530,73 @@ __host__ __device__ inline void gram_finish(const EventC& ec, const double* G, d
   const AmpFactors am = amp_factors(ec);
   auto at = [](int r, int c) { return r <= c ? 8 * r - (r * (r - 1)) / 2 + (c - r)
                                              : 8 * c - (c * (c - 1)) / 2 + (r - c); };
-  int g = 0;
-  for (int a = 0; a < 5; ++a)
-    for (int b = a; b < 5; ++b) F[at(kGramRows[a], kGramRows[b])] = G[g++];
-  for (int a = 0; a < 5; ++a) {
-    const int r = kGramRows[a];
-    const double tpr = G[15 + 4 * a], tpi = G[16 + 4 * a], txr = G[17 + 4 * a], txi = G[18 + 4 * a];
-    F[at(r, 2)] = -am.idL * fma(am.cplus, tpr, am.ccross * txi);
-    F[at(r, 5)] = fma(am.dcp, tpr, am.dcx * txi);
-    F[at(r, 6)] = 2.0 * fma(am.cplus, txr, -am.ccross * tpi);
-  }
-  const double spp = G[35], spx = G[36], sxx = G[37];
-  const double ci = am.ccross, si2 = (1.0 - ci) * (1.0 + ci);   // c+^2 - cx^2 = sin^4(iota)/4
-  F[at(2, 2)] = am.idL * am.idL * fma(am.cplus * am.cplus, spp, ci * ci * sxx);
-  F[at(2, 5)] = -am.idL * fma(am.cplus * am.dcp, spp, ci * am.dcx * sxx);
-  F[at(2, 6)] = -am.idL * 0.5 * si2 * si2 * spx;
+  const double cp = am.cplus, cx = am.ccross, a = am.dlnA;
+  const double spp = G[kGSpp], spx = G[kGSpx], sxx = G[kGSxx];
+  const double si2 = (1.0 - cx) * (1.0 + cx);                     // c+^2 - cx^2 = sin^4(iota)/4
+  const double W = fma(cp * cp, spp, cx * cx * sxx);
+  const double qi = fma(cp * am.dcp, spp, cx * am.dcx * sxx);     // Re(Q D_iota^*)
+  const double qp = 0.5 * si2 * si2 * spx;                        // Re(Q D_psi^*)
+  // Re(X Z^*) and Re(X Y^*) for X = Q, D_iota, D_psi
+  const double qz = fma(cp, G[kGPzr], cx * G[kGXzi]), qy = fma(cp, G[kGPyr], cx * G[kGXyi]);
+  const double iz = fma(am.dcp, G[kGPzr], am.dcx * G[kGXzi]), iy = fma(am.dcp, G[kGPyr], am.dcx * G[kGXyi]);
+  const double pz = 2.0 * fma(cp, G[kGXzr], -cx * G[kGPzi]), py = 2.0 * fma(cp, G[kGXyr], -cx * G[kGPyi]);
+  // Mc and eta
+  F[at(0, 0)] = fma(a, fma(a, W, 2.0 * G[kGMd]), G[kGMM]);
+  F[at(0, 1)] = fma(a, G[kGEd], G[kGME]);
+  F[at(1, 1)] = G[kGEE];
+  F[at(0, 3)] = fma(a, qy, G[kGMY]);
+  F[at(1, 3)] = G[kGEY];
+  const double mz = fma(a, qz, G[kGMZ]);
+  F[at(0, 4)] = -mz;
+  F[at(1, 4)] = -G[kGEZ];
+  F[at(0, 7)] = fma(kOmegaE, mz, G[kGMt]);
+  F[at(1, 7)] = fma(kOmegaE, G[kGEZ], G[kGEt]);
+  // theta, phi, tc
+  F[at(3, 3)] = G[kGYY];
+  F[at(3, 4)] = -G[kGZY];
+  F[at(3, 7)] = fma(kOmegaE, G[kGZY], G[kGtY]);
+  F[at(4, 4)] = G[kGZZ];
+  F[at(4, 7)] = -fma(kOmegaE, G[kGZZ], G[kGtZ]);
+  F[at(7, 7)] = fma(kOmegaE, fma(kOmegaE, G[kGZZ], 2.0 * G[kGtZ]), G[kGtt]);
+  // dL
+  F[at(0, 2)] = -am.idL * fma(a, W, G[kGMd]);
+  F[at(1, 2)] = -am.idL * G[kGEd];
+  F[at(2, 2)] = am.idL * am.idL * W;
+  F[at(2, 3)] = -am.idL * qy;
+  F[at(2, 4)] = am.idL * qz;
+  F[at(2, 5)] = -am.idL * qi;
+  F[at(2, 6)] = -am.idL * qp;
+  F[at(2, 7)] = -am.idL * (kOmegaE * qz);
+  // iota
+  F[at(0, 5)] = fma(a, qi, G[kGMi]);
+  F[at(1, 5)] = G[kGEi];
+  F[at(3, 5)] = iy;
+  F[at(4, 5)] = -iz;
   F[at(5, 5)] = fma(am.dcp * am.dcp, spp, am.dcx * am.dcx * sxx);
-  F[at(5, 6)] = 2.0 * fma(am.cplus, am.dcp, -ci * am.dcx) * spx;
-  F[at(6, 6)] = 4.0 * fma(am.cplus * am.cplus, sxx, ci * ci * spp);
+  F[at(5, 6)] = 2.0 * fma(cp, am.dcp, -cx * am.dcx) * spx;
+  F[at(5, 7)] = fma(kOmegaE, iz, G[kGTI]);
+  // psi
+  F[at(0, 6)] = fma(a, qp, G[kGMp]);
+  F[at(1, 6)] = G[kGEp];
+  F[at(3, 6)] = py;
+  F[at(4, 6)] = -pz;
+  F[at(6, 6)] = 4.0 * fma(cp * cp, sxx, cx * cx * spp);
+  F[at(6, 7)] = fma(kOmegaE, pz, G[kGTP]);
+}
+
+// The Phic column from the accumulator: -sum U_b of the rows Mc, eta, theta,
+// phi, iota, psi, tc (the dL row is zero), then sum W (= Gamma_{Phic,Phic}).
+__host__ __device__ inline void gram_phic(const EventC& ec, const double* G, double xc[8]) {
+  const AmpFactors am = amp_factors(ec);
+  const double iqz = fma(am.cplus, G[kGPzi], -am.ccross * G[kGXzr]);
+  xc[0] = -G[kGMu];
+  xc[1] = -G[kGEu];
+  xc[2] = fma(am.ccross, G[kGXyr], -am.cplus * G[kGPyi]);
+  xc[3] = iqz;
+  xc[4] = -(am.cplus * am.dcx - am.ccross * am.dcp) * G[kGSpx];
+  xc[5] = 2.0 * am.cplus * am.ccross * (G[kGSpp] + G[kGSxx]);
+  xc[6] = -fma(kOmegaE, iqz, G[kGTW]);
+  xc[7] = fma(am.cplus * am.cplus, G[kGSpp], am.ccross * am.ccross * G[kGSxx]);
 }
 
 // Plain accumulation of the phase-only blocks of one point into

@@ -23,15 +23,15 @@ namespace {
 // the delay, and for each computed arm the projected amplitude's real and
 // imaginary parts (c+ F+ and cx Fx, inclination factors folded in) as
 // trigonometric polynomials in the hour angle H: coefficients of
-// (1, cos H, sin H, cos 2H, sin 2H).
+// (1, cos H, sin H, cos 2H, sin H cos H).
 struct WaveSite {
   double cdl, sdl, k1, k0;
   double m[2][2][5];
   int32_t n_arm, pad;
 };
 
-__device__ inline double trig5(const double c[5], double cH, double sH, double c2H, double s2H) {
-  return fma(c[4], s2H, fma(c[3], c2H, fma(c[2], sH, c[1] * cH))) + c[0];
+__device__ inline double trig5(const double c[5], double cH, double sH, double c2H, double sc) {
+  return fma(c[4], sc, fma(c[3], c2H, fma(c[2], sH, c[1] * cH))) + c[0];
 }
 
 template <bool ROT, bool TIDAL, bool MIXED, bool EXPL>
@@ -128,16 +128,16 @@ __global__ __launch_bounds__(kWBlock) void waveform_kernel(WaveformArgs a) {
       const WaveSite& w = ws[s];
       const double cH = cth * w.cdl - sth * w.sdl;
       const double sH = sth * w.cdl + cth * w.sdl;
-      const double c2H = fma(cH, cH, -sH * sH), s2H = 2.0 * (sH * cH);
+      const double c2H = fma(cH, cH, -sH * sH), sc = sH * cH;
       double sn, cs;
       sincos_cycles<MIXED>(frac_center(fma(f, fma(w.k1, cH, w.k0), cyc)), &sn, &cs);
       const double ca = amp * cs, sa = amp * sn;
-      const double qr0 = trig5(w.m[0][0], cH, sH, c2H, s2H), qi0 = trig5(w.m[0][1], cH, sH, c2H, s2H);
+      const double qr0 = trig5(w.m[0][0], cH, sH, c2H, sc), qi0 = trig5(w.m[0][1], cH, sH, c2H, sc);
       const double2 h0 = make_double2(qr0 * ca - qi0 * sa, qr0 * sa + qi0 * ca);
       *o = h0;
       o += row;
       if (w.n_arm == 3) {                 // closed triangle: third arm = -(first + second)
-        const double qr1 = trig5(w.m[1][0], cH, sH, c2H, s2H), qi1 = trig5(w.m[1][1], cH, sH, c2H, s2H);
+        const double qr1 = trig5(w.m[1][0], cH, sH, c2H, sc), qi1 = trig5(w.m[1][1], cH, sH, c2H, sc);
         const double2 h1 = make_double2(qr1 * ca - qi1 * sa, qr1 * sa + qi1 * ca);
         o[0] = h1;
         o[row] = make_double2(-(h0.x + h1.x), -(h0.y + h1.y));
