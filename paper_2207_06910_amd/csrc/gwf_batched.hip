@@ -31,32 +31,39 @@ __global__ void fill_i32_kernel(int32_t* p, int32_t v, int64_t n) {
   if (i < n) p[i] = v;
 }
 
-// Lanes [0, n) take one event each (EventC and its status), lanes
-// [n, n + n n_site) one (event, site) pair each (SiteC, with pi M formed from
-// the parameters exactly as the event's lane forms it); both write straight
-// into the workspace.  A site of an event whose set-up fails is written
-// anyway and never read.
+// Lane e of the grid's row y: y = 0, 1, 2 form one part each of event e's
+// constants (EventC; the first part its status), y = 3 + s its constants of
+// site s (SiteC, with pi M formed from the parameters exactly as the event's
+// grid part forms it); all write straight into the workspace.  A site of an
+// event whose set-up fails is written anyway and never read.  The rows are
+// independent workgroups, so a small catalogue's set-up takes as long as the
+// longest of the parts, not their sum.
+constexpr int kSetupRows = 3;
+
 __global__ __launch_bounds__(64) void setup_kernel(SetupArgs a) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int n_site = a.net.n_site;
-  if (t >= a.n * (1 + n_site)) return;
-  const int64_t e = t < a.n ? t : (t - a.n) / n_site;
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= a.n) return;
+  const int row = blockIdx.y;
   const bool tidal = (a.flags & kFlagTidal) != 0;
   double p[kNparIn];
   for (int r = 0; r < 13; ++r) p[r] = (r < 11 || tidal) ? a.par[r * a.ld + e] : 0.0;
   p[13] = (a.flags & kFlagEcc) && a.ecc ? a.ecc[e] : 0.0;
   p[14] = (a.flags & kFlagEcc) && a.fref ? a.fref[e] : 0.0;
-  if (t < a.n) {
+  if (row == 0) {
     EventC& ec = a.evc[e];
-    event_setup(p, a.fmin[e], a.fmax ? a.fmax[e] : 0.0, a.npts[e], a.flags, ec);
+    event_grid_setup(p, a.fmin[e], a.fmax ? a.fmax[e] : 0.0, a.npts[e], a.flags, ec);
     if (!ec.status && (a.npts[e] != a.npts_plan[e] || a.npts[e] > a.npts_max))
       ec.status = kEvInvalid;   // grid changed since the items were built, or longer than they allow
     if (a.status) a.status[e] = ec.status;
-    return;
+  } else if (row == 1) {
+    event_phase_setup(p, a.flags, a.evc[e]);
+  } else if (row == 2) {
+    event_angle_setup(p, a.fmin[e], a.flags, a.evc[e]);
+  } else {
+    const int s = row - kSetupRows;
+    site_setup(p, a.net.site[s], kPi * total_mass_s(p), a.sic[e * a.net.n_site + s],
+               site_arms_on(a.active, a.ld, e, a.net, s));
   }
-  const int s = (int)(t - a.n - e * n_site);
-  site_setup(p, a.net.site[s], kPi * total_mass_s(p), a.sic[e * n_site + s],
-             site_arms_on(a.active, a.ld, e, a.net, s));
 }
 
 template <int NPI, bool ROT, bool MIXED, bool TAB>
@@ -189,8 +196,8 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s) {
 }
 
 hipError_t launch_setup(const SetupArgs& a, hipStream_t s) {
-  const int64_t lanes = a.n * (1 + (int64_t)a.net.n_site);
-  hipLaunchKernelGGL(setup_kernel, dim3((unsigned)((lanes + 63) / 64)), dim3(64), 0, s, a);
+  hipLaunchKernelGGL(setup_kernel, dim3((unsigned)((a.n + 63) / 64), (unsigned)(kSetupRows + a.net.n_site)), dim3(64),
+                     0, s, a);
   return hipGetLastError();
 }
 

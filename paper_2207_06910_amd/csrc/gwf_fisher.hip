@@ -47,10 +47,10 @@ __global__ __launch_bounds__(kBlock, 2) void fisher_kernel(FisherArgs a) {
   const int n_site = a.net.n_site;
   double p[kNparIn];
   load_par(a.par, a.ld, e, PO::tidal, PO::ecc ? a.ecc : nullptr, a.fref, p);
-  // the event's constants on lane 0 and the sites' on the second wavefront,
+  // the three parts of the event's constants and the sites' on a wavefront each,
   // at the same time (a site needs only the parameters and pi M)
   if (tid == 0) {
-    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, flags, ec);
+    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, flags, ec, kSetupGrid);
     int32_t sk = ec.status;
     if (!sk && a.snr_pre && !(a.snr_pre[e] > a.snr_th)) sk = kEvSkipped;
     skip = sk;
@@ -59,6 +59,10 @@ __global__ __launch_bounds__(kBlock, 2) void fisher_kernel(FisherArgs a) {
     const int s = tid - 64;
     site_setup(p, a.net.site[s], kPi * total_mass_s(p), sc[s],
                select_ifo(site_arms_on(a.active, a.ld, e, a.net, s), a.net, s, a.ifo_sel));
+  } else if (tid == 128) {
+    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, flags, ec, kSetupPhase);
+  } else if (tid == 192) {
+    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, flags, ec, kSetupAngle);
   }
   __syncthreads();
   if (skip) {
@@ -102,9 +106,13 @@ __global__ __launch_bounds__(kBlock) void snr_kernel(SnrArgs a) {
   const int n_site = a.net.n_site;
   double p[kNparIn];
   load_par(a.par, a.ld, e, a.tidal, nullptr, nullptr, p);
-  // the event's constants on lane 0 and the sites' on the second wavefront, at once
+  // the event's grid and angle constants and the sites', on a wavefront each at
+  // once (no phase series here)
+  const uint32_t ef = flags | (a.tidal ? kFlagTidal : 0u);
   if (tid == 0)
-    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, flags | (a.tidal ? kFlagTidal : 0u), ec);
+    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, ef, ec, kSetupGrid);
+  else if (tid == 192)
+    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, ef, ec, kSetupAngle);
   else if (tid >= 64 && tid < 64 + n_site)
     site_setup(p, a.net.site[tid - 64], kPi * total_mass_s(p), sc[tid - 64]);
   __syncthreads();

@@ -336,19 +336,21 @@ __host__ __device__ inline int32_t check_event(const double* p, bool tidal, doub
 // grid's v = (pi M f)^(1/3) and the PSD's x = f/f0 of every site).
 __host__ __device__ inline double total_mass_s(const double* p) { return p[0] * pow(p[1], -0.6) * kTsun; }
 
-__host__ __device__ inline void event_setup(const double* p, double fmin, double fmax, int32_t n,
-                                            uint32_t flags, EventC& ec) {
-  const bool tidal = (flags & kFlagTidal) != 0;
-  const bool rot = (flags & kFlagRot) != 0;
-  const bool ecc = (flags & kFlagEcc) != 0;
-  const double Mc = p[0], eta = p[1], dL = p[2];
+// The constants fall into three parts that share nothing but p, so that the
+// kernels can form them side by side, one wavefront or workgroup each (the
+// chain of one lane doing all of them is 7 us).  An event whose status is set
+// gets the other parts all the same; nothing reads them.
+enum { kSetupGrid = 1, kSetupPhase = 2, kSetupAngle = 4, kSetupAll = 7 };
+
+// The grid, the weights, the amplitude and the status.
+__host__ __device__ inline void event_grid_setup(const double* p, double fmin, double fmax, int32_t n,
+                                                 uint32_t flags, EventC& ec) {
+  const double Mc = p[0], dL = p[2];
   const double Ms = total_mass_s(p);
   if (!(fmax > 0.0)) fmax = cut_frequency_of(Ms);
   ec.n = n;
   ec.fx = nullptr;
-  ec.ecc = 0;
-  ec.ecc_lnvr = ec.ecc_psi = ec.ecc_mc = ec.ecc_e0 = ec.ecc_cyc = 0.0;
-  ec.status = check_event(p, tidal, fmin, fmax, n, ecc);
+  ec.status = check_event(p, (flags & kFlagTidal) != 0, fmin, fmax, n, (flags & kFlagEcc) != 0);
   if (ec.status) return;
   // grid
   const double D = log(fmax / fmin) / (double)(n - 1);
@@ -370,6 +372,13 @@ __host__ __device__ inline void event_setup(const double* p, double fmin, double
   ec.pad_rw = 0.0;
   ec.dlnA_dMc = 5.0 / (6.0 * Mc);
   ec.inv_dL = 1.0 / dL;
+  ec.lnA = 0.5 * log(0.25 * ec.KA4);
+}
+
+// The orientation, the eccentric terms and the sidereal-angle series.
+__host__ __device__ inline void event_angle_setup(const double* p, double fmin, uint32_t flags, EventC& ec) {
+  const bool rot = (flags & kFlagRot) != 0, ecc = (flags & kFlagEcc) != 0;
+  const double Mc = p[0], eta = p[1], Ms = total_mass_s(p);
   // 2 pi tcoal reduced to [0, 2 pi)
   const double tfrac = p[7] - floor(p[7]);
   ec.thc = kTwoPi * tfrac;
@@ -389,17 +398,43 @@ __host__ __device__ inline void event_setup(const double* p, double fmin, double
   // e0 given where the GW frequency is f_ref (the grid's first frequency
   // unless given, sec. 2.1).  At fixed f and f_ref it is proportional to
   // eta^-1 v^-5, i.e. to Mc^{-5/3} alone.
+  ec.ecc = 0;
+  ec.ecc_lnvr = ec.ecc_psi = ec.ecc_mc = ec.ecc_e0 = ec.ecc_cyc = 0.0;
   if (ecc) {
     const double e0 = p[13], fref = p[14] > 0.0 ? p[14] : fmin;
     const double K = (3.0 / (128.0 * eta)) * (-2355.0 / 1462.0);
     ec.ecc = 1;
-    ec.ecc_lnvr = (ec.lnpiM + log(fref)) / 3.0;
+    ec.ecc_lnvr = (log(kPi * Ms) + log(fref)) / 3.0;
     ec.ecc_psi = K * e0 * e0;
     ec.ecc_mc = -5.0 / (3.0 * Mc) * ec.ecc_psi;
     ec.ecc_e0 = 2.0 * K * e0;
     ec.ecc_cyc = ec.ecc_psi / kTwoPi;
   }
+  ec.cyc0 = -(p[8] + 0.25 * kPi) / kTwoPi;
 
+  // ---- rotation: sidereal-angle offset -Omega tau* and its Mc, eta derivatives
+  double t[8], te[8], l6;
+  tau_coefficients(eta, t, te, l6);
+  const double Kt = 5.0 * Ms / (256.0 * eta);
+  const double om = rot ? kOmegaE : 0.0;
+  double lk[8] = {0, 0, 0, 0, 0, 0, l6, 0};
+  for (int k = 0; k < 8; ++k) {
+    ec.ts[kTsTheta].c[k] = -om * Kt * t[k];
+    // d tau*/d Mc = (Kt/Mc) sum [(t_k + l_k L)(1 + (k-8)/3) + l_k/3] v^(k-8)
+    ec.ts[kTsMc].c[k] = -om * (Kt / Mc) * ((1.0 + (k - 8) / 3.0) * t[k] + lk[k] / 3.0);
+    // d tau*/d eta = Kt sum [t_k' - (k t_k + l_k)/(5 eta)] v^(k-8) + log part
+    ec.ts[kTsEta].c[k] = -om * Kt * (te[k] - (k * t[k] + lk[k]) / (5.0 * eta));
+  }
+  ec.ts[kTsEta].c[0] = 0.0;   // leading tau* does not depend on eta at fixed Mc
+  ec.ts[kTsTheta].l6 = -om * Kt * l6;
+  ec.ts[kTsMc].l6 = -om * (Kt / Mc) * (1.0 + (6 - 8) / 3.0) * l6;
+  ec.ts[kTsEta].l6 = -om * Kt * (-6.0 * l6 / (5.0 * eta));
+}
+
+// The phase series.
+__host__ __device__ inline void event_phase_setup(const double* p, uint32_t flags, EventC& ec) {
+  const bool tidal = (flags & kFlagTidal) != 0;
+  const double Mc = p[0], eta = p[1];
   // ---- phase-derivative series
   PNCoef c;
   pn_coefficients(eta, p[9], p[10], tidal ? p[11] : 0.0, tidal ? p[12] : 0.0, tidal, c);
@@ -456,26 +491,13 @@ __host__ __device__ inline void event_setup(const double* p, double fmin, double
     s.t10 = K * c.a10;
     s.t12 = K * c.a12;
   }
-  ec.lnA = 0.5 * log(0.25 * ec.KA4);
-  ec.cyc0 = -(p[8] + 0.25 * kPi) / kTwoPi;
+}
 
-  // ---- rotation: sidereal-angle offset -Omega tau* and its Mc, eta derivatives
-  double t[8], te[8], l6;
-  tau_coefficients(eta, t, te, l6);
-  const double Kt = 5.0 * Ms / (256.0 * eta);
-  const double om = rot ? kOmegaE : 0.0;
-  double lk[8] = {0, 0, 0, 0, 0, 0, l6, 0};
-  for (int k = 0; k < 8; ++k) {
-    ec.ts[kTsTheta].c[k] = -om * Kt * t[k];
-    // d tau*/d Mc = (Kt/Mc) sum [(t_k + l_k L)(1 + (k-8)/3) + l_k/3] v^(k-8)
-    ec.ts[kTsMc].c[k] = -om * (Kt / Mc) * ((1.0 + (k - 8) / 3.0) * t[k] + lk[k] / 3.0);
-    // d tau*/d eta = Kt sum [t_k' - (k t_k + l_k)/(5 eta)] v^(k-8) + log part
-    ec.ts[kTsEta].c[k] = -om * Kt * (te[k] - (k * t[k] + lk[k]) / (5.0 * eta));
-  }
-  ec.ts[kTsEta].c[0] = 0.0;   // leading tau* does not depend on eta at fixed Mc
-  ec.ts[kTsTheta].l6 = -om * Kt * l6;
-  ec.ts[kTsMc].l6 = -om * (Kt / Mc) * (1.0 + (6 - 8) / 3.0) * l6;
-  ec.ts[kTsEta].l6 = -om * Kt * (-6.0 * l6 / (5.0 * eta));
+__host__ __device__ inline void event_setup(const double* p, double fmin, double fmax, int32_t n,
+                                            uint32_t flags, EventC& ec, int parts = kSetupAll) {
+  if (parts & kSetupGrid) event_grid_setup(p, fmin, fmax, n, flags, ec);
+  if (parts & kSetupAngle) event_angle_setup(p, fmin, flags, ec);
+  if (parts & kSetupPhase) event_phase_setup(p, flags, ec);
 }
 
 // event_setup on event e's grid: the log descriptors, or an explicit grid
@@ -484,15 +506,15 @@ __host__ __device__ inline void event_setup(const double* p, double fmin, double
 // event is flagged invalid otherwise, before any other frequency is read).
 __host__ __device__ inline void event_setup_grid(const double* p, const double* fmin, const double* fmax,
                                                  const int32_t* npts, const int64_t* goff, const double* gf,
-                                                 int64_t e, uint32_t flags, EventC& ec) {
+                                                 int64_t e, uint32_t flags, EventC& ec, int parts = kSetupAll) {
   const int32_t n = npts[e];
   if (gf) {
     const double* fx = gf + goff[e];
     const bool ok = n >= 2 && fx[0] > 0.0 && fx[n - 1] > fx[0];
-    event_setup(p, ok ? fx[0] : 0.0, ok ? fx[n - 1] : 0.0, n, flags, ec);
-    ec.fx = fx;
+    event_setup(p, ok ? fx[0] : 0.0, ok ? fx[n - 1] : 0.0, n, flags, ec, parts);
+    if (parts & kSetupGrid) ec.fx = fx;
   } else {
-    event_setup(p, fmin[e], fmax ? fmax[e] : 0.0, n, flags, ec);
+    event_setup(p, fmin[e], fmax ? fmax[e] : 0.0, n, flags, ec, parts);
   }
 }
 
