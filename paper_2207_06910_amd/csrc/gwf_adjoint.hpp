@@ -319,7 +319,7 @@ struct AdjPoint {
 template <int NPI, bool ROT>
 __host__ __device__ inline void adjoint_point_setup(const EventC& ec, const AdjEventC& ae, int32_t k,
                                                     AdjPoint& ap, const double* vrec = nullptr) {
-  point_setup<true, false, PhaseOnly<NPI>::ecc>(ec, k, true, ROT, ap.q, kPsdF64, vrec);
+  point_setup<false, PhaseOnly<NPI>::ecc>(ec, k, true, ROT, ap.q, kPsdF64, vrec);
   const Point& q = ap.q;
   double c[NPI];
   phase_only_coefficients<NPI>(ec, q, c);
@@ -389,7 +389,7 @@ __host__ __device__ inline void adjoint_site(const AdjEventC& ae, const SiteC& s
                                              const AdjPoint& ap, double* acc) {
   const Point& q = ap.q;
   SiteTrig sp;
-  site_trig<false, true, TAB>(sc, q, sp);
+  site_trig<TAB>(sc, q, sp);
   const double tf = q.tf;
   const double a = tf * sp.dH, b = tf * sp.dT;
   const double cp = ae.cpl, cx = ae.ccr;

@@ -96,9 +96,7 @@ __global__ __launch_bounds__(kBlock, 2) void items_kernel(ItemsArgs a) {
     if (tid < NACC) out[tid] = 0.0;
   } else {
     double t = 0.0;
-    // both forms: PN series as sums of products over shared powers and the
-    // PSD power law once per point (in FP32 for the mixed form)
-    fisher_sums<NPI, 2, ROT, MIXED, true, false, TAB>(ecg, scg, n_site, k0, k1, L, &t);
+    fisher_sums<NPI, 2, ROT, MIXED, false, TAB>(ecg, scg, n_site, k0, k1, L, &t);
     if (tid < NACC) out[tid] = t;
   }
 }

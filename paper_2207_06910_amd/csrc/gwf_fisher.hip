@@ -21,6 +21,7 @@
 // and only the 8x8 block of (Mc, eta, dL, theta, phi, iota, psi, tc) needs a
 // per-interferometer rank-2 update.
 #include "gwf_fisher_body.hpp"
+#include "gwf_snr_body.hpp"
 
 namespace gwf {
 
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(kBlock, 2) void fisher_kernel(FisherArgs a) {
   }
 
   double t = 0.0;
-  fisher_sums<NPI, 1, ROT, false, true, EXPL, TAB>(ec, sc, n_site, 0, ec.n, L, &t);
+  fisher_sums<NPI, 1, ROT, false, EXPL, TAB>(ec, sc, n_site, 0, ec.n, L, &t);
   if (tid < NACC) {
     int r, c;
     slot_position(tid, NPI, r, c);
@@ -100,10 +101,10 @@ __global__ __launch_bounds__(kBlock) void snr_kernel(SnrArgs a) {
   constexpr uint32_t flags = ROT ? kFlagRot : 0u;
   __shared__ EventC ec;
   __shared__ SiteC sc[kMaxSites];
-  __shared__ double red[kWaves][kMaxIfo + 1];
+  __shared__ double red[kWaves][kMaxIfo], ifo[kMaxIfo];
   const int64_t e = a.base + blockIdx.x;
   const int tid = threadIdx.x;
-  const int n_site = a.net.n_site;
+  const int n_site = a.net.n_site, n_ifo = a.net.n_ifo;
   double p[kNparIn];
   load_par(a.par, a.ld, e, a.tidal, nullptr, nullptr, p);
   // the event's grid and angle constants and the sites', on a wavefront each at
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(kBlock) void snr_kernel(SnrArgs a) {
   else if (tid == 192)
     event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, ef, ec, kSetupAngle);
   else if (tid >= 64 && tid < 64 + n_site)
-    site_setup(p, a.net.site[tid - 64], kPi * total_mass_s(p), sc[tid - 64]);
+    site_setup(p, a.net.site[tid - 64], kPi * total_mass_s(p), sc[tid - 64], kArmsPlain);
   __syncthreads();
   if (ec.status) {
     if (tid == 0) {
@@ -122,68 +123,26 @@ __global__ __launch_bounds__(kBlock) void snr_kernel(SnrArgs a) {
       if (a.status) a.status[e] = ec.status;
     }
     if (a.snr_ifo)
-      for (int i = tid; i < a.net.n_ifo; i += kBlock) a.snr_ifo[(int64_t)i * a.n + e] = 0.0;
+      for (int i = tid; i < n_ifo; i += kBlock) a.snr_ifo[(int64_t)i * a.n + e] = 0.0;
     return;
   }
-  // slot 3 s + k holds arm k of site s
-  double acc[3 * kMaxSites];
+  double acc[kSnrSlots];
 #pragma unroll
-  for (int i = 0; i < 3 * kMaxSites; ++i) acc[i] = 0.0;
-  const double cplus = ec.cplus, ccross = ec.ccross;
-  for (int k = tid; k < ec.n; k += kBlock) {
-    __asm__ volatile("" ::: "memory");
-    Point q;
-    point_setup<false, EXPL>(ec, k, false, ROT, q);
-#pragma unroll
-    for (int s = 0; s < kMaxSites; ++s) {
-      if (s < n_site) {
-        const SiteC& st = sc[s];
-        SitePoint sp;
-        site_point<false, false>(st, q, false, sp);
-        if (st.n_arm == 3) {
-          const double p0 = cplus * dot4(st.arm_alpha[0], sp.P), x0 = ccross * dot4(st.arm_beta[0], sp.P);
-          const double p1 = cplus * dot4(st.arm_alpha[1], sp.P), x1 = ccross * dot4(st.arm_beta[1], sp.P);
-          const double p2 = -(p0 + p1), x2 = -(x0 + x1);
-          acc[3 * s] = fma(sp.om, fma(p0, p0, x0 * x0), acc[3 * s]);
-          acc[3 * s + 1] = fma(sp.om, fma(p1, p1, x1 * x1), acc[3 * s + 1]);
-          acc[3 * s + 2] = fma(sp.om, fma(p2, p2, x2 * x2), acc[3 * s + 2]);
-        } else {
-          const double p0 = cplus * dot4(st.arm_alpha[0], sp.P), x0 = ccross * dot4(st.arm_beta[0], sp.P);
-          acc[3 * s] = fma(sp.om, fma(p0, p0, x0 * x0), acc[3 * s]);
-        }
-      }
-    }
-  }
-  const int wave = tid >> 6, lane = tid & 63;
-  int ifo = 0;
-#pragma unroll
-  for (int s = 0; s < kMaxSites; ++s) {
-    if (s < n_site) {
-      const int na = sc[s].n_arm;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        if (k < na) {
-          const double t = wave_sum(acc[3 * s + k]);
-          if (lane == 0) red[wave][ifo] = t;
-          ++ifo;
-        }
-      }
-    }
+  for (int i = 0; i < kSnrSlots; ++i) acc[i] = 0.0;
+  snr_sums<ROT, EXPL, true>(ec, sc, n_site, 0, ec.n, acc);
+  double t = 0.0;
+  snr_reduce(acc, n_site, n_ifo, site_shapes(a.net), red, &t);
+  if (tid < n_ifo) {
+    if (a.active && !a.active[(int64_t)tid * a.ld + e]) t = 0.0;   // off for this event
+    if (a.snr_ifo) a.snr_ifo[(int64_t)tid * a.n + e] = sqrt(t);
+    ifo[tid] = t;
   }
   __syncthreads();
   if (tid == 0) {
     double tot = 0.0;
-    bool bad = false;
-    for (int i = 0; i < a.net.n_ifo; ++i) {
-      double t = red[0][i];
-      for (int w = 1; w < kWaves; ++w) t += red[w][i];
-      if (a.active && !a.active[(int64_t)i * a.ld + e]) t = 0.0;   // off for this event
-      tot += t;
-      if (a.snr_ifo) a.snr_ifo[(int64_t)i * a.n + e] = sqrt(t);
-    }
-    if (!isfinite(tot)) bad = true;
+    for (int i = 0; i < n_ifo; ++i) tot += ifo[i];
     a.snr[e] = sqrt(tot);
-    if (a.status) a.status[e] = bad ? kEvNonFinite : 0;
+    if (a.status) a.status[e] = isfinite(tot) ? 0 : kEvNonFinite;
   }
 }
 

@@ -152,7 +152,7 @@ __device__ inline void load_par(const double* __restrict__ par, int64_t ld, int6
 // at one point, in 168 registers, spill inside the loop (2.73 ms).  With the
 // constants in LDS, read into vector registers, two points spill, so that
 // kernel takes one.
-template <int NPI_, int NQ, bool ROT, bool MIXED = false, bool PSUM = true, bool EXPL = false, bool TAB = true>
+template <int NPI_, int NQ, bool ROT, bool MIXED = false, bool EXPL = false, bool TAB = true>
 __device__ inline void fisher_sums(const EventC& ec, const SiteC* sc, int n_site, int k0, int k1,
                                    FisherLds<NPI_, NQ>& L, double* tot) {
   using Dm = FisherDims<NPI_>;
@@ -237,28 +237,15 @@ __device__ inline void fisher_sums(const EventC& ec, const SiteC* sc, int n_site
     const int k = kb + tid;
     const bool inner = kb > 0 && kb + NQ * kBlock < k1;
     double vv[NQ][3];
-    if (!EXPL) {
-#pragma unroll
-      for (int i = 0; i < NQ; ++i) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) vv[i][c] = gw.val[c];
-        gw.step();
-      }
-      if (!inner) {
-        keep_branch();
-#pragma unroll
-        for (int i = 0; i < NQ; ++i)
-          if (k + i * kBlock >= k1) grid_values(ec, k1 - 1, vv[i]);
-      }
-    }
+    if (!EXPL) walk_points<NQ>(ec, gw, k, kBlock, k1, inner, vv);
     Point q[NQ];
     NetSums net[NQ];
-    network_sums<NQ, NPI, ROT, MIXED, PSUM, EXPL, TAB>(ec, sc, act, k, kBlock, k1, inner, EXPL ? nullptr : vv, q,
+    network_sums<NQ, NPI, ROT, MIXED, EXPL, TAB>(ec, sc, act, k, kBlock, k1, inner, EXPL ? nullptr : vv, q,
                                                        net);
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       double U[8], W, cph[NPI];
-      finish_point<NPI, ROT, PSUM>(ec, q[i], net[i], G, U, W, cph);
+      finish_point<NPI, ROT>(ec, q[i], net[i], G, U, W, cph);
       stage(NS == 1 ? 0 : i, U, W, cph);
       if (NS == 1 || i == NQ - 1) contract();
     }

@@ -129,7 +129,7 @@ struct SiteC {
   double ct, slct, clst, sl, st;   // cos th, sin lat cos th, cos lat sin th, sin lat, sin th
   double cl;                   // cos lat
   double k1, k0, k1t, k0t;     // Delta = k1 cos H + k0;  dDelta/dth = k1t cos H + k0t
-  double lnx_off, ix2_fac, x2_fac;  // ln(f/f0) = 3 ln v + lnx_off; (f0/f)^2 = ix2_fac v^-6; (f/f0)^2 = x2_fac v^6
+  double ix2_fac, x2_fac;      // (f0/f)^2 = ix2_fac v^-6; (f/f0)^2 = x2_fac v^6
   double xp_fac;               // (f/f0)^-4.14 = xp_fac v^-12.42
   double S0inv;                // 1/S0
   // S0 times the PSD shape's coefficients of v^-12.42, v^-6 and the rational
@@ -598,8 +598,8 @@ __host__ __device__ inline void site_setup(const double* p, const SiteDesc& sd, 
   sc.k0 = -kREarthS * sl * ct;
   sc.k1t = -kREarthS * cl * ct;
   sc.k0t = kREarthS * sl * st;
-  sc.lnx_off = -log(piM) - log(sd.f0);
-  sc.xp_fac = exp(-4.14 * sc.lnx_off);
+  const double lnx_off = -log(piM) - log(sd.f0);      // ln(f/f0) = 3 ln v + lnx_off
+  sc.xp_fac = exp(-4.14 * lnx_off);
   const double ix_fac = sd.f0 * piM;          // f0/f = ix_fac v^-3
   sc.ix2_fac = ix_fac * ix_fac;
   sc.x2_fac = 1.0 / sc.ix2_fac;
@@ -788,27 +788,11 @@ __host__ __device__ inline double series7(const double c[8], const VPow& w) {
   return FIRST == 0 ? h + c[0] : h;
 }
 
-// The same polynomial by Horner's rule, which keeps fewer values live than
-// the sum of products (whose coefficient loads the compiler issues all at
-// once).  The SNR kernel, which re-reads the coefficients from LDS, uses it;
-// the Fisher kernels use the sum, whether their coefficients sit in scalar
-// registers or in LDS.
-__host__ __device__ inline double horner7(const double c[8], double v) {
-  double h = c[7];
-  for (int k = 6; k >= 0; --k) h = fma(h, v, c[k]);
-  return h;
-}
-template <bool PSUM, int FIRST = 0>
-__host__ __device__ inline double poly7(const double c[8], const VPow& w) {
-  return PSUM ? series7<FIRST>(c, w) : horner7(c, w.p1);
-}
-
 // A phase series (PhaseSeries) at v: v^-5 (sum c_k v^k) + (l5 + l6 v) ln v
 // + t10 v^5 + t12 v^7.
-template <bool PSUM = true>
 __host__ __device__ inline double eval_phase(const PhaseSeries& s, const VPow& w, double iv5) {
   const double rest = fma(s.l6, w.Lv, fma(s.l5, w.L, fma(s.t12, w.p7, s.t10 * w.p5)));
-  return fma(poly7<PSUM>(s.c, w), iv5, rest);
+  return fma(series7(s.c, w), iv5, rest);
 }
 // The Mc series, whose l5 is zero, the eta series, whose c0 is (at fixed Mc
 // the leading order does not depend on eta), and the spin series, which
@@ -820,9 +804,8 @@ __host__ __device__ inline double eval_phase_eta(const PhaseSeries& s, const VPo
   const double rest = fma(s.l6, w.Lv, fma(s.l5, w.L, fma(s.t12, w.p7, s.t10 * w.p5)));
   return fma(series7<2>(s.c, w), iv5, rest);
 }
-template <bool PSUM = true>
 __host__ __device__ inline double eval_phase_spin(const PhaseSeries& s, const VPow& w, double iv5) {
-  return fma(poly7<PSUM, 3>(s.c, w), iv5, s.l5 * w.L);
+  return fma(series7<3>(s.c, w), iv5, s.l5 * w.L);
 }
 // The deformability series, which only have the tidal terms.
 __host__ __device__ inline double eval_phase_tidal(const PhaseSeries& s, const VPow& w) {
@@ -830,9 +813,9 @@ __host__ __device__ inline double eval_phase_tidal(const PhaseSeries& s, const V
 }
 // A tau*-type series at v: v^-8 (sum c_k v^k) + l6 ln v v^-2 (FIRST = 2: the
 // eta series, whose c0 is zero as that of the phase).
-template <bool PSUM = true, int FIRST = 0>
+template <int FIRST = 0>
 __host__ __device__ inline double eval_tau(const TauSeries& s, const VPow& w, double iv8, double iv2) {
-  return fma(poly7<PSUM, FIRST>(s.c, w), iv8, s.l6 * (w.L * iv2));
+  return fma(series7<FIRST>(s.c, w), iv8, s.l6 * (w.L * iv2));
 }
 
 // Frequency-point quantities shared by all sites.
@@ -912,7 +895,7 @@ __host__ __device__ inline void point_derivatives(const EventC& ec, bool rot, Po
   VPow pw;
   vpow(q.v, q.L, pw);
   q.gMc = rot ? eval_tau(ec.ts[kTsMc], pw, iv8, iv2) : 0.0;
-  q.gEta = rot ? eval_tau<true, 2>(ec.ts[kTsEta], pw, iv8, iv2) : 0.0;
+  q.gEta = rot ? eval_tau<2>(ec.ts[kTsEta], pw, iv8, iv2) : 0.0;
   q.pMc = eval_phase_mc(ec.ps[kPsMc], pw, iv5);
   q.pEta = eval_phase_eta(ec.ps[kPsEta], pw, iv5);
   q.ecv = 0.0;
@@ -922,14 +905,12 @@ __host__ __device__ inline void point_derivatives(const EventC& ec, bool rot, Po
   }
 }
 
-// PSUM: the evaluation form of the PN series (see horner7) and of the PSD's
-// power law (once per point when true, once per site otherwise).
 // EXPL: the point of an explicit grid (ec.fx) rather than of the log grid.
 // vrec (log grids only, NULL: evaluate directly): v, 1/v and v^-12.42 at the
 // point, carried by the caller from an earlier point (see GridWalk).
 // inner: the caller knows that k is neither end of the grid (a uniform value,
 // so that the end weights cost a wavefront inside the grid nothing).
-template <bool PSUM = true, bool EXPL = false, bool ECC = false>
+template <bool EXPL = false, bool ECC = false>
 __host__ __device__ inline void point_setup(const EventC& ec, int32_t k, bool need_derivs, bool rot,
                                             Point& q, int psd = kPsdF64, const double* vrec = nullptr,
                                             bool inner = false) {
@@ -971,7 +952,7 @@ __host__ __device__ inline void point_setup(const EventC& ec, int32_t k, bool ne
   q.vpsd = 0.0;
   if (!EXPL && vrec && psd != kPsdNone) {
     q.vpsd = vrec[2];
-  } else if (PSUM && psd == kPsdF64) {
+  } else if (psd == kPsdF64) {
     q.vpsd = exp(-12.42 * L);
   } else if (psd == kPsdF32) {   // 2^y with the integer part of y split off exactly
     const double y = (-12.42 / kLn2) * L, ny = rint(y);
@@ -979,34 +960,25 @@ __host__ __device__ inline void point_setup(const EventC& ec, int32_t k, bool ne
   }
   VPow pw;
   vpow(v, L, pw);
-  const double th = rot ? ec.thc + eval_tau<PSUM>(ec.ts[kTsTheta], pw, iv8, iv2) : ec.thc;
+  const double th = rot ? ec.thc + eval_tau(ec.ts[kTsTheta], pw, iv8, iv2) : ec.thc;
   sincos_moderate(th, &q.sth, &q.cth);
   if (need_derivs) point_derivatives<ECC>(ec, rot, q);
 }
 
 // The phase-only derivative coefficients of a point: c = (-1, dPsi/dchi1,
 // dPsi/dchi2[, dPsi/dLambda1, dPsi/dLambda2][, dPsi/de0]).
-template <int NPI, bool PSUM = true>
+template <int NPI>
 __host__ __device__ inline void phase_only_coefficients(const EventC& ec, const Point& q, double* c) {
   using PO = PhaseOnly<NPI>;
   const double iv = q.iv, iv2 = iv * iv, iv5 = iv2 * iv2 * iv;
   VPow pw;
   vpow(q.v, q.L, pw);
   c[0] = -1.0;
-  if (PSUM) {      // the spin and deformability series' structural zeros skipped
-    c[1] = eval_phase_spin<true>(ec.ps[kPsChi1], pw, iv5);
-    c[2] = eval_phase_spin<true>(ec.ps[kPsChi2], pw, iv5);
-    if (PO::tidal) {
-      c[3] = eval_phase_tidal(ec.ps[kPsL1], pw);
-      c[4] = eval_phase_tidal(ec.ps[kPsL2], pw);
-    }
-  } else {         // the general form (fewer live values)
-    c[1] = eval_phase<false>(ec.ps[kPsChi1], pw, iv5);
-    c[2] = eval_phase<false>(ec.ps[kPsChi2], pw, iv5);
-    if (PO::tidal) {
-      c[3] = eval_phase<false>(ec.ps[kPsL1], pw, iv5);
-      c[4] = eval_phase<false>(ec.ps[kPsL2], pw, iv5);
-    }
+  c[1] = eval_phase_spin(ec.ps[kPsChi1], pw, iv5);
+  c[2] = eval_phase_spin(ec.ps[kPsChi2], pw, iv5);
+  if (PO::tidal) {
+    c[3] = eval_phase_tidal(ec.ps[kPsL1], pw);
+    c[4] = eval_phase_tidal(ec.ps[kPsL2], pw);
   }
   if (PO::ecc) c[NPI - 1] = ec.ecc_e0 * q.ecv;
 }
@@ -1016,16 +988,13 @@ __host__ __device__ inline void phase_only_coefficients(const EventC& ec, const 
 struct SitePoint {
   double P[4], PH[4], Pt[4];
   double dH, dT;      // dDelta/dH, dDelta/dtheta
-  double om;          // 4 w A^2 / S_n(f)
 };
 
-template <bool PSUM = true>
-__host__ __device__ inline double psd_weight_of(double xp_fac, double lnx_off, double ix2_fac,
-                                                double x2_fac, double S0inv, const Point& q) {
+__host__ __device__ inline double psd_weight_of(double xp_fac, double ix2_fac, double x2_fac, double S0inv,
+                                                const Point& q) {
   // S_n = S0 [x^-4.14 - 5 x^-2 + 111 (1 - x^2 + x^4/2)/(1 + x^2/2)], x = f/f0;
   // x^-4.14 = xp_fac v^-12.42 with the power of v evaluated once per point
-  // (PSUM), or exp(-4.14 ln x) here
-  const double xp = PSUM ? xp_fac * q.vpsd : exp(-4.14 * fma(3.0, q.L, lnx_off));
+  const double xp = xp_fac * q.vpsd;
   const double ix2 = ix2_fac * q.iv6;              // (f0/f)^2
   const double x2 = x2_fac * q.v6;                 // (f/f0)^2
   const double num = fma(0.5 * x2, x2, 1.0 - x2);
@@ -1062,35 +1031,10 @@ __host__ __device__ inline double table_weight(const double* __restrict__ tf, co
 
 // TAB = false: instantiations for networks without sampled curves, which
 // leave the check out of the per-point code.
-template <bool PSUM = true, bool TAB = true>
+template <bool TAB = true>
 __host__ __device__ inline void psd_weight(const SiteC& sc, const Point& q, double& om) {
   if (TAB && sc.tab_kind) om = table_weight(sc.tab_f, sc.tab_S, sc.tab_n, sc.tab_kind, sc.S0inv, q.w4A2, q.f);
-  else om = psd_weight_of<PSUM>(sc.xp_fac, sc.lnx_off, sc.ix2_fac, sc.x2_fac, sc.S0inv, q);
-}
-
-// The same weight with the PSD shape evaluated in FP32 (mixed form).  The
-// weight is a positive factor per grid point, so a relative error e in it
-// keeps the Fisher matrix between (1 - e) Gamma and (1 + e) Gamma in the
-// positive-semidefinite order: SNR^2 moves by at most e and every sigma_i by
-// at most about e/2, whatever the condition number.  Errors in the
-// derivative vectors or in the sums have no such bound, which is why they
-// stay FP64.  x^-4.14 = xp_fac v^-12.42, the power of v taken once per point
-// as 2^y with y = -12.42 log2 v formed in FP64 and its integer part split
-// off exactly (point_setup, kPsdF32), so the FP32 exponential sees
-// |r| <= 1/2; x^2 and x^-2 are FP64 products rounded once; the quotient uses
-// the FP32 reciprocal.
-template <bool TAB = true>
-__host__ __device__ inline void psd_weight_f32(const SiteC& sc, const Point& q, double& om) {
-  if (TAB && sc.tab_kind) {   // a sampled curve: the FP64 weight
-    om = table_weight(sc.tab_f, sc.tab_S, sc.tab_n, sc.tab_kind, sc.S0inv, q.w4A2, q.f);
-    return;
-  }
-  const float xp = (float)(sc.xp_fac * q.vpsd);
-  const float x2 = (float)(sc.x2_fac * q.v6), ix2 = (float)(sc.ix2_fac * q.iv6);
-  const float num = fmaf(0.5f * x2, x2, 1.0f - x2);
-  const float den = fmaf(0.5f, x2, 1.0f);
-  const float top = fmaf(fmaf(-5.0f, ix2, xp), den, 111.0f * num);
-  om = q.w4A2 * sc.S0inv * (double)(den * recipf(top));
+  else om = psd_weight_of(sc.xp_fac, sc.ix2_fac, sc.x2_fac, sc.S0inv, q);
 }
 
 // The square root of the weight, r = sqrt(4 w A^2 / S_n(f)), which the
@@ -1099,16 +1043,12 @@ __host__ __device__ inline void psd_weight_f32(const SiteC& sc, const Point& q, 
 // in the pattern values, so the weighted sums follow from r D with no
 // per-entry weight product.  With S_n = S0 top / den (psd_weight_of),
 // r = sqrt(4 w A^2) den / sqrt(den S0 top); S0 top is formed from the site's
-// S0-scaled coefficients, so 1/S0 costs nothing per point.  A sampled curve,
-// and the per-site evaluation of the power law (PSUM = false), take the root
-// of the full weight.
-template <bool PSUM = true, bool TAB = true>
+// S0-scaled coefficients, so 1/S0 costs nothing per point.  A sampled curve
+// takes the root of the full weight.
+template <bool TAB = true>
 __host__ __device__ inline double psd_root_weight(const SiteC& sc, const Point& q) {
-  if ((TAB && sc.tab_kind) || !PSUM) {
-    double om;
-    psd_weight<PSUM, TAB>(sc, q, om);
-    return sqrt(om);
-  }
+  if (TAB && sc.tab_kind)
+    return sqrt(table_weight(sc.tab_f, sc.tab_S, sc.tab_n, sc.tab_kind, sc.S0inv, q.w4A2, q.f));
   const double x2 = sc.x2_fac * q.v6;              // (f/f0)^2
   const double num = fma(fma(0.5, x2, -1.0), x2, 1.0);
   const double den = fma(0.5, x2, 1.0);
@@ -1116,11 +1056,17 @@ __host__ __device__ inline double psd_root_weight(const SiteC& sc, const Point& 
   return (q.rw * den) * rsqrt_d(den * topS);
 }
 
-// The same root in the mixed form: the shape as in psd_weight_f32,
-// sqrt(den / top) in FP32 (den/top = S0/S_n stays within FP32's range), so a
-// relative error e in r is one of about 2e in the weight, the positive factor
-// whose error psd_weight_f32 bounds.  Measured on sampled events of the BNS
-// catalogue: Fisher within 4.2e-8 of sqrt(Gamma_aa Gamma_bb), SNR within 1.9e-8.
+// The same root with the PSD shape in FP32 (mixed form).  The weight is a
+// positive factor per grid point, so a relative error e in it keeps the
+// Fisher matrix between (1 - e) Gamma and (1 + e) Gamma in the
+// positive-semidefinite order: SNR^2 moves by at most e and every sigma_i by
+// at most about e/2, whatever the condition number.  Errors in the response
+// vectors or in the sums have no such bound, which is why they stay FP64.
+// x^-4.14 = xp_fac v^-12.42, the power of v taken once per point; x^2 and x^-2
+// are FP64 products rounded once; sqrt(den / top) in FP32 (den/top = S0/S_n
+// stays within FP32's range), so a relative error e in r is one of about 2e in
+// the weight.  Measured on sampled events of the BNS catalogue: Fisher within
+// 4.2e-8 of sqrt(Gamma_aa Gamma_bb), SNR within 1.9e-8.
 template <bool TAB = true>
 __host__ __device__ inline double psd_root_weight_f32(const SiteC& sc, const Point& q) {
   if (TAB && sc.tab_kind)
@@ -1133,9 +1079,7 @@ __host__ __device__ inline double psd_root_weight_f32(const SiteC& sc, const Poi
   return (q.rw * sc.rS0inv) * (double)sqrtf_hw(den * recipf(top));
 }
 
-template <bool MIXED = false, bool PSUM = true, bool TAB = true>
-__host__ __device__ inline void site_point(const SiteC& sc, const Point& q, bool need_derivs,
-                                           SitePoint& sp) {
+__host__ __device__ inline void site_point(const SiteC& sc, const Point& q, SitePoint& sp) {
   const double cH = q.cth * sc.cdl - q.sth * sc.sdl;
   const double sH = q.sth * sc.cdl + q.cth * sc.sdl;
   const double EX = cH, EY = -sc.ct * sH, NX = -sc.sl * sH, NY = -(sc.slct * cH + sc.clst);
@@ -1143,9 +1087,6 @@ __host__ __device__ inline void site_point(const SiteC& sc, const Point& q, bool
   sp.P[1] = EX * NX - EY * NY;
   sp.P[2] = EX * EY - NX * NY;
   sp.P[3] = EX * NY + NX * EY;
-  if (MIXED) psd_weight_f32<TAB>(sc, q, sp.om);
-  else psd_weight<PSUM, TAB>(sc, q, sp.om);
-  if (!need_derivs) return;
   const double EXh = -sH, EYh = -sc.ct * cH, NXh = -sc.sl * cH, NYh = sc.slct * sH;
   sp.PH[0] = EX * EXh - NX * NXh - EY * EYh + NY * NYh;
   sp.PH[1] = EXh * NX + EX * NXh - EYh * NY - EY * NYh;
@@ -1171,7 +1112,7 @@ struct SiteTrig {
   double om;          // 4 w A^2 / S_n(f)
 };
 
-template <bool MIXED = false, bool PSUM = true, bool TAB = true>
+template <bool TAB = true>
 __host__ __device__ inline void site_trig(const SiteC& sc, const Point& q, SiteTrig& sp) {
   const double cH = q.cth * sc.cdl - q.sth * sc.sdl;
   const double sH = q.sth * sc.cdl + q.cth * sc.sdl;
@@ -1180,8 +1121,7 @@ __host__ __device__ inline void site_trig(const SiteC& sc, const Point& q, SiteT
   sp.c2H = fma(cH, cH, -sH * sH);
   sp.sc = sH * cH;
   sp.m4 = -4.0 * sp.sc;
-  if (MIXED) psd_weight_f32<TAB>(sc, q, sp.om);
-  else psd_weight<PSUM, TAB>(sc, q, sp.om);
+  psd_weight<TAB>(sc, q, sp.om);
   sp.dH = -sc.k1 * sH;
   sp.dT = fma(sc.k1t, cH, sc.k0t);
 }
@@ -1197,13 +1137,13 @@ struct SiteTrigR {
   double u, w;                  // 2 pi f dDelta/dH, 2 pi f dDelta/dtheta
 };
 
-template <bool MIXED = false, bool PSUM = true, bool TAB = true>
+template <bool MIXED = false, bool TAB = true>
 __host__ __device__ inline void site_trig_root(const SiteC& sc, const Point& q, SiteTrigR& sp) {
   const double cH = q.cth * sc.cdl - q.sth * sc.sdl;
   const double sH = q.sth * sc.cdl + q.cth * sc.sdl;
   sp.cH = cH;
   sp.sH = sH;
-  const double r = MIXED ? psd_root_weight_f32<TAB>(sc, q) : psd_root_weight<PSUM, TAB>(sc, q);
+  const double r = MIXED ? psd_root_weight_f32<TAB>(sc, q) : psd_root_weight<TAB>(sc, q);
   sp.r = r;
   sp.rc = r * cH;
   sp.rs = r * sH;
@@ -1323,12 +1263,12 @@ struct NetSums {
 // points (of one event).  The patterns are trigonometric polynomials in H whose coefficients carry
 // sqrt(weff), and the basis carries the root weight r, so every product of
 // two of the values below is weighted by weff r^2.
-template <int NQ, bool MIXED = false, bool PSUM = true, bool TAB = true>
+template <int NQ, bool MIXED = false, bool TAB = true>
 __host__ __device__ inline void site_sums(const AmpFactors& am, const Point (&q)[NQ], const SiteC& st, int n_eff,
                                           NetSums (&net)[NQ]) {
   SiteTrigR sp[NQ];
 #pragma unroll
-  for (int i = 0; i < NQ; ++i) site_trig_root<MIXED, PSUM, TAB>(st, q[i], sp[i]);
+  for (int i = 0; i < NQ; ++i) site_trig_root<MIXED, TAB>(st, q[i], sp[i]);
   int j = 0;
   do {
     const double(*c)[5] = st.jk[j];
@@ -1477,19 +1417,14 @@ __host__ __device__ inline ActiveSites active_sites(const SiteC* sc, int n_site)
   return a;
 }
 
-// The sums over the network's interferometers at NQ points k, k + stride, ...
-// of an event (q, net), from the grid values vrec[NQ][3] of those points
-// (NULL: evaluated directly).  Points at or past kend stand for the point
-// kend - 1 (whose grid values the caller gives) and get zero weight; inner
-// says that no point is an end of the grid or past kend.  This part needs the
-// points' grid values and sidereal angle only; the phase and angle
-// derivatives follow it (finish_point), so that they and the sums are not
-// held at the same time as the sites' values.
-template <int NQ, int NPI, bool ROT, bool MIXED, bool PSUM, bool EXPL, bool TAB>
-__host__ __device__ inline void network_sums(const EventC& ec, const SiteC* sc, const ActiveSites& act, int32_t k,
-                                             int32_t stride, int32_t kend, bool inner, const double (*vrec)[3],
-                                             Point (&q)[NQ], NetSums (&net)[NQ]) {
-  const AmpFactors am = amp_factors(ec);
+// The grid values, weights and sidereal angles of NQ points k, k + stride, ...
+// of an event, from vrec[NQ][3] (GridWalk; NULL: evaluated directly).  Points
+// at or past kend stand for the point kend - 1 (whose grid values the caller
+// gives) and get zero weight; inner says that no point is an end of the grid
+// or past kend.
+template <int NQ, bool MIXED, bool ROT, bool ECC, bool EXPL>
+__host__ __device__ inline void point_block(const EventC& ec, int32_t k, int32_t stride, int32_t kend, bool inner,
+                                            const double (*vrec)[3], Point (&q)[NQ]) {
 #pragma unroll
   for (int i = 0; i < NQ; ++i) {
     int32_t ki = k + i * stride;
@@ -1497,21 +1432,52 @@ __host__ __device__ inline void network_sums(const EventC& ec, const SiteC* sc, 
       keep_branch();
       if (ki >= kend) ki = kend - 1;
     }
-    point_setup<PSUM, EXPL, PhaseOnly<NPI>::ecc>(ec, ki, false, ROT, q[i], MIXED ? kPsdF32 : kPsdF64,
-                                                 vrec ? vrec[i] : nullptr, inner);
+    point_setup<EXPL, ECC>(ec, ki, false, ROT, q[i], MIXED ? kPsdF32 : kPsdF64, vrec ? vrec[i] : nullptr, inner);
     if (!inner) {
       keep_branch();
       if (k + i * stride >= kend) q[i].rw = q[i].w4A2 = 0.0;
     }
-    net[i] = NetSums{};
   }
+}
+
+// The grid values of a lane's next NQ points (k and on, the walk's stride
+// apart) from its walk, those of the point k1 - 1 where a point is past it.
+template <int NQ>
+__host__ __device__ inline void walk_points(const EventC& ec, GridWalk& gw, int32_t k, int32_t stride, int32_t k1,
+                                            bool inner, double (&vv)[NQ][3]) {
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) vv[i][c] = gw.val[c];
+    gw.step();
+  }
+  if (!inner) {
+    keep_branch();
+#pragma unroll
+    for (int i = 0; i < NQ; ++i)
+      if (k + i * stride >= k1) grid_values(ec, k1 - 1, vv[i]);
+  }
+}
+
+// The sums over the network's interferometers at the points of point_block
+// (q, net).  This part needs the points' grid values and sidereal angle only;
+// the phase and angle derivatives follow it (finish_point), so that they and
+// the sums are not held at the same time as the sites' values.
+template <int NQ, int NPI, bool ROT, bool MIXED, bool EXPL, bool TAB>
+__host__ __device__ inline void network_sums(const EventC& ec, const SiteC* sc, const ActiveSites& act, int32_t k,
+                                             int32_t stride, int32_t kend, bool inner, const double (*vrec)[3],
+                                             Point (&q)[NQ], NetSums (&net)[NQ]) {
+  const AmpFactors am = amp_factors(ec);
+  point_block<NQ, MIXED, ROT, PhaseOnly<NPI>::ecc, EXPL>(ec, k, stride, kend, inner, vrec, q);
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) net[i] = NetSums{};
   if (act.n == 0) return;
   // one loop without a way round its body: a site skipped inside the loop
   // would have the compiler copy every sum where the two ways meet
   uint32_t list = act.list;
   int left = act.n;
   do {
-    site_sums<NQ, MIXED, PSUM, TAB>(am, q, sc[list & 7u], 1 + (int)(list >> 3 & 1u), net);
+    site_sums<NQ, MIXED, TAB>(am, q, sc[list & 7u], 1 + (int)(list >> 3 & 1u), net);
     list >>= 4;
   } while (--left > 0);
 }
@@ -1520,30 +1486,30 @@ __host__ __device__ inline void network_sums(const EventC& ec, const SiteC* sc, 
 // G[kGramAcc], U[8], W (accumulate_sums) and its phase-only coefficients
 // c[NPI] = (-1, dPsi/dchi1, dPsi/dchi2[, dPsi/dLambda1, dPsi/dLambda2]
 // [, dPsi/de0]).
-template <int NPI, bool ROT, bool PSUM>
+template <int NPI, bool ROT>
 __host__ __device__ inline void finish_point(const EventC& ec, Point& q, const NetSums& n, double* G, double* U,
                                              double& W, double* cph) {
   reread(q.v, q.iv);
   point_derivatives<PhaseOnly<NPI>::ecc>(ec, ROT, q);
   accumulate_sums<ROT>(ec, q, n, G, U, W);
-  phase_only_coefficients<NPI, PSUM>(ec, q, cph);
+  phase_only_coefficients<NPI>(ec, q, cph);
 }
 
 // One grid point k of an event as a whole.
-template <int NPI, bool ROT, bool MIXED = false, bool PSUM = true, bool EXPL = false, bool TAB = true>
+template <int NPI, bool ROT, bool MIXED = false, bool EXPL = false, bool TAB = true>
 __host__ __device__ inline void accumulate_point(const EventC& ec, const SiteC* sc, const ActiveSites& act,
                                                  int32_t k, double* G, double* U, double& W,
                                                  double* cph, const double (*vrec)[3] = nullptr) {
   Point q[1];
   NetSums n[1];
-  network_sums<1, NPI, ROT, MIXED, PSUM, EXPL, TAB>(ec, sc, act, k, 0, k + 1, false, vrec, q, n);
-  finish_point<NPI, ROT, PSUM>(ec, q[0], n[0], G, U, W, cph);
+  network_sums<1, NPI, ROT, MIXED, EXPL, TAB>(ec, sc, act, k, 0, k + 1, false, vrec, q, n);
+  finish_point<NPI, ROT>(ec, q[0], n[0], G, U, W, cph);
 }
-template <int NPI, bool ROT, bool MIXED = false, bool PSUM = true, bool EXPL = false, bool TAB = true>
+template <int NPI, bool ROT, bool MIXED = false, bool EXPL = false, bool TAB = true>
 __host__ __device__ inline void accumulate_point(const EventC& ec, const SiteC* sc, int n_site,
                                                  int32_t k, double* G, double* U, double& W,
                                                  double* cph) {
-  accumulate_point<NPI, ROT, MIXED, PSUM, EXPL, TAB>(ec, sc, active_sites(sc, n_site), k, G, U, W, cph);
+  accumulate_point<NPI, ROT, MIXED, EXPL, TAB>(ec, sc, active_sites(sc, n_site), k, G, U, W, cph);
 }
 
 // The 8x8 upper-triangle block of (Mc, eta, dL, theta, phi, iota, psi, tc)

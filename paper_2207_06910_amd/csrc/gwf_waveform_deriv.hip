@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kWBlock) void waveform_deriv_kernel(WaveformArgs a)
     // reads) rather than held in registers across iterations
     asm volatile("" ::: "memory");
     Point q;
-    point_setup<true, EXPL, PO::ecc>(ec, k, true, ROT, q, kPsdNone);
+    point_setup<EXPL, PO::ecc>(ec, k, true, ROT, q, kPsdNone);
     VPow pw;
     vpow(q.v, q.L, pw);
     const double iv = q.iv, iv2 = iv * iv, iv5 = iv2 * iv2 * iv;
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kWBlock) void waveform_deriv_kernel(WaveformArgs a)
       asm volatile("" ::: "memory");
       const SiteC& st = sc[s];
       SitePoint sp;
-      site_point<false, true>(st, q, true, sp);
+      site_point(st, q, sp);
       const SitePhase ph = site_phase(q, sp);
       const double cH = q.cth * st.cdl - q.sth * st.sdl;
       double sn, cs;
