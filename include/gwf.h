@@ -460,6 +460,40 @@ enum { GWF_BASIS_CHI_SA = 1, GWF_BASIS_LAMBDA_TILDE = 2, GWF_BASIS_M1M2 = 4 };
 gwf_status gwf_fisher_basis(int32_t P, int64_t n, const double* fisher, const gwf_events* ev,
                             uint32_t basis, double* out, int32_t* status, void* stream);
 
+/* -------------------------------------------------------- split form */
+/* gwf_snr, gwf_fisher and gwf_fisher_ifo with each event's grid split over
+ * several workgroups, in a workspace the caller gives for the call: the same
+ * outputs, statuses and thresholds (a split sum differs in its last bits), for
+ * log grids.  For few events, long grids or uneven ones, where one workgroup
+ * per event leaves the chip idle; the set-up, part and combine kernels are
+ * ordinary launches on `stream`, nothing is allocated or read back.
+ *   parts      1..GWF_SPLIT_PARTS_MAX, the most parts of one event's grid: a
+ *              grid of n points has parts of ceil(n / parts) points, rounded up
+ *              to a multiple of 512
+ *   work       device, 256-byte aligned, of at least gwf_split_bytes bytes; used
+ *              until the stream has passed the call; contents need not be set
+ *   gwf_split_bytes   the workspace of n events (-1 and gwf_last_error if the
+ *              arguments are invalid); what: 0 gwf_snr_split, 1 gwf_fisher_split,
+ *              2 the same with snr_th > 0 or snr_ifo, 3 gwf_fisher_ifo_split
+ * Other arguments as for the plain calls; explicit grids return
+ * GWF_E_UNSUPPORTED. */
+#define GWF_SPLIT_PARTS_MAX 64
+
+int64_t gwf_split_bytes(int64_t n, const gwf_network* net, uint32_t flags, int32_t what, int32_t parts);
+
+gwf_status gwf_snr_split(const gwf_events* ev, const gwf_network* net, const gwf_grid* grid,
+                         uint32_t flags, int32_t parts, double* snr, double* snr_ifo, int32_t* status,
+                         void* work, int64_t work_bytes, void* stream);
+
+gwf_status gwf_fisher_split(const gwf_events* ev, const gwf_network* net, const gwf_grid* grid,
+                            uint32_t flags, double snr_th, int32_t parts, double* fisher, double* snr,
+                            double* snr_ifo, int32_t* status, void* work, int64_t work_bytes,
+                            void* stream);
+
+gwf_status gwf_fisher_ifo_split(const gwf_events* ev, const gwf_network* net, const gwf_grid* grid,
+                                uint32_t flags, int32_t parts, double* fisher_ifo, int32_t* status,
+                                void* work, int64_t work_bytes, void* stream);
+
 /* ------------------------------------------------------ batched form */
 /* A plan runs the Fisher (and optionally the inversion) of one catalogue
  * repeatedly: the work is cut into items of at most `chunk` grid points

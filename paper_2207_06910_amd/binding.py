@@ -6,6 +6,7 @@ provides device memory and the stream.  The library must have been built
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 
@@ -128,6 +129,15 @@ def load():
         lib.gwf_plan_get_info.restype = i32
         lib.gwf_plan_destroy.argtypes = [vp]
         lib.gwf_plan_destroy.restype = i32
+        desc = [ctypes.POINTER(Events), ctypes.POINTER(Network), ctypes.POINTER(Grid), ctypes.c_uint32]
+        lib.gwf_split_bytes.argtypes = [i64, ctypes.POINTER(Network), ctypes.c_uint32, i32, i32]
+        lib.gwf_split_bytes.restype = i64
+        lib.gwf_snr_split.argtypes = desc + [i32, vp, vp, vp, vp, i64, vp]
+        lib.gwf_snr_split.restype = i32
+        lib.gwf_fisher_split.argtypes = desc + [d, i32, vp, vp, vp, vp, vp, i64, vp]
+        lib.gwf_fisher_split.restype = i32
+        lib.gwf_fisher_ifo_split.argtypes = desc + [i32, vp, vp, vp, i64, vp]
+        lib.gwf_fisher_ifo_split.restype = i32
         lib.gwf_network_n_ifo.argtypes = [ctypes.POINTER(Network)]
         lib.gwf_network_n_ifo.restype = i32
         lib.gwf_last_error.restype = ctypes.c_char_p
@@ -244,6 +254,9 @@ class DeviceWorkload:
                                                                   device=device)
         self.curves = upload_curves(self.sites, device)
         self.n_ifo = n_ifo(self.sites)
+        # the catalogue's longest grid and all its points, by which the plain
+        # calls choose how they split the work (never what they compute)
+        self.points_max, self.points = int(np.max(wl.npts)), int(np.sum(wl.npts, dtype=np.int64))
 
     def with_sites(self, sites) -> "DeviceWorkload":
         """The same device arrays with another network of the same shapes
@@ -276,6 +289,48 @@ class DeviceWorkload:
         return ev, net, grid, keep
 
 
+SPLIT_SNR, SPLIT_FISHER, SPLIT_SNR_FISHER, SPLIT_IFOS = 0, 1, 2, 3
+SPLIT_WORK_MAX = 256 << 20      # bytes of workspace a plain call may take
+
+
+def _split(dw: DeviceWorkload, net, what, stream):
+    """(parts, workspace) of a plain call in the split form (gwf_*_split), or
+    None where one workgroup per event is the better form.  That is: explicit
+    grids, which the split form does not take; catalogues whose constants would
+    need more than SPLIT_WORK_MAX, which fill the chip by themselves; and few
+    events with short grids, where one launch beats three.  Measured, plain and
+    split, us: Fisher of 400 events of 1800 points 38 and 44, of 1500 events of
+    1000 points 67 and 59, of one event of 3000 points 36 and 32; SNR of 100
+    events of 4000 points 26 and 33, of one event of 10^4 points 71 and 36."""
+    import torch
+    n = dw.n
+    short = 6144 if what == SPLIT_SNR else 2048
+    if dw.grid_f is not None or (dw.points_max <= short and dw.points <= 1 << 20 and
+                                 (what != SPLIT_IFOS or dw.n_ifo == 1)):
+        return None
+    if what == SPLIT_SNR_FISHER and dw.flags & ECCENTRIC:
+        return None             # an event whose e0 is invalid keeps the SNR of its circular form there
+    # parts of about 1/2048 of the work (the chip runs 512 workgroups at a time)
+    # in whole iterations of a workgroup (512 points), 2 to 16 of them: 600
+    # pairs' matrices 258 us with 1/8192, 234 with 1/4096, 210 with 1/2048
+    per = dw.points * (dw.n_ifo if what == SPLIT_IFOS else 1) // 2048
+    length = 512 * min(16, max(2, -(-per // 512)))
+    parts = min(64, -(-dw.points_max // length))
+    size = load().gwf_split_bytes(n, ctypes.byref(net), dw.flags, what, parts)
+    if size < 0 or size > SPLIT_WORK_MAX:
+        return None
+    # the workspace belongs to the call's stream: the allocator may hand it out
+    # again once the stream has passed the call.  Under graph capture, and
+    # without memory for it, the call runs as before it could be split.
+    with torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext():
+        if torch.cuda.is_current_stream_capturing():
+            return None
+        try:
+            return parts, torch.empty(size, dtype=torch.uint8, device=dw.par.device)
+        except torch.OutOfMemoryError:
+            return None
+
+
 def snr(dw: DeviceWorkload, per_ifo=False, stream=None, out=None):
     import torch
     dev = dw.par.device
@@ -285,6 +340,13 @@ def snr(dw: DeviceWorkload, per_ifo=False, stream=None, out=None):
         res.setdefault("snr_ifo", torch.empty((dw.n_ifo, dw.n), dtype=torch.float64, device=dev))
     res.setdefault("status", torch.empty(dw.n, dtype=torch.int32, device=dev))
     ev, net, grid, keep = dw.descriptors()
+    split = _split(dw, net, SPLIT_SNR, stream)
+    if split:
+        parts, work = split
+        _check(load().gwf_snr_split(ctypes.byref(ev), ctypes.byref(net), ctypes.byref(grid), dw.flags, parts,
+                                    _ptr(res["snr"]), _ptr(res.get("snr_ifo")), _ptr(res["status"]), _ptr(work),
+                                    work.numel(), _stream(stream)), "gwf_snr_split")
+        return res
     _check(load().gwf_snr(ctypes.byref(ev), ctypes.byref(net), ctypes.byref(grid), dw.flags,
                           _ptr(res["snr"]), _ptr(res.get("snr_ifo")), _ptr(res["status"]),
                           _stream(stream)), "gwf_snr")
@@ -303,6 +365,14 @@ def fisher(dw: DeviceWorkload, snr_th=0.0, per_ifo_snr=False, stream=None, out=N
     if per_ifo_snr:
         res.setdefault("snr_ifo", torch.empty((dw.n_ifo, dw.n), dtype=torch.float64, device=dev))
     ev, net, grid, keep = dw.descriptors()
+    split = _split(dw, net, SPLIT_SNR_FISHER if snr_th > 0.0 or "snr_ifo" in res else SPLIT_FISHER, stream)
+    if split:
+        parts, work = split
+        _check(load().gwf_fisher_split(ctypes.byref(ev), ctypes.byref(net), ctypes.byref(grid), dw.flags,
+                                       float(snr_th), parts, _ptr(res["fisher"]), _ptr(res["snr"]),
+                                       _ptr(res.get("snr_ifo")), _ptr(res["status"]), _ptr(work), work.numel(),
+                                       _stream(stream)), "gwf_fisher_split")
+        return res
     _check(load().gwf_fisher(ctypes.byref(ev), ctypes.byref(net), ctypes.byref(grid), dw.flags,
                              float(snr_th), _ptr(res["fisher"]), _ptr(res["snr"]),
                              _ptr(res.get("snr_ifo")), _ptr(res["status"]), _stream(stream)),
@@ -357,6 +427,13 @@ def fisher_ifo(dw: DeviceWorkload, stream=None, out=None):
             and tuple(F.shape) == (dw.n_ifo, P, P, dw.n)):
         raise GwfError(f"fisher_ifo must be a contiguous float64 device tensor of shape ({dw.n_ifo}, {P}, {P}, {dw.n})")
     ev, net, grid, keep = dw.descriptors()
+    split = _split(dw, net, SPLIT_IFOS, stream)
+    if split:
+        parts, work = split
+        _check(load().gwf_fisher_ifo_split(ctypes.byref(ev), ctypes.byref(net), ctypes.byref(grid), dw.flags, parts,
+                                           _ptr(F), _ptr(res["status"]), _ptr(work), work.numel(), _stream(stream)),
+               "gwf_fisher_ifo_split")
+        return res
     _check(load().gwf_fisher_ifo(ctypes.byref(ev), ctypes.byref(net), ctypes.byref(grid), dw.flags,
                                  _ptr(F), _ptr(res["status"]), _stream(stream)), "gwf_fisher_ifo")
     return res

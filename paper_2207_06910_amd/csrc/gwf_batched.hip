@@ -23,6 +23,7 @@
 // captured in a HIP graph and replayed.
 #include "gwf_batched.hpp"
 #include "gwf_fisher_body.hpp"
+#include "gwf_snr_body.hpp"
 
 namespace gwf {
 
@@ -32,9 +33,9 @@ __global__ void fill_i32_kernel(int32_t* p, int32_t v, int64_t n) {
 }
 
 // Lane e of the grid's row y: y = 0, 1, 2 form one part each of event e's
-// constants (EventC; the first part its status), y = 3 + s its constants of
-// site s (SiteC, with pi M formed from the parameters exactly as the event's
-// grid part forms it); all write straight into the workspace.  A site of an
+// constants (EventC; the first part its status), y = 3 + r its r-th site
+// constants (SiteSets; with pi M formed from the parameters exactly as the
+// event's grid part forms it); all write straight into the workspace.  A site of an
 // event whose set-up fails is written anyway and never read.  The rows are
 // independent workgroups, so a small catalogue's set-up takes as long as the
 // longest of the parts, not their sum.
@@ -56,13 +57,25 @@ __global__ __launch_bounds__(64) void setup_kernel(SetupArgs a) {
       ec.status = kEvInvalid;   // grid changed since the items were built, or longer than they allow
     if (a.status) a.status[e] = ec.status;
   } else if (row == 1) {
-    event_phase_setup(p, a.flags, a.evc[e]);
+    if (!a.no_phase) event_phase_setup(p, a.flags, a.evc[e]);
   } else if (row == 2) {
     event_angle_setup(p, a.fmin[e], a.flags, a.evc[e]);
   } else {
-    const int s = row - kSetupRows;
-    site_setup(p, a.net.site[s], kPi * total_mass_s(p), a.sic[e * a.net.n_site + s],
-               site_arms_on(a.active, a.ld, e, a.net, s));
+    const int r = row - kSetupRows;
+    int s = r;                                   // the entry's site
+    bool arms = a.sets == kSetsArms;
+    int32_t ifo_sel = 0;
+    if (a.sets == kSetsSitesArms && r >= a.net.n_site) {
+      s = r - a.net.n_site;
+      arms = true;
+    } else if (a.sets == kSetsIfos) {
+      ifo_sel = r + 1;
+      int left = r;
+      for (s = 0; left >= (a.net.site[s].shape == 1 ? 3 : 1); ++s) left -= a.net.site[s].shape == 1 ? 3 : 1;
+    }
+    const uint32_t on =
+        arms ? kArmsPlain : select_ifo(site_arms_on(a.active, a.ld, e, a.net, s), a.net, s, ifo_sel);
+    site_setup(p, a.net.site[s], kPi * total_mass_s(p), a.sic[e * a.n_set + r], on);
   }
 }
 
@@ -76,19 +89,38 @@ __global__ __launch_bounds__(kBlock, 2) void items_kernel(ItemsArgs a) {
   // workgroup b takes item b (the plan orders its items longest first, and
   // workgroups are dispatched in order); with the count on the device, the
   // grid is its upper bound and the surplus workgroups leave
-  const int32_t n_items = a.n_items_dev ? *a.n_items_dev : a.n_items;
-  const int64_t it = a.base + blockIdx.x;
-  if (it >= n_items) return;
-  const Item w = a.items[it];
+  Item w;
+  int32_t n_set = n_site, set0 = 0;
+  if (a.items) {
+    const int32_t n_items = a.n_items_dev ? *a.n_items_dev : a.n_items;
+    const int64_t it = a.base + blockIdx.x;
+    if (it >= n_items) return;
+    w = a.items[it];
+  } else {
+    // part-major within a matrix: the first parts, which every event has, come
+    // first, and the workgroups with nothing to do last
+    const uint32_t u = (uint32_t)(a.base + blockIdx.x), n = (uint32_t)a.n;
+    const uint32_t row = u / n, mat = row / (uint32_t)a.parts;
+    const int32_t part = (int32_t)(row - mat * (uint32_t)a.parts);
+    w.e = (int32_t)(u - row * n);
+    const int32_t ne = a.evc[w.e].n, len = part_length(ne, a.parts);
+    w.k0 = part * len;
+    w.k1 = min(ne, w.k0 + len);
+    if (a.evc[w.e].status || w.k0 >= ne) return;   // its sums are not read
+    w.slot = ((int32_t)mat * a.n + w.e) * a.parts + part;
+    n_set = a.n_set;
+    if (a.n_mat > 1) set0 = (int32_t)mat;
+  }
   const int32_t ew = __builtin_amdgcn_readfirstlane(w.e);
   const int32_t k0 = __builtin_amdgcn_readfirstlane(w.k0);
   const int32_t k1 = __builtin_amdgcn_readfirstlane(w.k1);
+  set0 = __builtin_amdgcn_readfirstlane(set0);
   // constants read through the constant address space: uniform, never
   // written during the kernel, so the compiler may use scalar loads
   typedef const __attribute__((address_space(4))) EventC CEventC;
   typedef const __attribute__((address_space(4))) SiteC CSiteC;
   CEventC* ecp = (CEventC*)(a.evc) + ew;
-  CSiteC* scp = (CSiteC*)(a.sic) + (int64_t)ew * n_site;
+  CSiteC* scp = (CSiteC*)(a.sic) + (int64_t)ew * n_set + set0;
   const EventC& ecg = *(const EventC*)ecp;
   const SiteC* scg = (const SiteC*)scp;
   double* out = a.partial + (int64_t)__builtin_amdgcn_readfirstlane(w.slot) * NACC;
@@ -106,19 +138,33 @@ __global__ void combine_kernel(CombineArgs a) {
   using Dm = FisherDims<NPI_>;
   constexpr int P = Dm::P, NPI = Dm::NPI, NACC = Dm::NACC;
   const int64_t t = a.base + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= a.n * NACC) return;
-  const int64_t e = t / NACC;
-  const int slot = (int)(t - e * NACC);
+  const int32_t n_mat = a.item_first ? 1 : a.n_mat;
+  if (t >= a.n * NACC * n_mat) return;
+  const int64_t u = t / NACC;                      // (matrix, event)
+  const int slot = (int)(t - u * NACC);
+  const int64_t mat = n_mat > 1 ? u / a.n : 0, e = u - mat * a.n;
   const int32_t st0 = a.evc[e].status;
   double s = 0.0;
-  if (!st0)
-    for (int32_t i = a.item_first[e]; i < a.item_first[e + 1]; ++i) s += a.partial[(int64_t)i * NACC + slot];
+  if (!st0) {
+    int64_t i0, i1;
+    if (a.item_first) {
+      i0 = a.item_first[e];
+      i1 = a.item_first[e + 1];
+    } else {
+      const int32_t ne = a.evc[e].n;
+      i0 = u * a.parts;
+      i1 = i0 + (ne - 1) / part_length(ne, a.parts) + 1;
+    }
+    for (int64_t i = i0; i < i1; ++i) s += a.partial[i * NACC + slot];
+  }
   int r, c;
   slot_position(slot, NPI, r, c);
-  if (r == 8 && c == 8) a.snr[e] = sqrt(s);
+  // an event skipped by the threshold keeps the SNR of the pass that skipped it
+  if (r == 8 && c == 8 && a.snr && st0 != kEvSkipped) a.snr[e] = sqrt(s);
   if (!rows_in(event_rows(a.par_mask, e), r, c)) s = 0.0;   // not one of the event's rows
-  a.fisher[((int64_t)r * P + c) * a.n + e] = s;
-  a.fisher[((int64_t)c * P + r) * a.n + e] = s;
+  double* F = a.fisher + mat * ((int64_t)P * P * a.n);
+  F[((int64_t)r * P + c) * a.n + e] = s;
+  F[((int64_t)c * P + r) * a.n + e] = s;
   // the set-up kernel wrote the parameter status; a non-finite sum adds its bit
   if (!st0 && !finite(s)) atomicOr(a.status + e, (int32_t)kEvNonFinite);
 }
@@ -194,8 +240,8 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s) {
 }
 
 hipError_t launch_setup(const SetupArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(setup_kernel, dim3((unsigned)((a.n + 63) / 64), (unsigned)(kSetupRows + a.net.n_site)), dim3(64),
-                     0, s, a);
+  hipLaunchKernelGGL(setup_kernel, dim3((unsigned)((a.n + 63) / 64), (unsigned)(kSetupRows + a.n_set)), dim3(64), 0, s,
+                     a);
   return hipGetLastError();
 }
 
@@ -234,7 +280,7 @@ int fisher_nacc(int npi) {
 }
 
 hipError_t launch_combine(const CombineArgs& a0, int npi, hipStream_t s) {
-  return launch_slices(a0, a0.n * fisher_nacc(npi), 256, 256, [&](const CombineArgs& a, dim3 grid, dim3 block) {
+  return launch_slices(a0, a0.n * fisher_nacc(npi) * (a0.item_first ? 1 : a0.n_mat), 256, 256, [&](const CombineArgs& a, dim3 grid, dim3 block) {
     switch (npi) {
       case 6: hipLaunchKernelGGL((combine_kernel<6>), grid, block, 0, s, a); break;
       case 5: hipLaunchKernelGGL((combine_kernel<5>), grid, block, 0, s, a); break;
@@ -242,6 +288,69 @@ hipError_t launch_combine(const CombineArgs& a0, int npi, hipStream_t s) {
       default: hipLaunchKernelGGL((combine_kernel<3>), grid, block, 0, s, a);
     }
   });
+}
+
+// The SNR sums of one part of one event's grid (split form), constants read by
+// scalar loads as in items_kernel.
+template <bool ROT, bool TAB>
+__global__ __launch_bounds__(kBlock, 2) void snr_parts_kernel(SnrPartsArgs a) {
+  __shared__ double red[kWaves][kMaxIfo];
+  const uint32_t u = (uint32_t)(a.base + blockIdx.x), n = (uint32_t)a.n;
+  const int32_t part = (int32_t)(u / n), e = (int32_t)(u - (uint32_t)part * n);
+  typedef const __attribute__((address_space(4))) EventC CEventC;
+  typedef const __attribute__((address_space(4))) SiteC CSiteC;
+  const EventC& ec = *(const EventC*)((CEventC*)(a.evc) + e);
+  const SiteC* sc = (const SiteC*)((CSiteC*)(a.sic) + (int64_t)e * a.n_set + a.set0);
+  const int32_t len = part_length(ec.n, a.parts), k0 = part * len;
+  if (ec.status || k0 >= ec.n) return;             // its sums are not read
+  double acc[kSnrSlots];
+#pragma unroll
+  for (int i = 0; i < kSnrSlots; ++i) acc[i] = 0.0;
+  snr_sums<ROT, false, TAB>(ec, sc, a.net.n_site, k0, min(ec.n, k0 + len), acc);
+  double t;
+  snr_reduce(acc, a.net.n_site, a.net.n_ifo, site_shapes(a.net), red, &t);
+  if ((int)threadIdx.x < a.net.n_ifo) a.partial[((int64_t)e * a.parts + part) * a.net.n_ifo + threadIdx.x] = t;
+}
+
+__global__ __launch_bounds__(64) void snr_combine_kernel(SnrCombineArgs a) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= a.n) return;
+  const int32_t st0 = a.evc[e].status;
+  const int32_t parts = st0 ? 0 : (a.evc[e].n - 1) / part_length(a.evc[e].n, a.parts) + 1;
+  double tot = 0.0;
+  for (int i = 0; i < a.n_ifo; ++i) {
+    double t = 0.0;
+    for (int32_t q = 0; q < parts; ++q) t += a.partial[(e * a.parts + q) * a.n_ifo + i];
+    if (a.active && !a.active[(int64_t)i * a.ld + e]) t = 0.0;   // off for this event
+    tot += t;
+    if (a.snr_ifo) a.snr_ifo[(int64_t)i * a.n + e] = sqrt(t);
+  }
+  const double snr = sqrt(tot);
+  a.snr[e] = snr;
+  if (st0) {
+    if (a.status) a.status[e] = st0;
+  } else if (a.snr_th > 0.0) {                     // the pass before the matrices
+    if (!(snr > a.snr_th)) {
+      a.evc[e].status = kEvSkipped;
+      if (a.status) a.status[e] = kEvSkipped;
+    }
+  } else if (a.status) {
+    a.status[e] = finite(tot) ? 0 : kEvNonFinite;
+  }
+}
+
+hipError_t launch_snr_parts(const SnrPartsArgs& a0, bool rot, bool tab, hipStream_t s) {
+  return launch_slices(a0, (int64_t)a0.n * a0.parts, 1, kBlock, [&](const SnrPartsArgs& a, dim3 grid, dim3 block) {
+    if (rot && tab) hipLaunchKernelGGL((snr_parts_kernel<true, true>), grid, block, 0, s, a);
+    else if (rot) hipLaunchKernelGGL((snr_parts_kernel<true, false>), grid, block, 0, s, a);
+    else if (tab) hipLaunchKernelGGL((snr_parts_kernel<false, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((snr_parts_kernel<false, false>), grid, block, 0, s, a);
+  });
+}
+
+hipError_t launch_snr_combine(const SnrCombineArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(snr_combine_kernel, dim3((unsigned)((a.n + 63) / 64)), dim3(64), 0, s, a);
+  return hipGetLastError();
 }
 
 int fisher_block() { return kBlock; }

@@ -10,6 +10,22 @@ struct Item {
   int32_t slot;             // partial-sum slot: the item's position in event order
 };
 
+// The site constants a set-up makes per event.
+enum SiteSets {
+  kSetsSites = 0,     // one per site: its effective interferometers (duty factor applied)
+  kSetsArms = 1,      // one per site: its arms themselves (kArmsPlain), the duty factor not applied
+  kSetsSitesArms = 2, // the n_site of kSetsSites, then the n_site of kSetsArms
+  kSetsIfos = 3       // one per interferometer: that one alone (duty factor applied)
+};
+
+// An event's grid of n points in at most `parts` parts of part_length points,
+// a multiple of what a workgroup takes in one iteration.
+constexpr int kPartUnit = 512;
+__host__ __device__ inline int32_t part_length(int32_t n, int32_t parts) {
+  const int32_t len = (n - 1) / parts + 1;
+  return ((len - 1) / kPartUnit + 1) * kPartUnit;
+}
+
 struct SetupArgs {
   const double* par;
   int64_t ld, n;
@@ -25,7 +41,9 @@ struct SetupArgs {
   NetDesc net;
   uint32_t flags;
   EventC* evc;                // [n]
-  SiteC* sic;                 // [n][n_site]
+  int32_t sets, n_set;        // SiteSets, and the SiteC per event that makes
+  int32_t no_phase;           // nonzero: the phase series are not wanted (SNR only)
+  SiteC* sic;                 // [n][n_set]
   int32_t* status;            // [n] or NULL, output: parameter status of each event
 };
 
@@ -33,10 +51,14 @@ struct ItemsArgs {
   const EventC* evc;
   const SiteC* sic;
   int32_t n_site;
-  const Item* items;          // one workgroup per item, in this order
+  const Item* items;          // one workgroup per item, in this order; NULL: the split form
   int32_t n_items;
   const int32_t* n_items_dev; // NULL, or the item count in device memory (read in place of n_items)
   double* partial;            // [n_items][NACC]
+  // split form: a workgroup for each of `parts` parts of n events (those a short
+  // grid does not fill leave at once), for each of n_mat matrices per event;
+  // n_set: SiteC per event, matrix m of several taking the m-th alone
+  int32_t parts, n, n_mat, n_set;
   int64_t base;               // first item of the launch (set by the launcher)
 };
 
@@ -45,12 +67,40 @@ struct CombineArgs {
   const EventC* evc;
   const int32_t* item_first;  // [n+1]: items of event e are item_first[e] .. item_first[e+1]-1
   const double* partial;
-  double* fisher;             // [P][P][n]
-  double* snr;                // [n]
+  int32_t parts, n_mat;       // split form (item_first NULL), see ItemsArgs
+  double* fisher;             // [n_mat][P][P][n]
+  double* snr;                // [n] or NULL
   int32_t* status;            // [n]
   const uint32_t* par_mask;   // [n] or NULL: rows of each event's Fisher matrix (others 0)
   int64_t base;               // first (event, slot) pair of the launch (set by the launcher)
 };
+
+// The SNR pass of the split form: a workgroup per event and part, with the
+// sites' constants as their arms (kSetsArms), then the sums of each
+// interferometer.
+struct SnrPartsArgs {
+  const EventC* evc;
+  const SiteC* sic;           // [n][n_set], the arms' from entry set0 on
+  int32_t n_set, set0, parts, n;
+  NetDesc net;
+  double* partial;            // [n][parts][n_ifo]
+  int64_t base;               // first workgroup of the launch (set by the launcher)
+};
+
+struct SnrCombineArgs {
+  int64_t n, ld;
+  int32_t parts, n_ifo;
+  const uint8_t* active;      // [n_ifo][ld] or NULL
+  EventC* evc;                // an event below the threshold gets its status here
+  const double* partial;
+  double snr_th;              // > 0: events whose SNR does not exceed it are skipped
+  double* snr;                // [n]
+  double* snr_ifo;            // [n_ifo][n] or NULL
+  int32_t* status;            // [n] or NULL
+};
+
+hipError_t launch_snr_parts(const SnrPartsArgs& a, bool rot, bool tab, hipStream_t s);
+hipError_t launch_snr_combine(const SnrCombineArgs& a, hipStream_t s);
 
 // The adjoint over work items (gwf_plan_adjoint).  AdjEventC and AdjSiteC
 // are declared in gwf_adjoint.hpp.

@@ -121,7 +121,7 @@ gwf_status enqueue(gwf_plan* p, const Outs& o, hipStream_t s) {
   sa.fmin = p->grid.fmin; sa.fmax = p->grid.fmax; sa.npts = p->grid.npts; sa.npts_plan = p->npts_plan;
   sa.npts_max = 0x7fffffff;
   sa.ecc = p->ev.ecc; sa.fref = p->ev.f_ref_ecc;
-  sa.net = p->net; sa.flags = p->flags; sa.evc = p->evc; sa.sic = p->sic; sa.status = o.status;
+  sa.net = p->net; sa.sets = kSetsSites; sa.n_set = p->net.n_site; sa.flags = p->flags; sa.evc = p->evc; sa.sic = p->sic; sa.status = o.status;
   sa.active = p->ev.active;
   hipError_t err = launch_setup(sa, s);
   if (err == hipSuccess) {
@@ -342,7 +342,7 @@ gwf_status gwf_plan_adjoint(gwf_plan* p, const double* gbar, const int32_t* stat
   sa.fmin = p->grid.fmin; sa.fmax = p->grid.fmax; sa.npts = p->grid.npts; sa.npts_plan = p->npts_plan;
   sa.npts_max = 0x7fffffff;
   sa.ecc = p->ev.ecc; sa.fref = p->ev.f_ref_ecc;
-  sa.net = p->net; sa.flags = p->flags; sa.evc = p->evc; sa.sic = p->sic; sa.status = nullptr;
+  sa.net = p->net; sa.sets = kSetsSites; sa.n_set = p->net.n_site; sa.flags = p->flags; sa.evc = p->evc; sa.sic = p->sic; sa.status = nullptr;
   sa.active = p->ev.active;
   hipError_t err = hipSuccess;
   if (!p->aec) {                    // the first adjoint call allocates its constants

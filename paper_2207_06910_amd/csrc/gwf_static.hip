@@ -111,7 +111,7 @@ gwf_status gwf_fisher_static(const gwf_events* ev, const gwf_network* net, const
     sa.fmin = grid->fmin; sa.fmax = grid->fmax; sa.npts = grid->npts; sa.npts_plan = grid->npts;
     sa.npts_max = npts_max;
     sa.ecc = ev->ecc; sa.fref = ev->f_ref_ecc;
-    sa.net = nd; sa.flags = flags; sa.evc = evc; sa.sic = sic; sa.status = status;
+    sa.net = nd; sa.sets = kSetsSites; sa.n_set = nd.n_site; sa.flags = flags; sa.evc = evc; sa.sic = sic; sa.status = status;
     sa.active = ev->active;
     err = launch_setup(sa, s);
   }
