@@ -126,8 +126,6 @@ struct EventC {
 
 struct SiteC {
   double cdl, sdl;             // cos, sin of (site longitude - phi)
-  double ct, slct, clst, sl, st;   // cos th, sin lat cos th, cos lat sin th, sin lat, sin th
-  double cl;                   // cos lat
   double k1, k0, k1t, k0t;     // Delta = k1 cos H + k0;  dDelta/dth = k1t cos H + k0t
   // (f0/f)^2 = ix2_fac v^-6; (f/f0)^2 = x2_fac v^6; a sampled curve has the
   // two coefficients of its interval guess here (see table_setup)
@@ -147,7 +145,6 @@ struct SiteC {
   // trigonometric polynomials in the hour angle H: coefficients of
   // (1, cos H, sin H, cos 2H, sin H cos H), each scaled by sqrt(weff)
   double jk[2][4][5];
-  double arm_alpha[3][4], arm_beta[3][4];   // individual arms (SNR per interferometer)
   int32_t n_eff, n_arm;
   // sampled noise curve (tab_kind 1: PSD, 2: ASD; 0: the analytic PSD above)
   const double* tab_f;
@@ -539,7 +536,7 @@ __host__ __device__ inline void trig_mul_add(const TrigLin& a, const TrigLin& b,
   out[4] += k * fma(a.v, b.w, a.w * b.v);
 }
 
-// The pattern vector P(H) of site_point and its theta derivative as
+// The pattern vector P(H) and its theta derivative as
 // trigonometric polynomials of degree two in the hour angle: the frame
 // components EX = cos H, EY = -cos th sin H, NX = -sin lat sin H,
 // NY = -(sin lat cos th cos H + cos lat sin th) are linear in (cos H, sin H),
@@ -631,9 +628,6 @@ __host__ __device__ inline void site_setup(const double* p, const SiteDesc& sd, 
   sc.cdl = cos(sd.lon - ph);
   sc.sdl = sin(sd.lon - ph);
   const double ct = cos(th), st = sin(th), sl = sin(sd.lat), cl = cos(sd.lat);
-  sc.ct = ct; sc.st = st; sc.sl = sl; sc.cl = cl;
-  sc.slct = sl * ct;
-  sc.clst = cl * st;
   // arrival-time offset -(n . r)/c with n.r/R = sin th cos lat cos H + cos th sin lat
   sc.k1 = -kREarthS * cl * st;
   sc.k0 = -kREarthS * sl * ct;
@@ -657,10 +651,8 @@ __host__ __device__ inline void site_setup(const double* p, const SiteDesc& sd, 
   if (sd.psd_kind) table_setup(sd, piM, sc);
   if (sd.shape == 1) {
     double al[3][4], be[3][4];
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < 3; ++k)
       pattern_map(sd.gamma + kPi / 6.0 + kTwoPi * k / 3.0, kPi / 3.0, c2p, s2p, al[k], be[k]);
-      for (int j = 0; j < 4; ++j) { sc.arm_alpha[k][j] = al[k][j]; sc.arm_beta[k][j] = be[k][j]; }
-    }
     sc.n_arm = 3;
     if ((arm_on & 7u) == 7u) {
       for (int j = 0; j < 4; ++j) {
@@ -685,10 +677,7 @@ __host__ __device__ inline void site_setup(const double* p, const SiteDesc& sd, 
     }
   } else {
     pattern_map(sd.gamma, sd.zeta, c2p, s2p, sc.alpha[0], sc.beta[0]);
-    for (int j = 0; j < 4; ++j) {
-      sc.arm_alpha[0][j] = sc.alpha[0][j]; sc.arm_beta[0][j] = sc.beta[0][j];
-      sc.alpha[1][j] = 0.0; sc.beta[1][j] = 0.0;
-    }
+    for (int j = 0; j < 4; ++j) { sc.alpha[1][j] = 0.0; sc.beta[1][j] = 0.0; }
     sc.weff[0] = 1.0; sc.weff[1] = 0.0;
     sc.n_eff = (arm_on & 1u) ? 1 : 0; sc.n_arm = 1;
   }
@@ -731,6 +720,10 @@ __host__ __device__ inline uint32_t site_arms_on(const uint8_t* active, int64_t 
     if (active[(int64_t)(ifo0 + k) * ld + e]) m |= 1u << k;
   return m;
 }
+
+// site_setup's arm mask for a site's arms on their own: the first two of a
+// triangle (the third response is minus their sum) or an L's one.
+constexpr uint32_t kArmsPlain = 3u;
 
 // The arms of site s that take part when only interferometer ifo_sel - 1 is
 // wanted (ifo_sel = 0: every arm in `arms`).
@@ -1025,13 +1018,6 @@ __host__ __device__ inline void phase_only_coefficients(const EventC& ec, const 
   if (PO::ecc) c[NPI - 1] = ec.ecc_e0 * q.ecv;
 }
 
-// Site-level quantities at one frequency: the P vectors and their hour-angle
-// and theta derivatives, the delay derivatives and the noise weight.
-struct SitePoint {
-  double P[4], PH[4], Pt[4];
-  double dH, dT;      // dDelta/dH, dDelta/dtheta
-};
-
 __host__ __device__ inline double psd_weight_of(double xp_fac, double ix2_fac, double x2_fac, double S0inv,
                                                 const Point& q) {
   // S_n = S0 [x^-4.14 - 5 x^-2 + 111 (1 - x^2 + x^4/2)/(1 + x^2/2)], x = f/f0;
@@ -1158,28 +1144,6 @@ __host__ __device__ inline double psd_root_weight_f32(const SiteC& sc, const Poi
   return (q.rw * sc.rS0inv) * (double)sqrtf_hw(den * recipf(top));
 }
 
-__host__ __device__ inline void site_point(const SiteC& sc, const Point& q, SitePoint& sp) {
-  const double cH = q.cth * sc.cdl - q.sth * sc.sdl;
-  const double sH = q.sth * sc.cdl + q.cth * sc.sdl;
-  const double EX = cH, EY = -sc.ct * sH, NX = -sc.sl * sH, NY = -(sc.slct * cH + sc.clst);
-  sp.P[0] = 0.5 * (EX * EX - NX * NX - EY * EY + NY * NY);
-  sp.P[1] = EX * NX - EY * NY;
-  sp.P[2] = EX * EY - NX * NY;
-  sp.P[3] = EX * NY + NX * EY;
-  const double EXh = -sH, EYh = -sc.ct * cH, NXh = -sc.sl * cH, NYh = sc.slct * sH;
-  sp.PH[0] = EX * EXh - NX * NXh - EY * EYh + NY * NYh;
-  sp.PH[1] = EXh * NX + EX * NXh - EYh * NY - EY * NYh;
-  sp.PH[2] = EXh * EY + EX * EYh - NXh * NY - NX * NYh;
-  sp.PH[3] = EXh * NY + EX * NYh + NXh * EY + NX * EYh;
-  const double EYt = sc.st * sH, NYt = sc.sl * sc.st * cH - sc.cl * sc.ct;
-  sp.Pt[0] = -EY * EYt + NY * NYt;
-  sp.Pt[1] = -(EYt * NY + EY * NYt);
-  sp.Pt[2] = EX * EYt - NX * NYt;
-  sp.Pt[3] = EX * NYt + NX * EYt;
-  sp.dH = -sc.k1 * sH;
-  sp.dT = fma(sc.k1t, cH, sc.k0t);
-}
-
 // Site-level quantities of the Fisher kernels at one frequency for the
 // trigonometric form of the patterns (SiteC::jk): cos H, sin H, cos 2H,
 // sin H cos H and the factor -4 sin H cos H of the cos 2H term's H derivative
@@ -1207,28 +1171,28 @@ __host__ __device__ inline void site_trig(const SiteC& sc, const Point& q, SiteT
 
 // The Fisher kernels' site quantities: the patterns' trigonometric basis
 // scaled by the root weight r (psd_root_weight), so that SiteC::jk's
-// polynomials give r F+, r Fx and their derivatives directly; cos H and
-// sin H themselves for the arrival-time derivatives.
+// polynomials give r F+, r Fx and their derivatives directly, and the
+// arrival-time derivatives.
 struct SiteTrigR {
-  double cH, sH;
   double r, rc, rs, rc2, rsc;   // r (1, cos H, sin H, cos 2H, sin H cos H)
   double rm4;                   // -4 r sin H cos H
   double u, w;                  // 2 pi f dDelta/dH, 2 pi f dDelta/dtheta
 };
 
-template <bool MIXED = false, bool TAB = true>
-__host__ __device__ inline void site_trig_root(const SiteC& sc, const Point& q, SiteTrigR& sp) {
-  const double cH = q.cth * sc.cdl - q.sth * sc.sdl;
-  const double sH = q.sth * sc.cdl + q.cth * sc.sdl;
-  sp.cH = cH;
-  sp.sH = sH;
-  const double r = MIXED ? psd_root_weight_f32<TAB>(sc, q) : psd_root_weight<TAB>(sc, q);
+__host__ __device__ inline void trig_basis(double cH, double sH, double r, SiteTrigR& sp) {
   sp.r = r;
   sp.rc = r * cH;
   sp.rs = r * sH;
   sp.rc2 = fma(sp.rc, cH, -sp.rs * sH);
   sp.rsc = sp.rs * cH;
   sp.rm4 = -4.0 * sp.rsc;
+}
+
+template <bool MIXED = false, bool TAB = true>
+__host__ __device__ inline void site_trig_root(const SiteC& sc, const Point& q, SiteTrigR& sp) {
+  const double cH = q.cth * sc.cdl - q.sth * sc.sdl;
+  const double sH = q.sth * sc.cdl + q.cth * sc.sdl;
+  trig_basis(cH, sH, MIXED ? psd_root_weight_f32<TAB>(sc, q) : psd_root_weight<TAB>(sc, q), sp);
   sp.u = q.tf * (-sc.k1 * sH);
   sp.w = fma(q.tf, sc.k1t * cH, q.tf * sc.k0t);
 }
@@ -1252,10 +1216,6 @@ __host__ __device__ inline double trig_dH(const double c[5], const SiteTrig& sp)
   return fma(c[4], sp.c2H, fma(c[3], sp.m4, fma(c[2], sp.cH, -c[1] * sp.sH)));
 }
 
-__host__ __device__ inline double dot4(const double a[4], const double b[4]) {
-  return fma(a[0], b[0], fma(a[1], b[1], fma(a[2], b[2], a[3] * b[3])));
-}
-
 // The event's amplitude factors that enter the derivative vectors.
 struct AmpFactors {
   double cplus, ccross, dcp, dcx, dlnA, idL;
@@ -1263,50 +1223,6 @@ struct AmpFactors {
 
 __host__ __device__ inline AmpFactors amp_factors(const EventC& ec) {
   return AmpFactors{ec.cplus, ec.ccross, ec.dcplus, ec.dcross, ec.dlnA_dMc, ec.inv_dL};
-}
-
-// A site's derivatives of the phase at one point (the delay's share
-// included): with respect to Mc, eta, theta, phi and tc [s].
-struct SitePhase {
-  double mc, eta, t, p, tc;
-};
-
-__host__ __device__ inline SitePhase site_phase(const Point& q, double dH, double dT) {
-  return SitePhase{fma(q.tf * dH, q.gMc, q.pMc), fma(q.tf * dH, q.gEta, q.pEta), q.tf * dT,
-                   -q.tf * dH, q.tf * fma(kOmegaE, dH, 1.0)};
-}
-__host__ __device__ inline SitePhase site_phase(const Point& q, const SitePoint& sp) {
-  return site_phase(q, sp.dH, sp.dT);
-}
-
-// Phase-free derivative vector of one interferometer at one point,
-// D_b = dQ_b + Q dlnA_b + i Q dPsi_b for b = (Mc, eta, dL, theta, phi, iota,
-// psi, tc), from its pattern values F = (alpha.P, beta.P) and their hour-angle
-// (H) and theta (t) derivatives; Q = c+ F+ + i cx Fx.  The strain derivative
-// is A exp(i Psi) D_b, and i Q c(f) for the phase-only parameters.
-__host__ __device__ inline void derivative_vector(const AmpFactors& am, const Point& q, const SitePhase& ph,
-                                                  double Fp, double Fx, double FpH, double FxH,
-                                                  double Fpt, double Fxt, double* Dr, double* Di) {
-  const double Qr = am.cplus * Fp, Qi = am.ccross * Fx;
-  const double QHr = am.cplus * FpH, QHi = am.ccross * FxH;
-  const double Qtr = am.cplus * Fpt, Qti = am.ccross * Fxt;
-  // D = dQ + Q dlnA + i Q dPsi, with i Q x = (-Qi x, Qr x)
-  Dr[0] = fma(Qr, am.dlnA, fma(QHr, q.gMc, -Qi * ph.mc));     // Mc
-  Di[0] = fma(Qi, am.dlnA, fma(QHi, q.gMc, Qr * ph.mc));
-  Dr[1] = fma(QHr, q.gEta, -Qi * ph.eta);                     // eta
-  Di[1] = fma(QHi, q.gEta, Qr * ph.eta);
-  Dr[2] = -Qr * am.idL;                                       // dL
-  Di[2] = -Qi * am.idL;
-  Dr[3] = fma(-Qi, ph.t, Qtr);                                // theta
-  Di[3] = fma(Qr, ph.t, Qti);
-  Dr[4] = fma(-Qi, ph.p, -QHr);                               // phi (H = ... - phi)
-  Di[4] = fma(Qr, ph.p, -QHi);
-  Dr[5] = am.dcp * Fp;                                        // iota
-  Di[5] = am.dcx * Fx;
-  Dr[6] = 2.0 * am.cplus * Fx;                                // psi: dF+ = 2Fx, dFx = -2F+
-  Di[6] = -2.0 * am.ccross * Fp;
-  Dr[7] = fma(kOmegaE, QHr, -Qi * ph.tc);                     // tc [s]
-  Di[7] = fma(kOmegaE, QHi, Qr * ph.tc);
 }
 
 // Marks v and 1/v as unknown to the compiler, so that their powers are formed

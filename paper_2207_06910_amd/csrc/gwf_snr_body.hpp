@@ -19,7 +19,6 @@
 
 namespace gwf {
 
-constexpr uint32_t kArmsPlain = 3u;          // site_setup: the first two arms on their own
 constexpr int kSnrSlots = 3 * kMaxSites;     // slot 3 s + k: arm k of site s
 
 // Adds the points [k0, k1) of the event to the lane's acc[kSnrSlots].

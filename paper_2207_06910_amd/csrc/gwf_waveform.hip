@@ -10,9 +10,11 @@
 // multiply-add), and only the final fraction in [-1/2, 1/2] goes through
 // sin/cos.
 //
-// One workgroup per event, lanes over grid points: each interferometer's
-// output row is written with consecutive lanes on consecutive 16-byte
-// complex values, so the kernel streams its output at HBM rate.
+// One or several workgroups per event (wave_parts), lanes over grid points:
+// each interferometer's output row is written with consecutive lanes on
+// consecutive 16-byte complex values.
+// What bounds it: the output's writes, 4.5 TB/s on 3.1 GB (a fill of 4 GiB
+// reaches 6.7).
 #include "gwf_waveform.hpp"
 
 namespace gwf {
@@ -43,50 +45,35 @@ __global__ __launch_bounds__(kWBlock) void waveform_kernel(WaveformArgs a) {
   const int64_t e = a.base + blockIdx.x;
   const int tid = threadIdx.x;
   const int n_site = a.net.n_site;
-  if (tid == 0) {
-    double p[kNparIn];
-    load_event(a, e, TIDAL, p);
-    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, flags | a.ecc_flag, ec);
-    // the event's columns [b, b + npts) must lie inside a row of h
-    const int64_t b = a.offsets[e];
-    const bool range_ok = b >= 0 && b <= a.total - (int64_t)a.npts[e];
-    int32_t st = ec.status;
-    if (!range_ok) st |= kEvInvalid;
-    ok = st == 0;
-    if (a.status) a.status[e] = st;
-  }
-  __syncthreads();
-  if (!ok) return;
-  if (tid < n_site) {
-    double p[kNparIn];
-    load_event(a, e, TIDAL, p);
+  // a site: its hour angle and delay, and its computed arms' patterns (the arms
+  // themselves, kArmsPlain) times the inclination factors; pi M does not enter
+  const bool some = wave_setup(a, e, TIDAL, flags | a.ecc_flag, ec, ok, [&](int s, const double* p) {
     SiteC sc;
-    site_setup(p, a.net.site[tid], ec, sc);
-    WaveSite& w = ws[tid];
+    SiteDesc sd = a.net.site[s];
+    sd.psd_kind = 0;                     // the noise curve plays no part
+    site_setup(p, sd, 1.0, sc, kArmsPlain);
+    WaveSite& w = ws[s];
     w.cdl = sc.cdl; w.sdl = sc.sdl;
     w.k1 = sc.k1; w.k0 = sc.k0;
-    double pc[4][5], ptc[4][5];
-    pattern_trig(sc.ct, sc.st, sc.sl, sc.cl, pc, ptc);
+    const double ci = cos(p[5]), cplus = 0.5 * (1.0 + ci * ci);
     for (int j = 0; j < 2; ++j)
       for (int m = 0; m < 5; ++m) {
-        double fp = 0.0, fx = 0.0;
-        for (int i = 0; i < 4; ++i) {
-          fp = fma(sc.arm_alpha[j][i], pc[i][m], fp);
-          fx = fma(sc.arm_beta[j][i], pc[i][m], fx);
-        }
-        w.m[j][0][m] = ec.cplus * fp;
-        w.m[j][1][m] = ec.ccross * fx;
+        w.m[j][0][m] = cplus * sc.jk[j][0][m];
+        w.m[j][1][m] = ci * sc.jk[j][1][m];
       }
     w.n_arm = sc.n_arm;
-  }
-  __syncthreads();
+  });
+  if (!some) return;
 
   const double tc = a.tc_s ? a.tc_s[e] : 0.0;
   const int64_t base = a.offsets[e];
   const double amp0 = exp(ec.lnA);
   double2* __restrict__ out = reinterpret_cast<double2*>(a.h) + base;
   const int64_t row = a.total;
-  for (int k = tid; k < ec.n; k += kWBlock) {
+  // point 0 sits sh places past a 128-byte line of the rows
+  const int sh = (int)(a.offsets[e] & 7);
+  for (int k = (int)blockIdx.y * kWBlock + tid - sh; k < ec.n; k += kWBlock * (int)gridDim.y) {
+    if (k < 0) continue;
     // explicit grids: ln v = (ln(pi M) + ln f)/3 from the given frequency
     const double L = EXPL ? (ec.lnpiM + log(ec.fx[k])) / 3.0 : fma((double)k, ec.dlnv, ec.lnv0);
     const double v = exp(L);
@@ -133,14 +120,14 @@ __global__ __launch_bounds__(kWBlock) void waveform_kernel(WaveformArgs a) {
       sincos_cycles<MIXED>(frac_center(fma(f, fma(w.k1, cH, w.k0), cyc)), &sn, &cs);
       const double ca = amp * cs, sa = amp * sn;
       const double qr0 = trig5(w.m[0][0], cH, sH, c2H, sc), qi0 = trig5(w.m[0][1], cH, sH, c2H, sc);
-      const double2 h0 = make_double2(qr0 * ca - qi0 * sa, qr0 * sa + qi0 * ca);
-      *o = h0;
+      const double h0r = qr0 * ca - qi0 * sa, h0i = qr0 * sa + qi0 * ca;
+      *o = make_double2(h0r, h0i);
       o += row;
       if (w.n_arm == 3) {                 // closed triangle: third arm = -(first + second)
         const double qr1 = trig5(w.m[1][0], cH, sH, c2H, sc), qi1 = trig5(w.m[1][1], cH, sH, c2H, sc);
-        const double2 h1 = make_double2(qr1 * ca - qi1 * sa, qr1 * sa + qi1 * ca);
-        o[0] = h1;
-        o[row] = make_double2(-(h0.x + h1.x), -(h0.y + h1.y));
+        const double h1r = qr1 * ca - qi1 * sa, h1i = qr1 * sa + qi1 * ca;
+        *o = make_double2(h1r, h1i);
+        o[row] = make_double2(-(h0r + h1r), -(h0i + h1i));
         o += 2 * row;
       }
     }
@@ -161,6 +148,7 @@ void launch_waveform_t(const WaveformArgs& a, bool tidal, bool rot, dim3 grid, d
 // An explicit grid (a.gf set) selects the instantiations that read it.
 hipError_t launch_waveform(const WaveformArgs& a0, bool tidal, bool rot, bool mixed, hipStream_t stream) {
   return launch_slices(a0, a0.n, 1, kWBlock, [&](const WaveformArgs& a, dim3 grid, dim3 block) {
+    grid.y = wave_parts(a.n);
     if (a.gf) {
       if (mixed) launch_waveform_t<true, true>(a, tidal, rot, grid, block, stream);
       else launch_waveform_t<false, true>(a, tidal, rot, grid, block, stream);

@@ -11,12 +11,61 @@ namespace gwf {
 
 constexpr int kWBlock = 256;
 
+// Workgroups per event: a small catalogue's grids are shared out (workgroup y
+// of an event takes every gridDim.y-th run of kWBlock points), so that about
+// 2048 workgroups are there, and two up to 8192 events, whose longest grids
+// would otherwise end the launch alone.  Measured, one workgroup per event and
+// this: strain of 600 neutron-star pairs 183 and 124 us, derivatives of 64
+// events 347 and 148 us.
+// The runs start on a 128-byte line of the rows (eight complex values): a
+// wavefront's 1 KB store is then whole lines, where a run that starts inside
+// one leaves the shared line to be completed by the next run's workgroup, on
+// another XCD.  Strain of 4000 pairs (3.1 GB) 825 -> 697 us, derivatives of 300
+// (3.0 GB) 904 -> 616 us.  Stores past the caches (non-temporal) were slower:
+// 948 and 881 us.
+inline unsigned wave_parts(int64_t n) {
+  const int64_t y = (2048 + n - 1) / n;
+  return n >= 8192 ? 1u : (unsigned)std::min<int64_t>(64, std::max<int64_t>(y, 2));
+}
+
 // Event e's inputs: the 13 parameters (no tidal rows without tides), e0 and
 // its reference frequency (with the eccentric flag, else zero).
 __device__ inline void load_event(const WaveformArgs& a, int64_t e, bool tidal, double* p) {
   for (int r = 0; r < 13; ++r) p[r] = (r < 11 || tidal) ? a.par[r * a.ld + e] : 0.0;
   p[13] = a.ecc_flag && a.ecc ? a.ecc[e] : 0.0;
   p[14] = a.ecc_flag && a.fref ? a.fref[e] : 0.0;
+}
+
+// The event's constants and its sites', by wavefronts side by side: wavefront 0
+// the grid, with the check that the event's columns [b, b + npts) lie inside
+// a row of the output, and the status; wavefront 1 calls site(s, p) on one lane
+// per site; wavefronts 2 and 3 the phase and angle series.  False (for the
+// whole workgroup) if there is nothing to write; a workgroup beyond the
+// event's points leaves before any of it.
+template <class Site>
+__device__ inline bool wave_setup(const WaveformArgs& a, int64_t e, bool tidal, uint32_t flags, EventC& ec,
+                                  int32_t& ok, const Site& site) {
+  const int tid = threadIdx.x;
+  if (blockIdx.y > 0 && (int64_t)blockIdx.y * kWBlock >= a.npts[e] + (int64_t)(a.offsets[e] & 7)) return false;
+  double p[kNparIn];
+  load_event(a, e, tidal, p);
+  if (tid == 0) {
+    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, flags, ec, kSetupGrid);
+    const int64_t b = a.offsets[e];
+    const bool range_ok = b >= 0 && b <= a.total - (int64_t)a.npts[e];
+    int32_t st = ec.status;
+    if (!range_ok) st |= kEvInvalid;
+    ok = st == 0;
+    if (a.status && blockIdx.y == 0) a.status[e] = st;
+  } else if (tid >= 64 && tid < 64 + a.net.n_site) {
+    site(tid - 64, p);
+  } else if (tid == 128) {
+    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, flags, ec, kSetupPhase);
+  } else if (tid == 192) {
+    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, flags, ec, kSetupAngle);
+  }
+  __syncthreads();
+  return ok != 0;
 }
 
 // x reduced to [-1/2, 1/2] by subtracting the nearest integer (exact).

@@ -14,14 +14,57 @@ namespace {
 // D the phase-free derivative vector of the Fisher kernels for (Mc, eta, dL,
 // theta, phi, iota, psi, tc) and i Q c_a for the phase-only parameters
 // (Phic, chi1z, chi2z[, Lambda1, Lambda2][, e0]); the phase in cycles exactly as
-// for the strain.  Each arm of a triangle is projected with its own pattern
-// map.  One workgroup per event, lanes over grid points; row (a, i) of dh
-// holds parameter a at interferometer i, consecutive lanes on consecutive
-// complex values.  FP64 only.
+// for the strain.  D is a combination of Q, iQ, Z and Y (NetSums), so a point
+// turns those three complex numbers by the phase and the rows follow by real
+// coefficients.  One or several workgroups per event (wave_parts), lanes over
+// grid points; row (a, i) of dh holds parameter a at interferometer i,
+// consecutive lanes on consecutive complex values.  FP64 only.
+// What bounds it: the output's writes, 4.9 TB/s on 3.0 GB of 300 neutron-star
+// pairs (616 us; every arm's rows from its own derivative vector, one
+// workgroup per event: 960 us).
+// One arm at one point: its patterns, and Q, Z and Y turned by A exp(i Psi).
+struct Response {
+  double Fp, Fx, qr, qi, zr, zi, yr, yi;
+};
+
+__device__ inline void arm_response(const AmpFactors& am, const double (*c)[5], const SiteTrigR& tr, double u,
+                                    double w, double ca, double sa, Response& r) {
+  r.Fp = trig_val_r(c[0], tr);
+  r.Fx = trig_val_r(c[1], tr);
+  const double Qr = am.cplus * r.Fp, Qi = am.ccross * r.Fx;
+  const double Zr = fma(am.cplus, trig_dH_r(c[0], tr), -u * Qi), Zi = fma(am.ccross, trig_dH_r(c[1], tr), u * Qr);
+  const double Yr = fma(am.cplus, trig_val_r(c[2], tr), -w * Qi), Yi = fma(am.ccross, trig_val_r(c[3], tr), w * Qr);
+  r.qr = fma(Qr, ca, -Qi * sa); r.qi = fma(Qr, sa, Qi * ca);
+  r.zr = fma(Zr, ca, -Zi * sa); r.zi = fma(Zr, sa, Zi * ca);
+  r.yr = fma(Yr, ca, -Yi * sa); r.yi = fma(Yr, sa, Yi * ca);
+}
+
+// The P rows of one arm at one point (see NetSums), those outside the event's
+// set pm as zeros.
+template <int NPI>
+__device__ inline void write_rows(const AmpFactors& am, const Point& q, const double* cph, double ca, double sa,
+                                  const Response& r, uint32_t pm, int64_t prow, double2* o) {
+  auto put = [&](int row, double x, double y) {
+    const bool in = (pm >> row) & 1u;
+    o[row * prow] = make_double2(in ? x : 0.0, in ? y : 0.0);
+  };
+  put(0, fma(am.dlnA, r.qr, fma(q.gMc, r.zr, -q.pMc * r.qi)), fma(am.dlnA, r.qi, fma(q.gMc, r.zi, q.pMc * r.qr)));
+  put(1, fma(q.gEta, r.zr, -q.pEta * r.qi), fma(q.gEta, r.zi, q.pEta * r.qr));
+  put(2, -am.idL * r.qr, -am.idL * r.qi);
+  put(3, r.yr, r.yi);
+  put(4, -r.zr, -r.zi);
+  const double ir = am.dcp * r.Fp, ii = am.dcx * r.Fx;
+  put(5, fma(ir, ca, -ii * sa), fma(ir, sa, ii * ca));
+  const double pr = 2.0 * am.cplus * r.Fx, pi = -2.0 * am.ccross * r.Fp;
+  put(6, fma(pr, ca, -pi * sa), fma(pr, sa, pi * ca));
+  put(7, fma(kOmegaE, r.zr, -q.tf * r.qi), fma(kOmegaE, r.zi, q.tf * r.qr));
+#pragma unroll
+  for (int i = 0; i < NPI; ++i) put(8 + i, -r.qi * cph[i], r.qr * cph[i]);
+}
+
 template <bool ROT, int NPI, bool EXPL>
 __global__ __launch_bounds__(kWBlock) void waveform_deriv_kernel(WaveformArgs a) {
   using PO = PhaseOnly<NPI>;
-  constexpr int P = PO::P;
   constexpr bool TIDAL = PO::tidal;
   constexpr uint32_t flags = (TIDAL ? kFlagTidal : 0u) | (ROT ? kFlagRot : 0u) | (PO::ecc ? kFlagEcc : 0u);
   __shared__ EventC ec;
@@ -30,25 +73,12 @@ __global__ __launch_bounds__(kWBlock) void waveform_deriv_kernel(WaveformArgs a)
   const int64_t e = a.base + blockIdx.x;
   const int tid = threadIdx.x;
   const int n_site = a.net.n_site;
-  if (tid == 0) {
-    double p[kNparIn];
-    load_event(a, e, TIDAL, p);
-    event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, flags, ec);
-    const int64_t b = a.offsets[e];
-    const bool range_ok = b >= 0 && b <= a.total - (int64_t)a.npts[e];
-    int32_t st = ec.status;
-    if (!range_ok) st |= kEvInvalid;
-    ok = st == 0;
-    if (a.status) a.status[e] = st;
-  }
-  __syncthreads();
-  if (!ok) return;
-  if (tid < n_site) {
-    double p[kNparIn];
-    load_event(a, e, TIDAL, p);
-    site_setup(p, a.net.site[tid], ec, sc[tid]);
-  }
-  __syncthreads();
+  const bool some = wave_setup(a, e, TIDAL, flags, ec, ok, [&](int s, const double* p) {
+    SiteDesc sd = a.net.site[s];
+    sd.psd_kind = 0;                     // the noise curve plays no part, nor does pi M
+    site_setup(p, sd, 1.0, sc[s], kArmsPlain);
+  });
+  if (!some) return;
 
   const uint32_t pm = event_rows(a.par_mask, e);
   const double tc = a.tc_s ? a.tc_s[e] : 0.0;
@@ -57,7 +87,10 @@ __global__ __launch_bounds__(kWBlock) void waveform_deriv_kernel(WaveformArgs a)
   double2* __restrict__ out = reinterpret_cast<double2*>(a.dh) + a.offsets[e];
   const int64_t row = a.total;
   const int64_t prow = (int64_t)a.net.n_ifo * row;     // one parameter's block of rows
-  for (int k = tid; k < ec.n; k += kWBlock) {
+  // point 0 sits sh places past a 128-byte line of the rows
+  const int sh = (int)(a.offsets[e] & 7);
+  for (int k = (int)blockIdx.y * kWBlock + tid - sh; k < ec.n; k += kWBlock * (int)gridDim.y) {
+    if (k < 0) continue;
     // the event and site constants are re-read from LDS (uniform broadcast
     // reads) rather than held in registers across iterations
     asm volatile("" ::: "memory");
@@ -78,30 +111,27 @@ __global__ __launch_bounds__(kWBlock) void waveform_deriv_kernel(WaveformArgs a)
     for (int s = 0; s < n_site; ++s) {
       asm volatile("" ::: "memory");
       const SiteC& st = sc[s];
-      SitePoint sp;
-      site_point(st, q, sp);
-      const SitePhase ph = site_phase(q, sp);
       const double cH = q.cth * st.cdl - q.sth * st.sdl;
+      const double sH = q.sth * st.cdl + q.cth * st.sdl;
       double sn, cs;
       sincos_cycles<false>(frac_center(fma(q.f, fma(st.k1, cH, st.k0), cyc)), &sn, &cs);
       const double ca = amp * cs, sa = amp * sn;
-      for (int j = 0; j < st.n_arm; ++j) {
-        const double Fp = dot4(st.arm_alpha[j], sp.P), Fx = dot4(st.arm_beta[j], sp.P);
-        double Dr[P], Di[P];
-        derivative_vector(am, q, ph, Fp, Fx, dot4(st.arm_alpha[j], sp.PH), dot4(st.arm_beta[j], sp.PH),
-                          dot4(st.arm_alpha[j], sp.Pt), dot4(st.arm_beta[j], sp.Pt), Dr, Di);
-        const double Qr = am.cplus * Fp, Qi = am.ccross * Fx;
-#pragma unroll
-        for (int i = 0; i < NPI; ++i) {          // i Q c
-          Dr[8 + i] = -Qi * cph[i];
-          Di[8 + i] = Qr * cph[i];
-        }
-#pragma unroll
-        for (int r = 0; r < P; ++r) {
-          const bool in = (pm >> r) & 1u;
-          o[r * prow] = in ? make_double2(Dr[r] * ca - Di[r] * sa, Dr[r] * sa + Di[r] * ca)
-                           : make_double2(0.0, 0.0);
-        }
+      SiteTrigR tr;                      // the patterns' basis, unweighted
+      trig_basis(cH, sH, 1.0, tr);
+      const double u = q.tf * (-st.k1 * sH), w = q.tf * fma(st.k1t, cH, st.k0t);
+      Response a0, a1;
+      arm_response(am, st.jk[0], tr, u, w, ca, sa, a0);
+      write_rows<NPI>(am, q, cph, ca, sa, a0, pm, prow, o);
+      o += row;
+      if (st.n_arm == 3) {               // closed triangle: third arm = -(first + second)
+        arm_response(am, st.jk[1], tr, u, w, ca, sa, a1);
+        write_rows<NPI>(am, q, cph, ca, sa, a1, pm, prow, o);
+        o += row;
+        a0.Fp = -(a0.Fp + a1.Fp); a0.Fx = -(a0.Fx + a1.Fx);
+        a0.qr = -(a0.qr + a1.qr); a0.qi = -(a0.qi + a1.qi);
+        a0.zr = -(a0.zr + a1.zr); a0.zi = -(a0.zi + a1.zi);
+        a0.yr = -(a0.yr + a1.yr); a0.yi = -(a0.yi + a1.yi);
+        write_rows<NPI>(am, q, cph, ca, sa, a0, pm, prow, o);
         o += row;
       }
     }
@@ -128,6 +158,7 @@ void launch_deriv_t(const WaveformArgs& a, int npi, bool rot, dim3 grid, dim3 bl
 
 hipError_t launch_waveform_deriv(const WaveformArgs& a0, int npi, bool rot, hipStream_t stream) {
   return launch_slices(a0, a0.n, 1, kWBlock, [&](const WaveformArgs& a, dim3 grid, dim3 block) {
+    grid.y = wave_parts(a.n);
     if (a.gf) launch_deriv_t<true>(a, npi, rot, grid, block, stream);
     else launch_deriv_t<false>(a, npi, rot, grid, block, stream);
   });
