@@ -35,6 +35,7 @@
 #include "gwf_adjoint.hpp"
 #include "gwf_batched.hpp"
 #include "gwf_kernels.hpp"
+#include "gwf_reduce.hpp"
 
 namespace gwf {
 
@@ -46,12 +47,6 @@ constexpr int kSlots = kAdjN;         // LDS accumulator values per site and col
 // at every point, whatever the workgroup size.
 constexpr int kWalk = 128;
 constexpr int kAnchor = 16 * kWalk;
-
-__device__ inline double wave_sum_a(double x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
-}
 
 // The sums of points [k0, k1) of one event into LDS columns (zeroed by the
 // caller, one writer per address, so the sums are in program order), by a
@@ -95,44 +90,42 @@ __device__ __attribute__((always_inline)) inline void adjoint_sums(const EventC&
     const bool in = k < k1;
     if (PAIR) {                      // both lanes of a pair take part in each exchange
       const int cols = nb >> 1;
-      AdjPoint ap;
-      if (in) adjoint_point_setup<NPI, ROT>(ec, ae, k, ap, gw.val);
-      for (int s = 0; s < n_site; ++s) {
-        asm volatile("" ::: "memory");
-        double acc[kAdjN];
-#pragma unroll
-        for (int i = 0; i < kAdjN; ++i) acc[i] = 0.0;
-        if (in) adjoint_site<TAB>(ae, sc[s], as[s], ap, acc);
+      AdjPoint ap[1];
+      if (in) adjoint_point_setup<NPI, ROT, 1>(ec, ae, {k}, ap, &gw.val);
+      adjoint_sites<1, TAB, false>(ae, sc, as, n_site, ap, [&](int s, const double (&t)[kAdjN]) {
 #pragma unroll
         for (int i = 0; i < kSlots; ++i) {
-          const double v = acc[i] + __shfl_xor(acc[i], 1, 64);
+          const double x = in ? t[i] : 0.0;
+          const double v = x + __shfl_xor(x, 1, 64);
           if ((tid & 1) == 0) atomicAdd(&accl[(s * kSlots + i) * cols + (tid >> 1)], v);
         }
-      }
+      });
     } else if (in) {
-      AdjPoint ap;
-      adjoint_point_setup<NPI, ROT>(ec, ae, k, ap, gw.val);
-      for (int s = 0; s < n_site; ++s) {
-        asm volatile("" ::: "memory");
-        double acc[kAdjN];
+      AdjPoint ap[1];
+      adjoint_point_setup<NPI, ROT, 1>(ec, ae, {k}, ap, &gw.val);
+      adjoint_sites<1, TAB, true>(ae, sc, as, n_site, ap, [&](int s, const double (&t)[kAdjN]) {
 #pragma unroll
-        for (int i = 0; i < kAdjN; ++i) acc[i] = 0.0;
-        adjoint_site<TAB>(ae, sc[s], as[s], ap, acc);
-#pragma unroll
-        for (int i = 0; i < kSlots; ++i) atomicAdd(&accl[(s * kSlots + i) * nb + tid], acc[i]);
-      }
+        for (int i = 0; i < kSlots; ++i) atomicAdd(&accl[(s * kSlots + i) * nb + tid], t[i]);
+      });
     }
   }
 }
 
 // adjoint_sums with PAIR = false and two grid points per lane and iteration,
 // k and k + nb (the same walk, taken two points at a time): the two points'
-// site terms are independent instruction streams the compiler interleaves,
-// and each site's constants are read once for both.  A point past k1 is
-// evaluated as the item's last point with zero weight (every term of
-// adjoint_site carries the weight), so the site code has no branch; its walk
-// values would overflow on a short grid.  The column gets the two points'
-// sum per site and iteration.
+// site terms are independent instruction streams, each site's constants are
+// read once for both, and the coefficients' gradients are contracted with the
+// directions once for both.  A point past k1 is evaluated as the item's last
+// point with zero weight (every value of adjoint_sites carries its root), so
+// the site code has no branch; its walk values would overflow on a short
+// grid.  The column gets the two points' sum per site and iteration.
+// About 235 FP64 instructions a point and 215 a point and site (286 and 418
+// with the form in the pattern derivatives of each site, its directions
+// evaluated per point); bound by FP64 issue, with waits for the scalar loads
+// of the ~4.5 KB of an event's constants between (73 to 78 % busy at two
+// wavefronts per SIMD).  10^4 mixed events on five sites, 1.1e8 points:
+// 6.66 ms before, 5.33 ms in this form, of which the loads asked for ahead of
+// their use account for 0.33 ms.
 template <int NPI, bool ROT, bool TAB>
 __device__ __attribute__((always_inline)) inline void adjoint_sums2(const EventC& ec, const AdjEventC& ae,
                                                                     const SiteC* sc, const AdjSiteC* as, int n_site,
@@ -170,40 +163,40 @@ __device__ __attribute__((always_inline)) inline void adjoint_sums2(const EventC
       }
     };
     if (it > 0) advance(k);
-    AdjPoint p1, p2;
-    double v1[3], v2[3];
-    values(k, v1);
-    adjoint_point_setup<NPI, ROT>(ec, ae, k < k1 ? k : k1 - 1, p1, v1);
+    AdjPoint ap[2];
+    double vv[2][3];
+    values(k, vv[0]);
     advance(k + nb);
-    values(k + nb, v2);
-    adjoint_point_setup<NPI, ROT>(ec, ae, k + nb < k1 ? k + nb : k1 - 1, p2, v2);
-    if (k >= k1) p1.q.w4A2 = 0.0;
-    if (k + nb >= k1) p2.q.w4A2 = 0.0;
-    for (int s = 0; s < n_site; ++s) {
-      asm volatile("" ::: "memory");
-      double acc[kAdjN];
+    values(k + nb, vv[1]);
+    const int last = k1 - 1;
+    adjoint_point_setup<NPI, ROT, 2>(ec, ae, {k < last ? k : last, k + nb < last ? k + nb : last}, ap, vv);
+    if (k >= k1) ap[0].q.rw = 0.0;
+    if (k + nb >= k1) ap[1].q.rw = 0.0;
+    adjoint_sites<2, TAB, true>(ae, sc, as, n_site, ap, [&](int s, const double (&t)[kAdjN]) {
 #pragma unroll
-      for (int i = 0; i < kAdjN; ++i) acc[i] = 0.0;
-      adjoint_site<TAB>(ae, sc[s], as[s], p1, acc);
-      adjoint_site<TAB>(ae, sc[s], as[s], p2, acc);
-#pragma unroll
-      for (int i = 0; i < kSlots; ++i) atomicAdd(&accl[(s * kSlots + i) * nb + tid], acc[i]);
-    }
+      for (int i = 0; i < kSlots; ++i) atomicAdd(&accl[(s * kSlots + i) * nb + tid], t[i]);
+    });
   }
 }
 
 // The site sums of the workgroup's columns (as adjoint_sums left them), in a
-// fixed order: wave w of the nb / 64 takes the values t = w, w + nb / 64, ...;
-// each lane adds its columns in column order, then the wavefront butterfly.
+// fixed order: wave w of the nb / 64 takes the sites w, w + nb / 64, ...; each
+// lane adds its columns in column order, then recursive halving over the
+// wavefront (10 exchanges for a site's 8 values, 48 with a butterfly each).
 template <bool PAIR>
-__device__ inline void adjoint_columns(const double* accl, int width, int nb, double* out) {
+__device__ inline void adjoint_columns(const double* accl, int n_site, int nb, double* out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int cols = PAIR ? nb >> 1 : nb;
-  for (int t = wave; t < width; t += nb >> 6) {
-    double c = 0.0;
-    for (int j = lane; j < cols; j += 64) c += accl[t * cols + j];
-    const double v = wave_sum_a(c);
-    if (lane == 0) out[t] = v;
+  for (int s = wave; s < n_site; s += nb >> 6) {
+    double v[kSlots];
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) {
+      v[i] = 0.0;
+      for (int j = lane; j < cols; j += 64) v[i] += accl[(s * kSlots + i) * cols + j];
+    }
+    int idx = 0, cnt = kSlots;
+    scatter_sum<kSlots, 32>(v, lane, idx, cnt);
+    if (cnt > 0) out[s * kSlots + idx] = v[0];
   }
 }
 
@@ -236,7 +229,7 @@ __global__ __launch_bounds__(kABlock, 2) void adjoint_kernel(AdjointArgs a) {
   __shared__ AdjEventC ae;
   __shared__ SiteC sc[kMaxSites];
   __shared__ AdjSiteC as[kMaxSites];
-  __shared__ double Gb[P * P];
+  __shared__ double Gb[P * P], GX[P * kNX];
   extern __shared__ double accl[];      // [n_site][kSlots][kABlock / 2]
   __shared__ double site_acc[kMaxSites * kSlots];
   __shared__ int32_t ok;
@@ -265,7 +258,7 @@ __global__ __launch_bounds__(kABlock, 2) void adjoint_kernel(AdjointArgs a) {
     if (tid < n_site * 4) ge[tid] = 0.0;
     return;
   }
-  if (tid == 0) adj_event_setup<NPI>(ec, GbarLds{Gb, P}, ae);
+  adj_event_setup<NPI>(ec, GbarLds{Gb, P}, ae, GX, tid, kABlock, [] { __syncthreads(); });
   if (tid < n_site) {
     const uint32_t arms = site_arms_on(a.active, a.ld, e, a.net, tid);
     site_setup(p, a.net.site[tid], ec, sc[tid], arms);
@@ -275,7 +268,7 @@ __global__ __launch_bounds__(kABlock, 2) void adjoint_kernel(AdjointArgs a) {
   __syncthreads();
   adjoint_sums<NPI, ROT, TAB, true>(ec, ae, sc, as, n_site, 0, ec.n, kABlock, accl);
   __syncthreads();
-  adjoint_columns<true>(accl, n_site * kSlots, kABlock, site_acc);
+  adjoint_columns<true>(accl, n_site, kABlock, site_acc);
   __syncthreads();
   if (tid < n_site * 4) {
     const int s = tid >> 2, m = tid & 3;
@@ -294,7 +287,7 @@ __global__ __launch_bounds__(kABlock) void reduce_kernel(const double* __restric
   const int c = blockIdx.x, tid = threadIdx.x;
   double t = 0.0;
   for (int64_t e = tid; e < n; e += kABlock) t += terms[e * width + c];
-  t = wave_sum_a(t);
+  t = wave_sum(t);
   if ((tid & 63) == 0) red[tid >> 6] = t;
   __syncthreads();
   if (tid == 0) {
@@ -305,29 +298,44 @@ __global__ __launch_bounds__(kABlock) void reduce_kernel(const double* __restric
 }
 
 // ---------------------------------------------------- batched (work items)
-// After the plan's set-up kernel has written EventC and SiteC: lanes
-// [0, n) take one event each, the contractions of its Gbar (AdjEventC, ok = 0
-// where the event is left out); lanes [n, n + n n_site) one (event, site)
-// pair each, its AdjSiteC (not written for an event whose set-up failed).
+// After the plan's set-up kernel has written EventC and SiteC.  The first
+// blocks take kSetupEvents events each, kSetupLanes lanes an event: the
+// contractions of its Gbar (AdjEventC, ok = 0 where the event is left out)
+// from a copy in LDS, whose loads are in flight together; with one lane an
+// event the set-up was as long as its ~200 loads one after the other (55 us
+// at 1000 events, 13 us in this form).  The other blocks take one (event, site)
+// pair a lane, its AdjSiteC (not written for an event whose set-up failed).
+constexpr int kSetupLanes = 16, kSetupEvents = 4;
+
 template <int NPI>
-__global__ __launch_bounds__(64) void adj_setup_kernel(AdjSetupArgs a) {
+__global__ __launch_bounds__(kSetupLanes * kSetupEvents) void adj_setup_kernel(AdjSetupArgs a, unsigned event_blocks) {
   constexpr int P = PhaseOnly<NPI>::P;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  constexpr int kLanes = kSetupLanes * kSetupEvents;
   const int n_site = a.net.n_site;
-  if (t < a.n) {
-    const int64_t e = t;
+  if (blockIdx.x < event_blocks) {
+    __shared__ double Gb[kSetupEvents][P * P], GX[kSetupEvents][P * kNX];
+    const int l = threadIdx.x % kSetupLanes, g = threadIdx.x / kSetupLanes;
+    const int64_t e0 = (int64_t)blockIdx.x * kSetupEvents;
+    const bool in = e0 + g < a.n;
+    const int64_t e = in ? e0 + g : a.n - 1;     // lanes past the end: the last event, nothing written
     const EventC& ec = a.evc[e];
-    const GbarOf gb{a.gbar, a.n, e, P, event_rows(a.par_mask, e)};
-    int32_t ok = ec.status == 0 && (a.status == nullptr || a.status[e] == 0);
-    for (int i = 0; i < P; ++i)               // gb is symmetric: the upper triangle decides
-      for (int j = i; j < P; ++j)
-        if (!finite(gb(i, j))) ok = 0;
-    AdjEventC& ae = a.aec[e];
-    adj_event_setup<NPI>(ec, gb, ae);
-    ae.ok = ok;
+    const uint32_t pm = event_rows(a.par_mask, e);
+    int bad = ec.status != 0 || (a.status != nullptr && a.status[e] != 0);
+    for (int t = l; t < P * P; t += kSetupLanes) {
+      const double x = GbarOf{a.gbar, a.n, e, P, pm}(t / P, t % P);
+      Gb[g][t] = x;
+      bad |= !finite(x);
+    }
+#pragma unroll
+    for (int off = kSetupLanes / 2; off >= 1; off >>= 1) bad |= __shfl_xor(bad, off, kSetupLanes);
+    __syncthreads();
+    __shared__ AdjEventC spare;                  // where the lanes past the end write
+    AdjEventC& ae = in ? a.aec[e] : spare;
+    adj_event_setup<NPI>(ec, GbarLds{Gb[g], P}, ae, GX[g], l, kSetupLanes, [] { __syncthreads(); });
+    if (l == 0) ae.ok = !bad;
     return;
   }
-  const int64_t u = t - a.n;
+  const int64_t u = (int64_t)(blockIdx.x - event_blocks) * kLanes + threadIdx.x;
   if (u >= a.n * n_site) return;
   const int64_t e = u / n_site;
   const int s = (int)(u - e * n_site);
@@ -340,7 +348,9 @@ __global__ __launch_bounds__(64) void adj_setup_kernel(AdjSetupArgs a) {
 
 // Two wavefronts per SIMD (the sums live in LDS, 40 KB per workgroup on
 // five sites).  Larger workgroups put fewer events' constants in a compute
-// unit's scalar cache but were measured slower on the mixed BBH/BNS workload.
+// unit's scalar cache but were measured slower on 10^4 mixed BBH/BNS events
+// (128 lanes 5.73 ms, 256 5.97 ms, 512 6.49 ms, before the loads were asked
+// for ahead).
 template <int NPI, bool ROT, bool TAB>
 __global__ __launch_bounds__(kABlock, 2) void adjoint_items_kernel(AdjItemsArgs a) {
   extern __shared__ double accl[];        // [n_site][kSlots][kABlock]
@@ -375,33 +385,31 @@ __global__ __launch_bounds__(kABlock, 2) void adjoint_items_kernel(AdjItemsArgs 
   if (PhaseOnly<NPI>::ecc) adjoint_sums<NPI, ROT, TAB, false>(ec, ae, sc, as, n_site, k0, k1, kABlock, accl);
   else adjoint_sums2<NPI, ROT, TAB>(ec, ae, sc, as, n_site, k0, k1, kABlock, accl);
   __syncthreads();
-  adjoint_columns<false>(accl, width, kABlock, out);
+  adjoint_columns<false>(accl, n_site, kABlock, out);
 }
 
-// One lane per event: its items' sums in item order, then the gradient terms.
+// One lane per (event, site): the site's items' sums in item order, then its
+// gradient terms; the SNR^2 of the network is summed by each of them.
 __global__ void adjoint_combine_kernel(AdjCombineArgs a) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= a.n) return;
+  const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (u >= a.n * a.n_site) return;
+  const int64_t e = u / a.n_site;
   const int width = a.n_site * kSlots;
   const int32_t i0 = a.item_first[e], i1 = a.item_first[e + 1];
   double W = 0.0;
   for (int s = 0; s < a.n_site; ++s)
-    for (int32_t i = i0; i < i1; ++i) W += a.partial[(int64_t)i * width + s * kSlots + 7];
+    for (int32_t i = i0; i < i1; ++i) W += a.partial[(int64_t)i * width + s * kSlots + kAdjW];
   const bool ok = W > 0.0 && finite(W);
-  double* ge = a.grad_event + e * (int64_t)(a.n_site * 4);
-  for (int s = 0; s < a.n_site; ++s) {
-    double t[kSlots];
+  const double* part = a.partial + (u - e * a.n_site) * kSlots;
+  double t[kSlots] = {};
+  for (int32_t i = i0; i < i1; ++i)
 #pragma unroll
-    for (int m = 0; m < kSlots; ++m) t[m] = 0.0;
-    for (int32_t i = i0; i < i1; ++i)
+    for (int m = 0; m < kSlots; ++m) t[m] += part[(int64_t)i * width + m];
 #pragma unroll
-      for (int m = 0; m < kSlots; ++m) t[m] += a.partial[(int64_t)i * width + s * kSlots + m];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      // d SNR^2 along ln S0 of a site is minus that site's SNR^2
-      const double dS = m < 3 ? t[4 + m] : -t[7];
-      ge[s * 4 + m] = ok ? fma(a.w_fisher, t[m], a.w_snr * dS / (2.0 * W)) : 0.0;
-    }
+  for (int m = 0; m < 4; ++m) {
+    // d SNR^2 along ln S0 of a site is minus that site's SNR^2
+    const double dS = m < 3 ? t[kAdjS + m] : -t[kAdjW];
+    a.grad_event[u * 4 + m] = ok ? fma(a.w_fisher, t[kAdjT + m], a.w_snr * dS / (2.0 * W)) : 0.0;
   }
 }
 
@@ -421,13 +429,14 @@ void launch_adjoint_items_n(const AdjItemsArgs& a, bool rot, bool tab, dim3 grid
 }
 
 hipError_t launch_adjoint_setup(const AdjSetupArgs& a, int npi, hipStream_t s) {
-  const int64_t lanes = a.n * (1 + (int64_t)a.net.n_site);
-  const dim3 grid((unsigned)((lanes + 63) / 64)), block(64);
+  const unsigned ev = (unsigned)((a.n + kSetupEvents - 1) / kSetupEvents);
+  const unsigned lanes = kSetupLanes * kSetupEvents;
+  const dim3 grid(ev + (unsigned)((a.n * a.net.n_site + lanes - 1) / lanes)), block(lanes);
   switch (npi) {
-    case 6: hipLaunchKernelGGL((adj_setup_kernel<6>), grid, block, 0, s, a); break;
-    case 5: hipLaunchKernelGGL((adj_setup_kernel<5>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((adj_setup_kernel<4>), grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL((adj_setup_kernel<3>), grid, block, 0, s, a);
+    case 6: hipLaunchKernelGGL((adj_setup_kernel<6>), grid, block, 0, s, a, ev); break;
+    case 5: hipLaunchKernelGGL((adj_setup_kernel<5>), grid, block, 0, s, a, ev); break;
+    case 4: hipLaunchKernelGGL((adj_setup_kernel<4>), grid, block, 0, s, a, ev); break;
+    default: hipLaunchKernelGGL((adj_setup_kernel<3>), grid, block, 0, s, a, ev);
   }
   return hipGetLastError();
 }
@@ -446,7 +455,7 @@ hipError_t launch_adjoint_items(const AdjItemsArgs& a0, int npi, bool rot, hipSt
 }
 
 hipError_t launch_adjoint_combine(const AdjCombineArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(adjoint_combine_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(adjoint_combine_kernel, dim3((unsigned)((a.n * a.n_site + 255) / 256)), dim3(256), 0, s, a);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   const int width = a.n_site * 4;

@@ -14,30 +14,32 @@
 //
 // Structure used (exact algebra).  An interferometer enters D only through
 // its six pattern values y = (F+, Fx, dF+/dH, dFx/dH, dF+/dth, dFx/dth)
-// (H the hour angle): with c+ = (1 + cos^2 i)/2, cx = cos i,
-//   Dr = v0 y0 + (-cx rho + 2 c+ e6) y1 + c+ gamma y2 + c+ e3 y4,
-//   Di = (c+ rho - 2 cx e6) y0 + w1 y1 + cx gamma y3 + cx e3 y5,
+// (H the hour angle).  With Q = (c+ y0, cx y1), c+ = (1 + cos^2 i)/2,
+// cx = cos i, and Z, Y as in the forward pass (gwf_model.hpp: the hour-angle
+// and theta derivatives of Q with the delay's phase terms i u Q, i w Q),
+//   Re D = v0 y0 + (2 c+ e6 - cx pi) y1 + gamma Re Z + e3 Re Y,
+//   Im D = (c+ pi - 2 cx e6) y0 + w1 y1 + gamma Im Z + e3 Im Y,
 // where e3, e6 are the unit vectors of theta and psi, v0 and w1 fixed
-// per-event vectors (amplitude, distance and inclination rows), gamma the
-// hour-angle direction of the phase derivatives (Mc, eta through the
-// sidereal angle at t(f); phi; tc) and rho = pi + 2 pi f (dDelta/dH gamma +
-// dDelta/dth e3) the site's phase-derivative vector (pi: the PN phase
-// derivatives, 2 pi f for tc and the phase-only coefficients c_i).  So the
-// form is y^T H y with H = M^T Gbar M built from the Gbar inner products
-// <a, b> = a^T Gbar b of just six vectors {pi, gamma, e3, e6, v0, w1}: those
-// among the fixed ones once per event, those with pi and gamma once per grid
-// point (shared by all sites), and those with rho, which depend on the
-// site's arrival-time derivatives, by two multiply-adds each per site.  Per
-// interferometer the point then needs two 4 x 4 quadratic forms in y instead
-// of z = Gbar D (an 8 x 8 product for two vectors).
+// per-event vectors (amplitude, distance and inclination rows), pi the PN
+// phase derivatives (with 2 pi f for tc and the phase-only coefficients c_i)
+// and gamma the hour-angle direction of the phase derivatives (Mc, eta
+// through the sidereal angle at t(f); phi; tc).  None of these vectors knows
+// the site, so the quadratic form's 14 coefficients are formed once per grid
+// point from Gbar inner products <a, b> = a^T Gbar b (AdjPoint), and an
+// interferometer costs 28 multiply-adds for the form's gradient h in
+// (y0, y1, Z, Y).
 //
 // Derivatives: J_point depends on the detector parameters through y (the
 // patterns: latitude and gamma move their coefficients, longitude the hour
 // angle H), through the arrival-time derivatives dDelta/dH and dDelta/dth
 // (latitude and longitude) and, for ln S0, through the weight (dw = -w).
-// The patterns are trigonometric polynomials in H (SiteC::jk), so along
-// longitude y' follows from the same coefficients, and along latitude and
-// gamma from their per-event derivatives (AdjSiteC).
+// The patterns are trigonometric polynomials in H (SiteC::jk) whose five
+// basis functions no direction changes: along every direction dy follows
+// from that direction's coefficients and the same basis.  So the gradient is
+// taken in the coefficients (4 polynomials x 5, and 2 x 5 for SNR^2), summed
+// over the points a lane holds, and contracted once with each direction's
+// coefficients (latitude and gamma: AdjSiteC; longitude: jk's own, turned),
+// in place of evaluating each direction's polynomials at every point.
 #pragma once
 
 #include "gwf_model.hpp"
@@ -215,85 +217,93 @@ struct AdjEventC {
   double cq[kMaxNpi * (kMaxNpi + 1) / 2];    // <e_{8+i}, e_{8+j}> for i = j, twice that for i < j
   double xx[kNX * (kNX + 1) / 2];            // <X, Y>
   double cpl, ccr;                           // c+, cx
-  // products of the above that the per-site rows need (see adjoint_site)
+  double cpp, cxx, cc4;                      // c+^2, cx^2, 4 c+ cx
+  // constant parts of the point's coefficients (see AdjPoint)
   double h00c, h11c;                         // <v0,v0> + 4 cx^2 <e6,e6>, <w1,w1> + 4 c+^2 <e6,e6>
   double h01c;                               // 2 c+ <e6,v0> - 2 cx <e6,w1>
-  double h04, h15;                           // c+ <e3,v0>, cx <e3,w1>
-  double cpx33, cxx33;                       // c+ <e3,e3>, cx <e3,e3>
   double cp2x36, cx2x36;                     // 2 c+ <e3,e6>, 2 cx <e3,e6>
   int32_t ok, pad;
 };
 
-// gb(i, j): Gbar_ij, symmetric, zero outside the event's rows.  The fixed
-// vectors have at most three nonzero entries each, so Gbar X takes those
-// columns of Gbar only; every index is fixed at compile time.
-template <int NPI, class GB>
-__host__ __device__ inline void adj_event_setup(const EventC& ec, const GB& gb, AdjEventC& ae) {
+// gb(i, j): Gbar_ij, symmetric, zero outside the event's rows; GX: scratch
+// of (8 + NPI) kNX values.  The work is shared by `lanes` callers (this one:
+// `lane`), which sync() brings together; the fixed vectors have at most three
+// nonzero entries each, so Gbar X takes those columns of Gbar only.
+template <int NPI, class GB, class SYNC>
+__host__ __device__ inline void adj_event_setup(const EventC& ec, const GB& gb, AdjEventC& ae, double* GX, int lane,
+                                                int lanes, SYNC sync) {
   const double v0a = ec.dlnA_dMc * ec.cplus, v0b = -ec.cplus * ec.inv_dL, v0c = ec.dcplus;
   const double w1a = ec.dlnA_dMc * ec.ccross, w1b = -ec.ccross * ec.inv_dL, w1c = ec.dcross;
   // X_x^T v for a vector v on the binary's eight rows (Mc, eta, dL, theta,
-  // phi, iota, psi, tc)
-  auto xdot = [&](int x, const double* v) -> double {
+  // phi, iota, psi, tc), its entries st apart
+  auto xdot = [&](int x, const double* v, int st) -> double {
     switch (x) {
-      case kXe3: return v[3];
-      case kXe6: return v[6];
-      case kXv0: return fma(v0c, v[5], fma(v0b, v[2], v0a * v[0]));
-      case kXw1: return fma(w1c, v[5], fma(w1b, v[2], w1a * v[0]));
-      default: return fma(kOmegaE, v[7], -v[4]);
+      case kXe3: return v[3 * st];
+      case kXe6: return v[6 * st];
+      case kXv0: return fma(v0c, v[5 * st], fma(v0b, v[2 * st], v0a * v[0]));
+      case kXw1: return fma(w1c, v[5 * st], fma(w1b, v[2 * st], w1a * v[0]));
+      default: return fma(kOmegaE, v[7 * st], -v[4 * st]);
     }
   };
-  double GX[kNX][8];                           // (Gbar X)_r on the eight rows
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
+  for (int r = lane; r < 8 + NPI; r += lanes) {      // (Gbar X)_r
     double row[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) row[c] = gb(r, c);
 #pragma unroll
-    for (int x = 0; x < kNX; ++x) GX[x][r] = xdot(x, row);
+    for (int x = 0; x < kNX; ++x) GX[r * kNX + x] = xdot(x, row, 1);
   }
-#pragma unroll
-  for (int i = 0; i < kMaxNpi; ++i) {
-    double row[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) row[c] = i < NPI ? gb(8 + i, c) : 0.0;
-#pragma unroll
-    for (int x = 0; x < kNX; ++x) ae.cx[x][i] = i < NPI ? xdot(x, row) : 0.0;
-  }
+  sync();
   constexpr int rows[3] = {0, 1, 7};
-  ae.g3[0] = gb(0, 0); ae.g3[1] = gb(0, 1); ae.g3[2] = gb(0, 7);
-  ae.g3[3] = gb(1, 1); ae.g3[4] = gb(1, 7); ae.g3[5] = gb(7, 7);
-#pragma unroll
-  for (int b = 0; b < 3; ++b)
-#pragma unroll
-    for (int x = 0; x < kNX; ++x) ae.bx[b][x] = GX[x][rows[b]];
-#pragma unroll
-  for (int b = 0; b < 3; ++b)
-#pragma unroll
-    for (int i = 0; i < kMaxNpi; ++i) ae.cb[b][i] = i < NPI ? gb(rows[b], 8 + i) : 0.0;
-#pragma unroll
-  for (int i = 0; i < kMaxNpi; ++i)
-#pragma unroll
-    for (int j = i; j < kMaxNpi; ++j)
-      ae.cq[cc_index(i, j)] = (i < NPI && j < NPI) ? (i == j ? 1.0 : 2.0) * gb(8 + i, 8 + j) : 0.0;
-#pragma unroll
-  for (int x = 0; x < kNX; ++x)
-#pragma unroll
-    for (int y = x; y < kNX; ++y) ae.xx[xx_index(x, y)] = xdot(y, GX[x]);
-  ae.cpl = ec.cplus;
-  ae.ccr = ec.ccross;
-  const double cp = ec.cplus, cx = ec.ccross;
-  const double x66 = ae.xx[xx_index(kXe6, kXe6)], x33 = ae.xx[xx_index(kXe3, kXe3)];
-  const double x36 = ae.xx[xx_index(kXe3, kXe6)];
-  ae.h00c = ae.xx[xx_index(kXv0, kXv0)] + 4.0 * cx * cx * x66;
-  ae.h11c = ae.xx[xx_index(kXw1, kXw1)] + 4.0 * cp * cp * x66;
-  ae.h01c = 2.0 * cp * ae.xx[xx_index(kXe6, kXv0)] - 2.0 * cx * ae.xx[xx_index(kXe6, kXw1)];
-  ae.h04 = cp * ae.xx[xx_index(kXe3, kXv0)];
-  ae.h15 = cx * ae.xx[xx_index(kXe3, kXw1)];
-  ae.cpx33 = cp * x33;
-  ae.cxx33 = cx * x33;
-  ae.cp2x36 = 2.0 * cp * x36;
-  ae.cx2x36 = 2.0 * cx * x36;
-  ae.pad = 0;
+  for (int t = lane; t < 8; t += lanes) {
+    auto XX = [&](int x, int y) { return xdot(y, GX + x, kNX); };     // <X, Y>
+    const double cp = ec.cplus, cx = ec.ccross;
+    switch (t) {
+      case 0:
+        ae.g3[0] = gb(0, 0); ae.g3[1] = gb(0, 1); ae.g3[2] = gb(0, 7);
+        ae.g3[3] = gb(1, 1); ae.g3[4] = gb(1, 7); ae.g3[5] = gb(7, 7);
+        break;
+      case 1:
+        for (int b = 0; b < 3; ++b)
+          for (int x = 0; x < kNX; ++x) ae.bx[b][x] = GX[rows[b] * kNX + x];
+        break;
+      case 2:
+        ae.cpl = cp;
+        ae.ccr = cx;
+        ae.cpp = cp * cp;
+        ae.cxx = cx * cx;
+        ae.cc4 = 4.0 * cp * cx;
+        ae.pad = 0;
+        break;
+      case 3: ae.h00c = XX(kXv0, kXv0) + 4.0 * cx * cx * XX(kXe6, kXe6); break;
+      case 4: ae.h11c = XX(kXw1, kXw1) + 4.0 * cp * cp * XX(kXe6, kXe6); break;
+      case 5: ae.h01c = 2.0 * cp * XX(kXe6, kXv0) - 2.0 * cx * XX(kXe6, kXw1); break;
+      case 6: ae.cp2x36 = 2.0 * cp * XX(kXe3, kXe6); break;
+      default: ae.cx2x36 = 2.0 * cx * XX(kXe3, kXe6);
+    }
+  }
+  for (int t = lane; t < kNX * kMaxNpi; t += lanes) {
+    const int x = t / kMaxNpi, i = t - x * kMaxNpi;
+    ae.cx[x][i] = i < NPI ? GX[(8 + i) * kNX + x] : 0.0;
+  }
+  for (int t = lane; t < 3 * kMaxNpi; t += lanes) {
+    const int b = t / kMaxNpi, i = t - b * kMaxNpi;
+    ae.cb[b][i] = i < NPI ? gb(b == 2 ? 7 : b, 8 + i) : 0.0;
+  }
+  for (int t = lane; t < kMaxNpi * kMaxNpi; t += lanes) {
+    const int i = t / kMaxNpi, j = t - i * kMaxNpi;
+    if (i <= j) ae.cq[cc_index(i, j)] = (i < NPI && j < NPI) ? (i == j ? 1.0 : 2.0) * gb(8 + i, 8 + j) : 0.0;
+  }
+  for (int t = lane; t < kNX * kNX; t += lanes) {
+    const int x = t / kNX, y = t - x * kNX;
+    if (x <= y) ae.xx[xx_index(x, y)] = xdot(y, GX + x, kNX);
+  }
+}
+
+// By one caller.
+template <int NPI, class GB>
+__host__ __device__ inline void adj_event_setup(const EventC& ec, const GB& gb, AdjEventC& ae) {
+  double GX[(8 + NPI) * kNX];
+  adj_event_setup<NPI>(ec, gb, ae, GX, 0, 1, [] {});
 }
 
 // Accumulator slots of one site: sum Gbar dGamma along (lat, lon, gamma,
@@ -302,184 +312,302 @@ __host__ __device__ inline void adj_event_setup(const EventC& ec, const GB& gb, 
 enum { kAdjT = 0, kAdjS = 4, kAdjW = 7, kAdjN = 8 };
 
 // ------------------------------------------------------ one grid point
-// The point quantities shared by all sites: the inner products of pi and
-// gamma with each other and with the fixed vectors.
+// The point quantities shared by all sites: the coefficients of the quadratic
+// form in (y0, y1, Z, Y), with r = 2 c+ e6 - cx pi and m = c+ pi - 2 cx e6
+// (<e3,v0>, <e3,w1> and <e3,e3> are the event's).
 struct AdjPoint {
   Point q;
-  double pX[kNX];        // <pi, X>
-  double gX[4];          // <gamma, X>, X = e3, e6, v0, w1
-  double pp, pg, gg;     // <pi, pi>, <pi, gamma>, <gamma, gamma>
-  // products the per-site rows take from them
-  double cpgg, cxgg, cpg3, cxg3;   // c+ <g,g>, cx <g,g>, c+ <g,e3>, cx <g,e3>
-  double h02, h13;                 // c+ <g,v0>, cx <g,w1>
-  double cp2g6, cx2g6;             // 2 c+ <g,e6>, 2 cx <g,e6>
+  double k00, k11, k01;        // <v0,v0> + <m,m>, <w1,w1> + <r,r>, <v0,r> + <m,w1>
+  double gv0, gr, gm, gw1;     // <gamma, v0>, <gamma, r>, <gamma, m>, <gamma, w1>
+  double er, em;               // <e3, r>, <e3, m>
+  double gg, g3;               // <gamma, gamma>, <gamma, e3>
 };
 
-// vrec: v, 1/v and v^-12.42 at the point (GridWalk), or NULL.
-template <int NPI, bool ROT>
-__host__ __device__ inline void adjoint_point_setup(const EventC& ec, const AdjEventC& ae, int32_t k,
-                                                    AdjPoint& ap, const double* vrec = nullptr) {
-  point_setup<false, PhaseOnly<NPI>::ecc>(ec, k, true, ROT, ap.q, kPsdF64, vrec);
-  const Point& q = ap.q;
-  double c[NPI];
-  phase_only_coefficients<NPI>(ec, q, c);
-  // u_b = <e_b, C>, C = sum c_i e_{8+i}; cCc = <C, C>
-  double u[3];
-#pragma unroll
-  for (int b = 0; b < 3; ++b) {
-    double t = 0.0;
-#pragma unroll
-    for (int i = 0; i < NPI; ++i) t = fma(ae.cb[b][i], c[i], t);
-    u[b] = t;
-  }
-  // cCc = sum_i c_i (Gbar_ii c_i + 2 sum_{j > i} Gbar_ij c_j)
-  double cCc = 0.0;
-#pragma unroll
-  for (int i = 0; i < NPI; ++i) {
-    double t = 0.0;
-#pragma unroll
-    for (int j = i; j < NPI; ++j) t = fma(ae.cq[cc_index(i, j)], c[j], t);
-    cCc = fma(c[i], t, cCc);
-  }
-  // pi = pMc e0 + pEta e1 + tf e7 + C
-  const double pm = q.pMc, pe = q.pEta, tf = q.tf;
-#pragma unroll
-  for (int x = 0; x < kNX; ++x) {
-    double t = fma(pm, ae.bx[0][x], fma(pe, ae.bx[1][x], tf * ae.bx[2][x]));
-#pragma unroll
-    for (int i = 0; i < NPI; ++i) t = fma(c[i], ae.cx[x][i], t);
-    ap.pX[x] = t;
-  }
-  const double pe0 = fma(pm, ae.g3[0], fma(pe, ae.g3[1], fma(tf, ae.g3[2], u[0])));   // <pi, e0>
-  const double pe1 = fma(pm, ae.g3[1], fma(pe, ae.g3[3], fma(tf, ae.g3[4], u[1])));   // <pi, e1>
-  const double pe7 = fma(pm, ae.g3[2], fma(pe, ae.g3[4], fma(tf, ae.g3[5], u[2])));   // <pi, e7>
-  ap.pp = fma(pm, pe0, fma(pe, pe1, fma(tf, pe7, fma(pm, u[0], fma(pe, u[1], fma(tf, u[2], cCc))))));
-  // gamma = gMc e0 + gEta e1 + gamma0 (gMc = gEta = 0 without rotation)
-  const double gm = q.gMc, ge = q.gEta;
-#pragma unroll
-  for (int x = 0; x < 4; ++x) ap.gX[x] = fma(gm, ae.bx[0][x], fma(ge, ae.bx[1][x], ae.xx[xx_index(kXg0, x)]));
-  ap.pg = fma(gm, pe0, fma(ge, pe1, ap.pX[kXg0]));
-  const double ge0 = fma(gm, ae.g3[0], fma(ge, ae.g3[1], 2.0 * ae.bx[0][kXg0]));
-  const double ge1 = fma(gm, ae.g3[1], fma(ge, ae.g3[3], 2.0 * ae.bx[1][kXg0]));
-  ap.gg = fma(gm, ge0, fma(ge, ge1, ae.xx[xx_index(kXg0, kXg0)]));
-  const double cp = ae.cpl, cx = ae.ccr;
-  ap.cpgg = cp * ap.gg;
-  ap.cxgg = cx * ap.gg;
-  ap.cpg3 = cp * ap.gX[kXe3];
-  ap.cxg3 = cx * ap.gX[kXe3];
-  ap.h02 = cp * ap.gX[kXv0];
-  ap.h13 = cx * ap.gX[kXw1];
-  ap.cp2g6 = 2.0 * cp * ap.gX[kXe6];
-  ap.cx2g6 = 2.0 * cx * ap.gX[kXe6];
+// Marks memory as changed: what is read behind it is read there (scalar loads
+// of an event's constants), not held in registers from before.
+__host__ __device__ inline void constants_again() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __asm__ volatile("" ::: "memory");
+#endif
 }
 
-// A trigonometric polynomial of SiteC::jk and its second hour-angle
-// derivative from the same partial sums: with a1 = c1 cos H + c2 sin H and
-// a2 = c3 cos 2H + c4 sin H cos H, y = c0 + a1 + a2 and y'' = -(a1 + 4 a2).
-__host__ __device__ inline void trig_val_dHH(const double c[5], const SiteTrig& sp, double& y, double& yhh) {
-  const double a1 = fma(c[2], sp.sH, c[1] * sp.cH);
-  const double a2 = fma(c[4], sp.sc, c[3] * sp.c2H);
-  y = (a1 + a2) + c[0];
-  yhh = -fma(4.0, a2, a1);
+// The NQ points k of an event; vrec: v, 1/v and v^-12.42 at each (GridWalk), or
+// NULL.  Each group of constants is read once for all points.
+template <int NPI, bool ROT, int NQ>
+__host__ __device__ inline void adjoint_point_setup(const EventC& ec, const AdjEventC& ae, const int32_t (&k)[NQ],
+                                                    AdjPoint (&ap)[NQ], const double (*vrec)[3] = nullptr) {
+  double c[NQ][NPI];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {
+    constants_again();
+    point_setup<false, PhaseOnly<NPI>::ecc>(ec, k[n], true, ROT, ap[n].q, kPsdF64, vrec ? vrec[n] : nullptr);
+    phase_only_coefficients<NPI>(ec, ap[n].q, c[n]);
+  }
+  constants_again();
+  // u_b = <e_b, C>, C = sum c_i e_{8+i}; pp = <C, C>
+  //   = sum_i c_i (Gbar_ii c_i + 2 sum_{j > i} Gbar_ij c_j)
+  double u[NQ][3], pp[NQ];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      double t = 0.0;
+#pragma unroll
+      for (int i = 0; i < NPI; ++i) t = fma(ae.cb[b][i], c[n][i], t);
+      u[n][b] = t;
+    }
+    pp[n] = 0.0;
+#pragma unroll
+    for (int i = 0; i < NPI; ++i) {
+      double t = 0.0;
+#pragma unroll
+      for (int j = i; j < NPI; ++j) t = fma(ae.cq[cc_index(i, j)], c[n][j], t);
+      pp[n] = fma(c[n][i], t, pp[n]);
+    }
+  }
+  constants_again();
+  // pi = pMc e0 + pEta e1 + tf e7 + C; pe: <pi, e0> and <pi, e1>
+  double pX[NQ][kNX], pe[NQ][2];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {
+    const double a = ap[n].q.pMc, b = ap[n].q.pEta, tf = ap[n].q.tf;
+    pe[n][0] = fma(a, ae.g3[0], fma(b, ae.g3[1], fma(tf, ae.g3[2], u[n][0])));
+    pe[n][1] = fma(a, ae.g3[1], fma(b, ae.g3[3], fma(tf, ae.g3[4], u[n][1])));
+    const double pe7 = fma(a, ae.g3[2], fma(b, ae.g3[4], fma(tf, ae.g3[5], u[n][2])));
+    pp[n] = fma(a, pe[n][0], fma(b, pe[n][1], fma(tf, pe7, fma(a, u[n][0], fma(b, u[n][1], fma(tf, u[n][2], pp[n]))))));
+#pragma unroll
+    for (int x = 0; x < kNX; ++x) pX[n][x] = fma(a, ae.bx[0][x], fma(b, ae.bx[1][x], tf * ae.bx[2][x]));
+  }
+  constants_again();
+#pragma unroll
+  for (int n = 0; n < NQ; ++n)
+#pragma unroll
+    for (int x = 0; x < kNX; ++x)
+#pragma unroll
+      for (int i = 0; i < NPI; ++i) pX[n][x] = fma(c[n][i], ae.cx[x][i], pX[n][x]);
+  constants_again();
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {
+    AdjPoint& p = ap[n];
+    // gamma = gMc e0 + gEta e1 + gamma0 (gMc = gEta = 0 without rotation)
+    const double gm = p.q.gMc, ge = p.q.gEta;
+    double gX[4];                                // <gamma, X>
+#pragma unroll
+    for (int x = 0; x < 4; ++x) gX[x] = fma(gm, ae.bx[0][x], fma(ge, ae.bx[1][x], ae.xx[xx_index(kXg0, x)]));
+    const double pg = fma(gm, pe[n][0], fma(ge, pe[n][1], pX[n][kXg0]));
+    const double ge0 = fma(gm, ae.g3[0], fma(ge, ae.g3[1], 2.0 * ae.bx[0][kXg0]));
+    const double ge1 = fma(gm, ae.g3[1], fma(ge, ae.g3[3], 2.0 * ae.bx[1][kXg0]));
+    const double cp = ae.cpl, cx = ae.ccr;
+    const double c6 = -ae.cc4 * pX[n][kXe6];
+    p.k00 = fma(ae.cpp, pp[n], ae.h00c + c6);
+    p.k11 = fma(ae.cxx, pp[n], ae.h11c + c6);
+    p.k01 = fma(-cx, pX[n][kXv0], fma(cp, pX[n][kXw1], ae.h01c));
+    p.gv0 = gX[kXv0];
+    p.gw1 = gX[kXw1];
+    p.gr = fma(-cx, pg, 2.0 * cp * gX[kXe6]);
+    p.gm = fma(cp, pg, -2.0 * cx * gX[kXe6]);
+    p.er = fma(-cx, pX[n][kXe3], ae.cp2x36);
+    p.em = fma(cp, pX[n][kXe3], -ae.cx2x36);
+    p.gg = fma(gm, ge0, fma(ge, ge1, ae.xx[xx_index(kXg0, kXg0)]));
+    p.g3 = gX[kXe3];
+  }
 }
 
-// Adds the contribution of one site at the point to acc[kAdjN].
-template <bool TAB>
-__host__ __device__ inline void adjoint_site(const AdjEventC& ae, const SiteC& sc, const AdjSiteC& as,
-                                             const AdjPoint& ap, double* acc) {
-  const Point& q = ap.q;
-  SiteTrig sp;
-  site_trig<TAB>(sc, q, sp);
-  const double tf = q.tf;
-  const double a = tf * sp.dH, b = tf * sp.dT;
-  const double cp = ae.cpl, cx = ae.ccr;
-  // <rho, X> for the site's rho = pi + a gamma + b e3
-  double R[4];
+// What a site's trigonometry and noise weight take from its constants.
+struct SiteHead {
+  double cdl, sdl, k1, k1t, k0t, x2_fac, xpS0, m5S0, k111S0;
+};
+
+__host__ __device__ inline SiteHead site_head(const SiteC& sc) {
+  return SiteHead{sc.cdl, sc.sdl, sc.k1, sc.k1t, sc.k0t, sc.x2_fac, sc.xpS0, sc.m5S0, sc.k111S0};
+}
+
+// The constants read before this line are asked for here, ahead of the work
+// behind it: scalar loads complete out of order, so a use waits for every load
+// in flight, and left alone the compiler puts each group right before its use.
+__host__ __device__ inline void loads_ahead() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __asm__ volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
+struct Poly4 {
+  double c[4][5];
+};
+
+__host__ __device__ inline Poly4 poly4(const double (&p)[4][5]) {
+  Poly4 r;
 #pragma unroll
-  for (int x = 0; x < 4; ++x) R[x] = fma(a, ap.gX[x], fma(b, ae.xx[xx_index(kXe3, x)], ap.pX[x]));
-  const double Rg = fma(a, ap.gg, fma(b, ap.gX[kXe3], ap.pg));
-  const double Rr = fma(a, ap.pg + Rg, fma(b, ap.pX[kXe3] + R[kXe3], ap.pp));   // <rho, rho>
-  // rows gamma^T Gbar M and e3^T Gbar M of the real (y0, y1, y2, y4) and
-  // imaginary (y0, y1, y3, y5) parts
-  const double rg1 = fma(-cx, Rg, ap.cp2g6);
-  const double re1 = fma(-cx, R[kXe3], ae.cp2x36);
-  const double ig0 = fma(cp, Rg, -ap.cx2g6);
-  const double ie0 = fma(cp, R[kXe3], -ae.cx2x36);
-  // rows 0 and 1 of Hr + Hi (the y0, y1 rows, where both parts meet)
-  const double f = 4.0 * cp * cx * R[kXe6];
-  const double h00 = fma(cp * cp, Rr, ae.h00c - f);
-  const double h11 = fma(cx * cx, Rr, ae.h11c - f);
-  const double h01 = fma(-cx, R[kXv0], fma(cp, R[kXw1], ae.h01c));
-  const double h03 = cx * ig0, h05 = cx * ie0, h12 = cp * rg1, h14 = cp * re1;
-  const double twom = 2.0 * sp.om;
-  const double om = sp.om;
-  const double wp = twom * cp, wx = twom * cx;     // 2 w c+, 2 w cx
-  double wdH = 0.0, wdT = 0.0;
+  for (int q = 0; q < 4; ++q)
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    if (j >= sc.n_eff) break;
-    const double(*C)[5] = sc.jk[j];
-    double y0, y1, y2h, y3h;
-    trig_val_dHH(C[0], sp, y0, y2h);
-    trig_val_dHH(C[1], sp, y1, y3h);
-    const double y2 = trig_dH(C[0], sp), y3 = trig_dH(C[1], sp);
-    const double y4 = trig_val(C[2], sp), y5 = trig_val(C[3], sp);
-    const double tgr = fma(ap.gX[kXv0], y0, fma(rg1, y1, fma(ap.cpgg, y2, ap.cpg3 * y4)));
-    const double ter = fma(ae.xx[xx_index(kXe3, kXv0)], y0, fma(re1, y1, fma(ap.cpg3, y2, ae.cpx33 * y4)));
-    const double tgi = fma(ig0, y0, fma(ap.gX[kXw1], y1, fma(ap.cxgg, y3, ap.cxg3 * y5)));
-    const double tei = fma(ie0, y0, fma(ae.xx[xx_index(kXe3, kXw1)], y1, fma(ap.cxg3, y3, ae.cxx33 * y5)));
-    const double hy0 = fma(h00, y0, fma(h01, y1, fma(ap.h02, y2, fma(h03, y3, fma(ae.h04, y4, h05 * y5)))));
-    const double hy1 = fma(h01, y0, fma(h11, y1, fma(h12, y2, fma(ap.h13, y3, fma(h14, y4, ae.h15 * y5)))));
-    // the point's Gbar-weighted quadratic form, and its gradient in y (times 2 w)
-    const double J = fma(y0, hy0, fma(y1, hy1, fma(cp, fma(y2, tgr, y4 * ter), cx * fma(y3, tgi, y5 * tei))));
-    const double g0 = twom * hy0, g1 = twom * hy1;
-    const double g2 = wp * tgr, g3 = wx * tgi, g4 = wp * ter, g5 = wx * tei;
-    // Q = (c+ y0, cx y1); the arrival-time derivatives' adjoints (times 1/tf)
-    const double Qr = cp * y0, Qi = cx * y1;
-    wdH = fma(twom, fma(Qr, tgi, -Qi * tgr), wdH);
-    wdT = fma(twom, fma(Qr, tei, -Qi * ter), wdT);
-    // SNR^2 = sum w |Q|^2 and its gradient in (y0, y1)
-    const double q2 = fma(Qr, Qr, Qi * Qi);
-    const double s0 = wp * Qr, s1 = wx * Qi;
-    // longitude (= hour angle): y0' = y2, y1' = y3
-    const double y4h = trig_dH(C[2], sp), y5h = trig_dH(C[3], sp);
-    acc[kAdjT + 1] = fma(g0, y2, fma(g1, y3, fma(g2, y2h, fma(g3, y3h, fma(g4, y4h, fma(g5, y5h, acc[kAdjT + 1]))))));
-    acc[kAdjS + 1] = fma(s0, y2, fma(s1, y3, acc[kAdjS + 1]));
-    // latitude
-    {
-      const double(*L)[5] = as.jl[j];
-      const double l0 = trig_val(L[0], sp), l1 = trig_val(L[1], sp);
-      const double l2 = trig_dH(L[0], sp), l3 = trig_dH(L[1], sp);
-      const double l4 = trig_val(L[2], sp), l5 = trig_val(L[3], sp);
-      acc[kAdjT + 0] = fma(g0, l0, fma(g1, l1, fma(g2, l2, fma(g3, l3, fma(g4, l4, fma(g5, l5, acc[kAdjT + 0]))))));
-      acc[kAdjS + 0] = fma(s0, l0, fma(s1, l1, acc[kAdjS + 0]));
+    for (int k = 0; k < 5; ++k) r.c[q][k] = p[q][k];
+  return r;
+}
+
+// The sites' contributions at NQ points, out(s, t[kAdjN]) for each.  The basis
+// carries the root weight (trig_basis), as in the forward pass.
+template <int NQ, bool TAB, bool AHEAD, class OUT>
+__host__ __device__ inline void adjoint_sites(const AdjEventC& ae, const SiteC* scs, const AdjSiteC* ass, int n_site,
+                                              const AdjPoint (&ap)[NQ], OUT out) {
+  SiteHead hd = site_head(scs[0]);
+  for (int site = 0; site < n_site; ++site) {
+    const SiteC& sc = scs[site];
+    const AdjSiteC& as = ass[site];
+    const double cp = ae.cpl, cx = ae.ccr;
+    const double ev0 = ae.xx[xx_index(kXe3, kXv0)], ew1 = ae.xx[xx_index(kXe3, kXw1)];
+    const double ee = ae.xx[xx_index(kXe3, kXe3)];
+    const int n_eff = sc.n_eff;
+    Poly4 c = poly4(sc.jk[0]);
+    if (AHEAD) loads_ahead();
+    SiteTrigR sp[NQ];
+    double tc[NQ], ts[NQ], wu[NQ], ww[NQ];   // 2 pi f (cos H, sin H); adjoints of u and w (halved)
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const Point& q = ap[i].q;
+      const double cH = q.cth * hd.cdl - q.sth * hd.sdl;
+      const double sH = q.sth * hd.cdl + q.cth * hd.sdl;
+      const double r = TAB ? psd_root_weight<TAB>(sc, q) : psd_root_of(hd.x2_fac, hd.xpS0, hd.m5S0, hd.k111S0, q);
+      trig_basis(cH, sH, r, sp[i]);
+      tc[i] = q.tf * cH;
+      ts[i] = q.tf * sH;
+      sp[i].u = -hd.k1 * ts[i];
+      sp[i].w = fma(hd.k1t, tc[i], q.tf * hd.k0t);
+      wu[i] = ww[i] = 0.0;
     }
-    // gamma
-    {
-      const double(*G)[5] = as.jg[j];
-      const double l0 = trig_val(G[0], sp), l1 = trig_val(G[1], sp);
-      const double l2 = trig_dH(G[0], sp), l3 = trig_dH(G[1], sp);
-      const double l4 = trig_val(G[2], sp), l5 = trig_val(G[3], sp);
-      acc[kAdjT + 2] = fma(g0, l0, fma(g1, l1, fma(g2, l2, fma(g3, l3, fma(g4, l4, fma(g5, l5, acc[kAdjT + 2]))))));
-      acc[kAdjS + 2] = fma(s0, l0, fma(s1, l1, acc[kAdjS + 2]));
+    double t[kAdjN] = {};
+    for (int j = 0; j < n_eff; ++j) {      // none where the duty factor turns the whole site off
+      if (j > 0) c = poly4(sc.jk[j]);
+      Poly4 d = poly4(as.jl[j]);
+      if (AHEAD) loads_ahead();
+      // half the gradients of J in the coefficients of the four polynomials,
+      // and of SNR^2/2 in those of the first two (over c+ and cx)
+      double m[4][5] = {}, s[2][5] = {};
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) {
+        const AdjPoint& a = ap[i];
+        const SiteTrigR& b = sp[i];
+        const double y0 = trig_val_r(c.c[0], b), y1 = trig_val_r(c.c[1], b);
+        const double y2 = trig_dH_r(c.c[0], b), y3 = trig_dH_r(c.c[1], b);
+        const double Qr = cp * y0, Qi = cx * y1;
+        const double Zr = fma(cp, y2, -b.u * Qi);
+        const double Zi = fma(cx, y3, b.u * Qr);
+        const double Yr = fma(cp, trig_val_r(c.c[2], b), -b.w * Qi);
+        const double Yi = fma(cx, trig_val_r(c.c[3], b), b.w * Qr);
+        const double h0 = fma(a.k00, y0, fma(a.k01, y1, fma(a.gv0, Zr, fma(a.gm, Zi, fma(ev0, Yr, a.em * Yi)))));
+        const double h1 = fma(a.k01, y0, fma(a.k11, y1, fma(a.gr, Zr, fma(a.gw1, Zi, fma(a.er, Yr, ew1 * Yi)))));
+        const double hzr = fma(a.gv0, y0, fma(a.gr, y1, fma(a.gg, Zr, a.g3 * Yr)));
+        const double hzi = fma(a.gm, y0, fma(a.gw1, y1, fma(a.gg, Zi, a.g3 * Yi)));
+        const double hyr = fma(ev0, y0, fma(a.er, y1, fma(a.g3, Zr, ee * Yr)));
+        const double hyi = fma(a.em, y0, fma(ew1, y1, fma(a.g3, Zi, ee * Yi)));
+        t[kAdjT + 3] -= fma(y0, h0, fma(y1, h1, fma(Zr, hzr, fma(Zi, hzi, fma(Yr, hyr, Yi * hyi)))));
+        t[kAdjW] = fma(Qr, Qr, fma(Qi, Qi, t[kAdjW]));
+        wu[i] = fma(Qr, hzi, fma(-Qi, hzr, wu[i]));
+        ww[i] = fma(Qr, hyi, fma(-Qi, hyr, ww[i]));
+        const double g0 = fma(cp, fma(b.u, hzi, b.w * hyi), h0);
+        const double g1 = fma(-cx, fma(b.u, hzr, b.w * hyr), h1);
+        const double g2 = cp * hzr, g3 = cx * hzi, g4 = cp * hyr, g5 = cx * hyi;
+        if (NQ == 1) {
+          // one point: each direction's polynomials themselves
+          auto along = [&](double l0, double l1, double l2, double l3, double l4, double l5, double& T, double& S) {
+            T = fma(g0, l0, fma(g1, l1, fma(g2, l2, fma(g3, l3, fma(g4, l4, fma(g5, l5, T))))));
+            S = fma(cp * Qr, l0, fma(cx * Qi, l1, S));
+          };
+          // the second H derivative: -(c1 cos H + c2 sin H + 4 (c3 cos 2H + c4 sin H cos H))
+          auto dHH = [&](const double* C) {
+            return -fma(4.0, fma(C[4], b.rsc, C[3] * b.rc2), fma(C[2], b.rs, C[1] * b.rc));
+          };
+          along(y2, y3, dHH(c.c[0]), dHH(c.c[1]), trig_dH_r(c.c[2], b), trig_dH_r(c.c[3], b), t[kAdjT + 1],
+                t[kAdjS + 1]);
+          along(trig_val_r(d.c[0], b), trig_val_r(d.c[1], b), trig_dH_r(d.c[0], b), trig_dH_r(d.c[1], b),
+                trig_val_r(d.c[2], b), trig_val_r(d.c[3], b), t[kAdjT + 0], t[kAdjS + 0]);
+          const Poly4 dg = poly4(as.jg[j]);
+          along(trig_val_r(dg.c[0], b), trig_val_r(dg.c[1], b), trig_dH_r(dg.c[0], b), trig_dH_r(dg.c[1], b),
+                trig_val_r(dg.c[2], b), trig_val_r(dg.c[3], b), t[kAdjT + 2], t[kAdjS + 2]);
+          continue;
+        }
+        // two points or more: the coefficients' gradients, summed over them
+        const double bv[5] = {b.r, b.rc, b.rs, b.rc2, b.rsc};
+        const double bd[5] = {0.0, -b.rs, b.rc, b.rm4, b.rc2};
+        m[0][0] = fma(g0, bv[0], m[0][0]);
+        m[1][0] = fma(g1, bv[0], m[1][0]);
+#pragma unroll
+        for (int k = 1; k < 5; ++k) {
+          m[0][k] = fma(g0, bv[k], fma(g2, bd[k], m[0][k]));
+          m[1][k] = fma(g1, bv[k], fma(g3, bd[k], m[1][k]));
+        }
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+          m[2][k] = fma(g4, bv[k], m[2][k]);
+          m[3][k] = fma(g5, bv[k], m[3][k]);
+          s[0][k] = fma(Qr, bv[k], s[0][k]);
+          s[1][k] = fma(Qi, bv[k], s[1][k]);
+        }
+      }
+      if (NQ == 1) continue;
+      // longitude: d/dH of c0 + c1 cos H + c2 sin H + c3 cos 2H + c4 sin H cos H
+      // has the coefficients (0, c2, -c1, c4, -4 c3)
+      double S1[2];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        double& T = t[kAdjT + 1];
+        const double* C = c.c[q];
+        T = fma(C[2], m[q][1], fma(-C[1], m[q][2], fma(C[4], m[q][3], fma(C[3], -4.0 * m[q][4], T))));
+        if (q < 2) S1[q] = fma(C[2], s[q][1], fma(-C[1], s[q][2], fma(C[4], s[q][3], C[3] * (-4.0 * s[q][4]))));
+      }
+      t[kAdjS + 1] = fma(cp, S1[0], fma(cx, S1[1], t[kAdjS + 1]));
+      // latitude and gamma: the directions' coefficients
+      auto along = [&](const Poly4& d, double& T, double& S) {
+        double x = 0.0, y = 0.0;
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) T = fma(d.c[q][k], m[q][k], T);
+          x = fma(d.c[0][k], s[0][k], x);
+          y = fma(d.c[1][k], s[1][k], y);
+        }
+        S = fma(cp, x, fma(cx, y, S));
+      };
+      const Poly4 dg = poly4(as.jg[j]);
+      if (AHEAD) loads_ahead();
+      along(d, t[kAdjT + 0], t[kAdjS + 0]);
+      along(dg, t[kAdjT + 2], t[kAdjS + 2]);
     }
-    acc[kAdjT + 3] = fma(-om, J, acc[kAdjT + 3]);
-    acc[kAdjW] = fma(om, q2, acc[kAdjW]);
+    // arrival-time derivatives: dDelta/dH = -k1 sin H, dDelta/dth = k1t cos H + k0t
+    //   d/dH:   d(dDelta/dH) = -k1 cos H,      d(dDelta/dth) = -k1t sin H
+    //   d/dlat: d(dDelta/dH) = -k1l sin H,     d(dDelta/dth) = k1tl cos H + k0tl
+    const double k1 = sc.k1, k1t = sc.k1t, k1l = as.k1l, k1tl = as.k1tl, k0tl = as.k0tl;
+    hd = site_head(scs[site + 1 < n_site ? site + 1 : site]);
+    if (AHEAD) loads_ahead();
+    double uc = 0.0, us = 0.0, wc = 0.0, ws = 0.0, w1 = 0.0;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      uc = fma(wu[i], tc[i], uc);
+      us = fma(wu[i], ts[i], us);
+      wc = fma(ww[i], tc[i], wc);
+      ws = fma(ww[i], ts[i], ws);
+      w1 = fma(ww[i], ap[i].q.tf, w1);
+    }
+    t[kAdjT + 1] = fma(-k1, uc, fma(-k1t, ws, t[kAdjT + 1]));
+    t[kAdjT + 0] = fma(-k1l, us, fma(k1tl, wc, fma(k0tl, w1, t[kAdjT + 0])));
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      t[kAdjT + i] *= 2.0;
+      t[kAdjS + i] *= 2.0;
+    }
+    out(site, t);
   }
-  // arrival-time derivatives: dDelta/dH = -k1 sin H, dDelta/dth = k1t cos H + k0t
-  //   d/dH:   d(dDelta/dH) = -k1 cos H,      d(dDelta/dth) = -k1t sin H
-  //   d/dlat: d(dDelta/dH) = -k1l sin H,     d(dDelta/dth) = k1tl cos H + k0tl
-  acc[kAdjT + 1] += tf * fma(wdH, -sc.k1 * sp.cH, -wdT * sc.k1t * sp.sH);
-  acc[kAdjT + 0] += tf * fma(wdH, -as.k1l * sp.sH, wdT * fma(as.k1tl, sp.cH, as.k0tl));
 }
 
 // One grid point and one site (host checks).
 template <int NPI, bool ROT>
 __host__ __device__ inline void adjoint_point(const EventC& ec, const AdjEventC& ae, const SiteC& sc,
                                               const AdjSiteC& as, int32_t k, double* acc) {
-  AdjPoint ap;
-  adjoint_point_setup<NPI, ROT>(ec, ae, k, ap);
-  adjoint_site<true>(ae, sc, as, ap, acc);
+  AdjPoint ap[1];
+  adjoint_point_setup<NPI, ROT, 1>(ec, ae, {k}, ap);
+  adjoint_sites<1, true, false>(ae, &sc, &as, 1, ap, [&](int, const double (&t)[kAdjN]) {
+    for (int i = 0; i < kAdjN; ++i) acc[i] += t[i];
+  });
 }
 
 }  // namespace gwf

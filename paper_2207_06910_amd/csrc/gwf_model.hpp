@@ -132,7 +132,6 @@ struct SiteC {
   union { double ix2_fac, tab_a; };
   union { double x2_fac, tab_b; };
   double xp_fac;               // (f/f0)^-4.14 = xp_fac v^-12.42
-  double S0inv;                // 1/S0
   // S0 times the PSD shape's coefficients of v^-12.42, v^-6 and the rational
   // part (the root weight's form, see psd_root_weight), and sqrt(1/S0)
   // (a sampled curve: the ends of its range)
@@ -638,11 +637,10 @@ __host__ __device__ inline void site_setup(const double* p, const SiteDesc& sd, 
   const double ix_fac = sd.f0 * piM;          // f0/f = ix_fac v^-3
   sc.ix2_fac = ix_fac * ix_fac;
   sc.x2_fac = 1.0 / sc.ix2_fac;
-  sc.S0inv = 1.0 / sd.S0;
   sc.xpS0 = sd.S0 * sc.xp_fac;
   sc.m5S0 = -5.0 * sd.S0 * sc.ix2_fac;
   sc.k111S0 = 111.0 * sd.S0;
-  sc.rS0inv = sqrt(sc.S0inv);
+  sc.rS0inv = sqrt(1.0 / sd.S0);
   sc.tab_f = sd.tab_f;
   sc.tab_S = sd.tab_S;
   sc.tab_n = sd.tab_n;
@@ -1018,20 +1016,6 @@ __host__ __device__ inline void phase_only_coefficients(const EventC& ec, const 
   if (PO::ecc) c[NPI - 1] = ec.ecc_e0 * q.ecv;
 }
 
-__host__ __device__ inline double psd_weight_of(double xp_fac, double ix2_fac, double x2_fac, double S0inv,
-                                                const Point& q) {
-  // S_n = S0 [x^-4.14 - 5 x^-2 + 111 (1 - x^2 + x^4/2)/(1 + x^2/2)], x = f/f0;
-  // x^-4.14 = xp_fac v^-12.42 with the power of v evaluated once per point
-  const double xp = xp_fac * q.vpsd;
-  const double ix2 = ix2_fac * q.iv6;              // (f0/f)^2
-  const double x2 = x2_fac * q.v6;                 // (f/f0)^2
-  const double num = fma(0.5 * x2, x2, 1.0 - x2);
-  const double den = fma(0.5, x2, 1.0);
-  // shape = [(x^-4.14 - 5 x^-2) den + 111 num] / den
-  const double top = fma(fma(-5.0, ix2, xp), den, 111.0 * num);
-  return q.w4A2 * S0inv * den * recip(top);
-}
-
 // A sampled noise curve at f (sec. 3.1, a PSD or ASD file): the PSD between
 // two samples on the straight line through them (an ASD squared at the samples
 // first), not yet scaled by S0; false outside the sampled range.  Where the
@@ -1083,42 +1067,36 @@ __host__ __device__ inline bool table_psd(const SiteC& sc, const Point& q, doubl
   return true;
 }
 
-// The weight 4 w A^2 / S_n(f) with a sampled curve, and its square root; zero
+// The square root of the weight 4 w A^2 / S_n(f) with a sampled curve; zero
 // outside the sampled range.
-__host__ __device__ inline double table_weight(const SiteC& sc, const Point& q) {
-  double S;
-  return table_psd(sc, q, S) ? q.w4A2 * sc.S0inv / S : 0.0;
-}
 __host__ __device__ inline double table_root_weight(const SiteC& sc, const Point& q) {
   double S;
   return table_psd(sc, q, S) ? (q.rw * sc.rS0inv) * rsqrt_d(S) : 0.0;
-}
-
-// TAB = false: instantiations for networks without sampled curves, which
-// leave the check out of the per-point code.
-template <bool TAB = true>
-__host__ __device__ inline void psd_weight(const SiteC& sc, const Point& q, double& om) {
-  if (TAB && sc.tab_kind) om = table_weight(sc, q);
-  else om = psd_weight_of(sc.xp_fac, sc.ix2_fac, sc.x2_fac, sc.S0inv, q);
 }
 
 // The square root of the weight, r = sqrt(4 w A^2 / S_n(f)), which the
 // Fisher kernels fold into the pattern values: every Fisher entry is a sum of
 // w Re(D_a D_b^*), bilinear in the derivative vectors, and those are linear
 // in the pattern values, so the weighted sums follow from r D with no
-// per-entry weight product.  With S_n = S0 top / den (psd_weight_of),
+// per-entry weight product.  S_n = S0 [x^-4.14 - 5 x^-2
+// + 111 (1 - x^2 + x^4/2)/(1 + x^2/2)], x = f/f0, = S0 top / den, and
 // r = sqrt(4 w A^2) den / sqrt(den S0 top); S0 top is formed from the site's
 // S0-scaled coefficients, so 1/S0 costs nothing per point.  A sampled curve
-// takes the root of the full weight.
+// takes the root of the full weight.  TAB = false: instantiations for networks
+// without sampled curves, which leave the check out of the per-point code.
+__host__ __device__ inline double psd_root_of(double x2_fac, double xpS0, double m5S0, double k111S0, const Point& q) {
+  const double x2 = x2_fac * q.v6;                 // (f/f0)^2
+  const double num = fma(fma(0.5, x2, -1.0), x2, 1.0);
+  const double den = fma(0.5, x2, 1.0);
+  const double topS = fma(fma(m5S0, q.iv6, xpS0 * q.vpsd), den, k111S0 * num);
+  return (q.rw * den) * rsqrt_d(den * topS);
+}
+
 template <bool TAB = true>
 __host__ __device__ inline double psd_root_weight(const SiteC& sc, const Point& q) {
   if (TAB && sc.tab_kind)
     return table_root_weight(sc, q);
-  const double x2 = sc.x2_fac * q.v6;              // (f/f0)^2
-  const double num = fma(fma(0.5, x2, -1.0), x2, 1.0);
-  const double den = fma(0.5, x2, 1.0);
-  const double topS = fma(fma(sc.m5S0, q.iv6, sc.xpS0 * q.vpsd), den, sc.k111S0 * num);
-  return (q.rw * den) * rsqrt_d(den * topS);
+  return psd_root_of(sc.x2_fac, sc.xpS0, sc.m5S0, sc.k111S0, q);
 }
 
 // The same root with the PSD shape in FP32 (mixed form).  The weight is a
@@ -1142,31 +1120,6 @@ __host__ __device__ inline double psd_root_weight_f32(const SiteC& sc, const Poi
   const float den = fmaf(0.5f, x2, 1.0f);
   const float top = fmaf(fmaf(-5.0f, ix2, xp), den, 111.0f * num);
   return (q.rw * sc.rS0inv) * (double)sqrtf_hw(den * recipf(top));
-}
-
-// Site-level quantities of the Fisher kernels at one frequency for the
-// trigonometric form of the patterns (SiteC::jk): cos H, sin H, cos 2H,
-// sin H cos H and the factor -4 sin H cos H of the cos 2H term's H derivative
-// (that of sin H cos H is cos 2H); the arrival-time derivatives and the noise
-// weight.
-struct SiteTrig {
-  double cH, sH, c2H, sc, m4;
-  double dH, dT;      // dDelta/dH, dDelta/dtheta
-  double om;          // 4 w A^2 / S_n(f)
-};
-
-template <bool TAB = true>
-__host__ __device__ inline void site_trig(const SiteC& sc, const Point& q, SiteTrig& sp) {
-  const double cH = q.cth * sc.cdl - q.sth * sc.sdl;
-  const double sH = q.sth * sc.cdl + q.cth * sc.sdl;
-  sp.cH = cH;
-  sp.sH = sH;
-  sp.c2H = fma(cH, cH, -sH * sH);
-  sp.sc = sH * cH;
-  sp.m4 = -4.0 * sp.sc;
-  psd_weight<TAB>(sc, q, sp.om);
-  sp.dH = -sc.k1 * sH;
-  sp.dT = fma(sc.k1t, cH, sc.k0t);
 }
 
 // The Fisher kernels' site quantities: the patterns' trigonometric basis
@@ -1198,22 +1151,13 @@ __host__ __device__ inline void site_trig_root(const SiteC& sc, const Point& q, 
 }
 
 // r times a trigonometric polynomial of SiteC::jk, and r times its H
-// derivative (the constant term last, as in trig_val).
+// derivative (the constant term last: the coefficients sit in scalar registers,
+// and as the first addend it would need copying into vector registers).
 __host__ __device__ inline double trig_val_r(const double c[5], const SiteTrigR& sp) {
   return fma(c[0], sp.r, fma(c[4], sp.rsc, fma(c[3], sp.rc2, fma(c[2], sp.rs, c[1] * sp.rc))));
 }
 __host__ __device__ inline double trig_dH_r(const double c[5], const SiteTrigR& sp) {
   return fma(c[4], sp.rc2, fma(c[3], sp.rm4, fma(c[2], sp.rc, -c[1] * sp.rs)));
-}
-
-// A trigonometric polynomial of SiteC::jk at the point, and its H derivative.
-// The constant term is added last: the coefficients sit in scalar registers,
-// and as the first addend it would need copying into vector registers.
-__host__ __device__ inline double trig_val(const double c[5], const SiteTrig& sp) {
-  return fma(c[4], sp.sc, fma(c[3], sp.c2H, fma(c[2], sp.sH, c[1] * sp.cH))) + c[0];
-}
-__host__ __device__ inline double trig_dH(const double c[5], const SiteTrig& sp) {
-  return fma(c[4], sp.c2H, fma(c[3], sp.m4, fma(c[2], sp.cH, -c[1] * sp.sH)));
 }
 
 // The event's amplitude factors that enter the derivative vectors.

@@ -40,9 +40,14 @@ struct gwf_plan {
   int32_t* item_first = nullptr;
   double* partial = nullptr;
   size_t items_cap = 0;
-  // the adjoint's constants (allocated by the first gwf_plan_adjoint)
+  // the adjoint's constants and, where it splits the events finer than chunk,
+  // its work items (allocated by the first gwf_plan_adjoint)
   AdjEventC* aec = nullptr;
   AdjSiteC* asc = nullptr;
+  Item* adj_items = nullptr;
+  int32_t* adj_first = nullptr;
+  double* adj_partial = nullptr;
+  int adj_n_items = 0;
   int64_t workspace_bytes = 0;
   // graph cache, keyed by the output pointers of the last replay
   hipStream_t cap = nullptr;
@@ -104,6 +109,47 @@ gwf_status set_items(gwf_plan* p, int chunk) {
   p->chunk = chunk;
   p->n_items = (int)items.size();
   return GWF_OK;
+}
+
+// The adjoint's own work items where the plan's are too long for it: its
+// workgroups have 128 lanes, 1024 of them run at once, and a plan's chunk is
+// chosen for the forward kernels, which the whole chip takes 512 lanes a
+// compute unit of.  The events are cut so that about three rounds of
+// workgroups cover the points (the last round's idle share stays small), in
+// lengths of 1024 points and more (a shorter item does not pay for its zeroed
+// and reduced columns).  Mixed events on five sites, adjoint with the plan's
+// items / with its own: 100 events 0.26 / 0.16 ms, 1000 0.87 / 0.62 ms, 1500
+// 1.20 / 0.88 ms; units of 512 points 0.18 ms at 100 events; two or six rounds
+// 0.66 and 0.65 ms at 1000.  From about 5e7 points on (10^4 events) the plan's
+// items are short enough and are taken as they are.
+// Without memory for its own items the adjoint takes the plan's.
+constexpr int64_t kAdjointGroups = 3072, kAdjointUnit = 1024;
+void split_adjoint(gwf_plan* p) {
+  int64_t points = 0;
+  for (int32_t n : p->npts_host) points += n >= 2 ? n : 2;
+  const int64_t len = (points / kAdjointGroups / kAdjointUnit + 1) * kAdjointUnit;
+  if (len >= p->chunk) return;
+  std::vector<Item> items;
+  std::vector<int32_t> first;
+  build_items(p->npts_host, (int)len, items, first);
+  const size_t width = (size_t)p->n_site_alloc * 8;
+  int64_t bytes = 0;
+  if (dev_alloc(&p->adj_items, items.size(), bytes) == hipSuccess &&
+      dev_alloc(&p->adj_first, first.size(), bytes) == hipSuccess &&
+      dev_alloc(&p->adj_partial, items.size() * width, bytes) == hipSuccess &&
+      hipMemcpy(p->adj_items, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice) == hipSuccess &&
+      hipMemcpy(p->adj_first, first.data(), first.size() * sizeof(int32_t), hipMemcpyHostToDevice) == hipSuccess) {
+    p->adj_n_items = (int)items.size();
+    p->workspace_bytes += bytes;
+    return;
+  }
+  (void)hipGetLastError();
+  (void)hipFree(p->adj_items);
+  (void)hipFree(p->adj_first);
+  (void)hipFree(p->adj_partial);
+  p->adj_items = nullptr;
+  p->adj_first = nullptr;
+  p->adj_partial = nullptr;
 }
 
 struct Outs {
@@ -173,7 +219,8 @@ void free_plan(gwf_plan* p) {
   if (p->ev0) (void)hipEventDestroy(p->ev0);
   if (p->ev1) (void)hipEventDestroy(p->ev1);
   for (void* q : {(void*)p->evc, (void*)p->sic, (void*)p->npts_plan, (void*)p->items, (void*)p->item_first,
-                  (void*)p->partial, (void*)p->aec, (void*)p->asc})
+                  (void*)p->partial, (void*)p->aec, (void*)p->asc,
+                  (void*)p->adj_items, (void*)p->adj_first, (void*)p->adj_partial})
     (void)hipFree(q);
   delete p;
 }
@@ -358,6 +405,7 @@ gwf_status gwf_plan_adjoint(gwf_plan* p, const double* gbar, const int32_t* stat
       return api_fail(GWF_E_NOMEM, "adjoint constants of %lld events", (long long)p->n);
     }
     p->workspace_bytes += (int64_t)((size_t)p->n * (adjoint_event_bytes() + p->n_site_alloc * adjoint_site_bytes()));
+    split_adjoint(p);
   }
   err = launch_setup(sa, s);
   if (err == hipSuccess) {
@@ -370,12 +418,16 @@ gwf_status gwf_plan_adjoint(gwf_plan* p, const double* gbar, const int32_t* stat
   if (err == hipSuccess) {
     AdjItemsArgs aa{};
     aa.net = p->net; aa.evc = p->evc; aa.sic = p->sic; aa.aec = p->aec; aa.asc = p->asc;
-    aa.items = p->items; aa.n_items = p->n_items; aa.partial = p->partial;
+    aa.items = p->adj_items ? p->adj_items : p->items;
+    aa.n_items = p->adj_items ? p->adj_n_items : p->n_items;
+    aa.partial = p->adj_items ? p->adj_partial : p->partial;
     err = launch_adjoint_items(aa, p->npi, p->rot, s);
   }
   if (err == hipSuccess) {
     AdjCombineArgs ca{};
-    ca.n = p->n; ca.n_site = p->net.n_site; ca.item_first = p->item_first; ca.partial = p->partial;
+    ca.n = p->n; ca.n_site = p->net.n_site;
+    ca.item_first = p->adj_items ? p->adj_first : p->item_first;
+    ca.partial = p->adj_items ? p->adj_partial : p->partial;
     ca.w_snr = w_snr; ca.w_fisher = w_fisher; ca.grad_event = grad_event; ca.grad = grad;
     err = launch_adjoint_combine(ca, s);
   }
