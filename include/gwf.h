@@ -326,6 +326,20 @@ gwf_status gwf_fisher_adjoint(const gwf_events* ev, const gwf_network* net, cons
                               double w_snr, double w_fisher, double* grad_event, double* grad,
                               void* stream);
 
+/* The value of a figure of merit, w_snr sum_e ln SNR_e + w_logdet sum_e
+ * ln det Gamma_e over the events with status 0, and the Gbar of its gradient
+ * (gwf_fisher_adjoint): the covariances of the rows set in `rows` (bit i row i
+ * of P) embedded in the full matrix, zero elsewhere.
+ *   snr, logdet, status  device [n] (status as gwf_covariance leaves it)
+ *   cov   device [Po][Po][n], Po the number of rows; required with gbar
+ *   gbar  device [P][P][n] or NULL
+ *   work  device [GWF_FOM_WORK], overwritten
+ *   J     device [1], summed in a fixed order (bitwise reproducible) */
+#define GWF_FOM_WORK 512
+gwf_status gwf_fom(int32_t P, int64_t n, uint32_t rows, const double* snr, const double* logdet,
+                   const int32_t* status, const double* cov, double w_snr, double w_logdet, double* gbar,
+                   double* work, double* J, void* stream);
+
 /* Batched FP64 inversion (sec. 4.1) of n Fisher matrices of size P
  * (1 <= P <= 13) in the [P][P][n] layout: each matrix is normalised by the
  * square root of its diagonal (skipped when a diagonal entry is not > 0),
@@ -564,9 +578,11 @@ gwf_status gwf_plan_fisher(gwf_plan* plan, double* fisher, double* snr, int32_t*
  * (one stream, or synchronised).  The first call on a plan allocates the
  * adjoint's constants (the contractions of each event's Gbar, about 1 KB per
  * event, and each site's pattern-derivative polynomials, about 0.7 KB per
- * event and site), kept with the plan until gwf_plan_destroy and counted in
- * gwf_plan_info's workspace_bytes; later calls allocate nothing.  Returns
- * GWF_E_NOMEM if that allocation fails. */
+ * event and site), and shorter work items of the adjoint's own where the
+ * plan's would leave it few, kept with the plan until gwf_plan_destroy and
+ * counted in gwf_plan_info's workspace_bytes; later calls allocate nothing.
+ * Returns GWF_E_NOMEM if the constants cannot be allocated (without memory for
+ * its own items it takes the plan's). */
 gwf_status gwf_plan_adjoint(gwf_plan* plan, const double* gbar, const int32_t* status, double w_snr,
                             double w_fisher, double* grad_event, double* grad, void* stream);
 

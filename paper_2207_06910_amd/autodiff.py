@@ -15,8 +15,8 @@ gwf_covariance (which returns ln det Gamma and Gamma^-1); the backward pass
 runs the hand-written adjoint gwf_fisher_adjoint (or gwf_plan_adjoint) with
 Gbar = Gamma^-1 embedded in the full matrix, recomputing the strain
 derivatives at every grid point instead of storing them.  Every per-point
-and per-event step runs in the library's kernels; this module only moves
-tensors and adds the per-event values.
+and per-event step and the sum over events (gwf_fom) run in the library's
+kernels; this module only moves tensors.
 """
 from __future__ import annotations
 
@@ -41,8 +41,7 @@ def site_parameters(dw):
                         dtype=torch.float64)
 
 
-def _forward(dw, xi, w_snr, w_logdet, rows, cond_max, plan=None):
-    import torch
+def _forward(dw, xi, w_snr, w_logdet, rows, cond_max, plan=None, want_gbar=False):
     dwx = dw.with_sites(_sites_at(dw.sites, xi))
     if plan is not None:              # the batched form: the plan's work items, network replaced
         plan.set_sites(dwx.sites)
@@ -55,9 +54,8 @@ def _forward(dw, xi, w_snr, w_logdet, rows, cond_max, plan=None):
     # parameter set (par_mask) is honoured by the inversion
     fixed = () if rows is None else [i for i in range(P) if i not in set(int(k) for k in rows)]
     inv = binding.covariance(F, r["status"], fixed=fixed, cond_max=cond_max, par_mask=dwx.par_mask)
-    ok = inv["status"] == 0
-    J = (w_snr * torch.log(r["snr"][ok]).sum() + w_logdet * inv["logdet"][ok].sum()).to(torch.float64)
-    return dwx, r, inv, ok, J
+    J, gbar = binding.fom_terms(r["snr"], inv, P, float(w_snr), float(w_logdet), want_gbar)
+    return dwx, inv, J, gbar
 
 
 class NetworkFoM(__import__("torch").autograd.Function):
@@ -65,15 +63,7 @@ class NetworkFoM(__import__("torch").autograd.Function):
 
     @staticmethod
     def forward(ctx, xi, dw, w_snr, w_logdet, rows, cond_max, plan):
-        import torch
-        dwx, r, inv, ok, J = _forward(dw, xi, w_snr, w_logdet, rows, cond_max, plan)
-        P = r["fisher"].shape[0]
-        gbar = inv["cov"]
-        if len(inv["out"]) != P:
-            full = torch.zeros((P, P, dw.n), dtype=torch.float64, device=gbar.device)
-            idx = torch.as_tensor(list(inv["out"]), dtype=torch.long, device=gbar.device)
-            full[idx.view(-1, 1), idx.view(1, -1)] = gbar
-            gbar = full
+        dwx, inv, J, gbar = _forward(dw, xi, w_snr, w_logdet, rows, cond_max, plan, want_gbar=True)
         ctx.dwx, ctx.gbar, ctx.status, ctx.plan = dwx, gbar, inv["status"], plan
         ctx.w = (float(w_snr), float(w_logdet))
         ctx.xi_device, ctx.xi_dtype = xi.device, xi.dtype
@@ -102,6 +92,5 @@ def network_fom(xi, dw, w_snr=1.0, w_logdet=1.0, rows=None, cond_max=1e13, plan=
 
 def network_fom_value(xi, dw, w_snr=1.0, w_logdet=1.0, rows=None, cond_max=1e13):
     """J(xi) without gradient bookkeeping, and the mask of events that entered."""
-    dwx, r, inv, ok, J = _forward(dw, xi, w_snr, w_logdet, None if rows is None else tuple(rows),
-                                  float(cond_max))
-    return J, ok
+    _, inv, J, _ = _forward(dw, xi, w_snr, w_logdet, None if rows is None else tuple(rows), float(cond_max))
+    return J, inv["status"] == 0

@@ -112,6 +112,9 @@ def load():
                                            ctypes.POINTER(Grid), ctypes.c_uint32, vp, vp, d, d,
                                            vp, vp, vp]
         lib.gwf_fisher_adjoint.restype = i32
+        lib.gwf_fom.argtypes = [i32, i64, ctypes.c_uint32, vp, vp, vp, vp, ctypes.c_double, ctypes.c_double, vp, vp,
+                                vp, vp]
+        lib.gwf_fom.restype = i32
         lib.gwf_plan_create.argtypes = [ctypes.POINTER(Events), ctypes.POINTER(Network),
                                         ctypes.POINTER(Grid), ctypes.c_uint32,
                                         ctypes.POINTER(PlanOptions), ctypes.POINTER(vp), vp]
@@ -468,6 +471,26 @@ def waveform_deriv(dw: DeviceWorkload, offsets=None, total=None, stream=None, ou
                                      _ptr(offsets), int(total), _ptr(dh), _ptr(res["status"]),
                                      _stream(stream)), "gwf_waveform_deriv")
     return res
+
+
+FOM_WORK = 512                  # GWF_FOM_WORK
+
+
+def fom_terms(snr, inv, P, w_snr, w_logdet, want_gbar=True, stream=None):
+    """gwf_fom: J = w_snr sum ln SNR + w_logdet sum ln det over the events
+    ``covariance`` left with status 0 (its result ``inv``), a float64 scalar
+    on the device, and the covariances embedded in [P][P][N] (those of all P
+    rows are returned as they are; None without want_gbar)."""
+    import torch
+    n, dev = snr.shape[0], snr.device
+    full = len(inv["out"]) == P
+    gbar = torch.empty((P, P, n), dtype=torch.float64, device=dev) if want_gbar and not full else None
+    work = torch.empty(FOM_WORK, dtype=torch.float64, device=dev)
+    J = torch.empty((), dtype=torch.float64, device=dev)
+    _check(load().gwf_fom(P, n, sum(1 << i for i in inv["out"]), _ptr(snr), _ptr(inv["logdet"]),
+                          _ptr(inv["status"]), _ptr(inv["cov"]) if gbar is not None else None, w_snr, w_logdet,
+                          _ptr(gbar), _ptr(work), _ptr(J), _stream(stream)), "gwf_fom")
+    return J, inv["cov"] if want_gbar and full else gbar
 
 
 def invert(F, status=None, cond_max=1e50, want_cov=True, par_mask=None, stream=None, out=None):

@@ -265,6 +265,23 @@ gwf_status gwf_fisher_adjoint(const gwf_events* ev, const gwf_network* net, cons
   return GWF_OK;
 }
 
+gwf_status gwf_fom(int32_t P, int64_t n, uint32_t rows, const double* snr, const double* logdet,
+                   const int32_t* status, const double* cov, double w_snr, double w_logdet, double* gbar,
+                   double* work, double* J, void* stream) {
+  if (P < 1 || P > GWF_NPAR_MAX) return api_fail(GWF_E_INVALID_ARG, "P=%d outside 1..%d", P, GWF_NPAR_MAX);
+  if (n < 0) return api_fail(GWF_E_INVALID_ARG, "n=%lld is negative", (long long)n);
+  if ((rows >> P) != 0) return api_fail(GWF_E_INVALID_ARG, "rows=0x%x of %d", rows, P);
+  if (!work || !J || (n > 0 && (!snr || !logdet || !status)) || (gbar && rows && !cov))
+    return api_fail(GWF_E_INVALID_ARG, "snr, logdet, status, work and J are required, and cov with gbar");
+  gwf::FomArgs a{};
+  a.n = n; a.P = P; a.Po = __builtin_popcount(rows); a.rows = rows;
+  a.snr = snr; a.logdet = logdet; a.status = status; a.cov = cov;
+  a.w_snr = w_snr; a.w_logdet = w_logdet; a.gbar = gbar; a.work = work; a.J = J;
+  hipError_t err = gwf::launch_fom(a, (hipStream_t)stream);
+  if (err != hipSuccess) return api_hip_fail(err, "figure-of-merit kernel launch");
+  return GWF_OK;
+}
+
 gwf_status gwf_invert(int32_t P, int64_t n, const double* fisher, double cond_max, double* cov,
                       double* sigma, double* cond, double* inv_err, double* logdet, int32_t* status,
                       void* stream) {

@@ -149,6 +149,24 @@ struct AdjointArgs {
   int64_t base;             // first event of the launch (set by the launcher)
 };
 
+// The value of a figure of merit from its events' SNR and ln det Gamma, and
+// the covariances embedded in the full matrix (rows: which of its rows they
+// are of, bit i row i).
+struct FomArgs {
+  int64_t n;
+  int P, Po;                // rows of the full matrix, of cov
+  uint32_t rows;
+  const double* snr;        // [n]
+  const double* logdet;     // [n]
+  const int32_t* status;    // [n]: events with a nonzero status are left out of J
+  const double* cov;        // [Po][Po][n], with gbar
+  double w_snr, w_logdet;
+  double* gbar;             // [P][P][n] or NULL
+  double* work;             // [2 kFomParts]
+  double* J;                // [1]
+};
+constexpr int kFomParts = 256;
+
 // npi: phase-only parameters, 3 + 2 (tides) + 1 (eccentricity)
 hipError_t launch_fisher(const FisherArgs& a, int npi, bool rot, hipStream_t stream);
 hipError_t launch_snr(const SnrArgs& a, bool rot, hipStream_t stream);
@@ -157,5 +175,6 @@ hipError_t launch_basis(const BasisArgs& a, int P, hipStream_t stream);
 hipError_t launch_waveform_deriv(const WaveformArgs& a, int npi, bool rot, hipStream_t stream);
 hipError_t launch_waveform(const WaveformArgs& a, bool tidal, bool rot, bool mixed, hipStream_t stream);
 hipError_t launch_adjoint(const AdjointArgs& a, int npi, bool rot, hipStream_t stream);
+hipError_t launch_fom(const FomArgs& a, hipStream_t stream);
 
 }  // namespace gwf
