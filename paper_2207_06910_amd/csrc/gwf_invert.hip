@@ -10,15 +10,28 @@
 // Sixteen lanes per matrix, lane j holding column j in registers; a
 // wavefront (one workgroup) works on four matrices.
 //
-// Condition number.  The |eigenvalues| of the symmetric normalised matrix
-// are its singular values, found by one-sided (Hestenes) Jacobi: at each
-// step the columns are paired by a round-robin schedule, each lane fetches
-// its partner's column through cross-lane permutes, and both lanes of a pair
-// compute the same rotation from bitwise identical inputs and update their
-// own column, so one step makes P/2 rotations with no further exchange.  For
-// a matrix with unit diagonal the singular values come out with relative
-// errors of order kappa u (Demmel and Veselic, SIAM J. Matrix Anal. Appl. 13,
-// 1992), the accuracy of a two-sided Jacobi on the same matrix.
+// Condition number.  The eigenvalues of a positive definite normalised matrix
+// G^ = L L^T are the squares of the singular values of L (its Cholesky factor,
+// formed for the inversion); of any other matrix, and where singular vectors
+// are wanted, the |eigenvalues| are the matrix's own singular values.  Either
+// are found by one-sided (Hestenes) Jacobi: at each step the columns are
+// paired by a round-robin schedule, each lane fetches its partner's column
+// (exchange_column), and both lanes of a pair compute the same rotation from
+// bitwise identical inputs and update their own column, so one step makes P/2
+// rotations with no further exchange.  For a matrix with unit diagonal the
+// singular values come out with relative errors of order kappa u (Demmel and
+// Veselic, SIAM J. Matrix Anal. Appl. 13, 1992), the accuracy of a two-sided
+// Jacobi on the same matrix; on L the sweeps see the square root of the
+// spread.  Sweeps until nothing rotates, the longest of four matrices: 7.2 on
+// L and 9.4 on G^ (13 x 13 with condition numbers of 20 to 6e4), 7.6 and 10.0
+// on BNS Fisher matrices (1e10 to 5e15); pivoting the factor would save 0.3
+// and cost a second factorisation.
+//
+// What bounds it: 10^4 matrices are 2500 wavefronts, 2 or 3 to a SIMD, each a
+// chain of about 94 steps; the LDS pipe carried the columns 73 % of the time
+// as 28 four-byte permutes a step, and as 14 sixteen-byte accesses 63 % of a
+// shorter time.  10^4 13 x 13 matrices: covariance and condition 179 us
+// before, 142 us in this form; one matrix 79 and 67 us.
 //
 // Inversion.  The Cholesky factorisation is right-looking over columns: at
 // step k the pivot lane's column is broadcast and every later column updates
@@ -81,28 +94,13 @@ __device__ inline void load_row(const InvertArgs& a, int64_t e, uint32_t am, int
   for (int k = 0; k < P; ++k) row[k] = gamma_rc(a, e, am, j, k);
 }
 
-// Column j of the normalised matrix (the kept upper triangle with the prior
-// on the diagonal, divided by d_i d_j), the same bits as the values the
-// kernel starts from; zeros where valid is false.
+// The condition number of the normalised matrix from the columns X of the
+// one-sided Jacobi on it or (factor) on its Cholesky factor, whose singular
+// values (the norms) are its eigenvalues' magnitudes or their square roots;
+// the ill-conditioned flag and whether the matrix is inverted by its Cholesky
+// factor.
 template <int P>
-__device__ inline void load_col(const InvertArgs& a, int64_t e, uint32_t am, int j, bool valid,
-                                const double* d, double dj, double* h) {
-#pragma unroll
-  for (int i = 0; i < P; ++i) {
-    double v = 0.0;
-    if (valid) {
-      const int r = i <= j ? i : j, c = i <= j ? j : i;
-      v = gamma_rc(a, e, am, r, c) / (d[i] * dj);
-    }
-    h[i] = v;
-  }
-}
-
-// The condition number of the normalised matrix from the columns X of its
-// one-sided Jacobi (the norms are its singular values), the ill-conditioned
-// flag and whether the matrix is inverted by its Cholesky factor.
-template <int P>
-__device__ inline void condition_of(const double* x, bool own, bool go0, bool pd, double cond_max,
+__device__ inline void condition_of(const double* x, bool factor, bool own, bool go0, bool pd, double cond_max,
                                     double& cond, bool& ill, bool& ok) {
   double smax = 0.0, smin = INFINITY;
   if (own) smax = smin = sqrt(col_dot<P>(x, x));
@@ -112,11 +110,51 @@ __device__ inline void condition_of(const double* x, bool own, bool go0, bool pd
     smin = fmin(smin, __shfl_xor(smin, off, kGroup));
   }
   cond = smin > 0.0 ? smax / smin : INFINITY;
+  if (factor) cond *= cond;
   ill = go0 && !(cond <= cond_max);
   ok = go0 && !ill && pd;
 }
 
 __device__ inline dd shfl_dd(dd v, int src) { return dd{__shfl(v.hi, src, kGroup), __shfl(v.lo, src, kGroup)}; }
+
+// Row length (doubles) of the columns the Jacobi exchanges through LDS: room
+// for a column and its norm, a multiple of 16 bytes, and an odd number of
+// those, so that the 16 rows of a matrix start in different banks.
+template <int P>
+constexpr int kExchangeLd = ((P + 2) / 2) % 2 ? (P + 2) / 2 * 2 : (P + 2) / 2 * 2 + 2;
+
+// Column q of the matrix into y and its squared norm into ny, from the lanes'
+// own columns x and norms nx: seven 16-byte writes and reads a lane at P = 13
+// in place of 28 four-byte permutes.  xs: the matrix's columns in LDS.  The
+// lanes of one wavefront exchange here, whose LDS operations are carried out
+// in order, so the reads see the writes before them without a wait.
+template <int P>
+__device__ inline void exchange_column(double* xs, int j, int q, const double* x, double nx, double* y, double& ny) {
+  constexpr int M = P + (P & 1), LDX = kExchangeLd<P>, N2 = (P + 2) / 2;
+  double v[2 * N2];
+#pragma unroll
+  for (int i = 0; i < 2 * N2; ++i) v[i] = i < P ? x[i] : i == P ? nx : 0.0;
+  if (j < M) {
+    double2* to = reinterpret_cast<double2*>(xs + j * LDX);
+#pragma unroll
+    for (int i = 0; i < N2; ++i) to[i] = double2{v[2 * i], v[2 * i + 1]};
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const double2* from = reinterpret_cast<const double2*>(xs + (q < M ? q : 0) * LDX);
+#pragma unroll
+  for (int i = 0; i < N2; ++i) {
+    const double2 w = from[i];
+    v[2 * i] = w.x;
+    v[2 * i + 1] = w.y;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int i = 0; i < P; ++i) y[i] = v[i];
+  ny = v[P];
+}
 
 // At least 3 waves per SIMD: left free, the compiler spends all 256 registers
 // on load scheduling and a SIMD runs one wave of this latency-bound kernel.
@@ -130,8 +168,10 @@ __global__ __launch_bounds__(kInvBlock, 3) void invert_kernel(InvertArgs a) {
   //       Gs[g][i], then Gamma again for the residual;
   //   Ls: column k of L at Ls[g][k] (1/L_kk on the diagonal), then column j
   //       of Cov at Ls[g][j].
-  __shared__ double Gs[kGroups][P][LD];
+  //   Xs: during the Jacobi, in Gs's place: column j and its squared norm.
+  __shared__ __align__(16) double GX[kGroups * (P * LD > M * kExchangeLd<P> ? P * LD : M * kExchangeLd<P>)];
   __shared__ double Ls[kGroups][P][LD];
+  double(*Gs)[P][LD] = reinterpret_cast<double(*)[P][LD]>(GX);
   const int lane = threadIdx.x;
   const int g = lane / kGroup, j = lane % kGroup;
   const int64_t e = a.base + xcd_block(blockIdx.x, gridDim.x) * kGroups + g;
@@ -207,54 +247,28 @@ __global__ __launch_bounds__(kInvBlock, 3) void invert_kernel(InvertArgs a) {
 #pragma unroll
   for (int off = kGroup / 2; off >= 1; off >>= 1) ld += __shfl_xor(ld, off, kGroup);
 
-  // ---- L^-1, column j by forward substitution
+  // L (and the normalisation, in the padding column) into LDS
   if (j < P) {
 #pragma unroll
     for (int i = 0; i < P; ++i)
       if (i >= j) Ls[g][j][i] = l[i];
-  }
-  __syncthreads();
-  double y[P];
-#pragma unroll
-  for (int i = 0; i < P; ++i) {
-    double s = 0.0;
-#pragma unroll
-    for (int k = 0; k < i; ++k) s = fma(Ls[g][k][i], y[k], s);   // y_k = 0 for k < j
-    const double inv_ii = Ls[g][i][i];
-    y[i] = i < j ? 0.0 : i == j ? inv_ii : -s * inv_ii;
-  }
-  if (j < P) {
-#pragma unroll
-    for (int k = 0; k < P; ++k) Gs[g][j][k] = y[k];
+    Ls[g][j][P] = dj;
   }
   __syncthreads();
 
-  // ---- C_ij for i <= j, undone normalisation, both triangles into LDS
-  if (j < P) {
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-      double s = 0.0;
-#pragma unroll
-      for (int k = i; k < P; ++k) s = fma(Gs[g][i][k], y[k], s);   // zero terms for k < j
-      if (i <= j) {
-        const double cij = s / (d[i] * dj);
-        Ls[g][j][i] = cij;
-        Ls[g][i][j] = cij;
-      }
-    }
-  }
-  __syncthreads();
-
-  // ---- condition number: one-sided Jacobi on the normalised columns
-  // (reloaded: the same bits as h).  A wavefront that holds a matrix the SVD
-  // below inverts, or whose eigen-decomposition is wanted, accumulates the
-  // rotations V as well (H V = X), so that the SVD needs no second Jacobi; X
-  // and the condition number come out the same either way.
+  // ---- condition number: one-sided Jacobi on the columns of the Cholesky
+  // factor, or of the normalised matrix where it has none.  A wavefront that
+  // holds a matrix the SVD below inverts, or whose eigen-decomposition is
+  // wanted, accumulates the rotations V as well (H V = X), so that the SVD
+  // needs no second Jacobi; X and the condition number come out the same
+  // either way.
   const bool want_eig = a.eigval != nullptr || a.eigvec != nullptr;
   const bool need_v =
       __any(go0 && (a.method == 2 || a.method == 3 || (a.method == 1 && !pd))) || want_eig;
   double x[P];
-  load_col<P>(a, e, am, j, go0 && j < P, d, dj, x);
+  const bool factor = go0 && pd && a.method != 2 && a.method != 3 && !want_eig;
+#pragma unroll
+  for (int i = 0; i < P; ++i) x[i] = !factor ? h[i] : i < j || j >= P ? 0.0 : i == j ? ljj : l[i];
   double cond;
   bool ill, ok, svd_done = false;
   if (need_v) {
@@ -288,7 +302,7 @@ __global__ __launch_bounds__(kInvBlock, 3) void invert_kernel(InvertArgs a) {
       }
       if (!__any(rotated)) break;
     }
-    condition_of<P>(x, own, go0, pd, a.cond_max, cond, ill, ok);
+    condition_of<P>(x, factor, own, go0, pd, a.cond_max, cond, ill, ok);
 
     // ---- SVD inversions and eigen-decomposition, on request, from the Jacobi
     // above with the rotations V accumulated: H V = X = U diag(s) with
@@ -395,16 +409,47 @@ __global__ __launch_bounds__(kInvBlock, 3) void invert_kernel(InvertArgs a) {
 #pragma unroll 1
       for (int t = 0; t < M - 1; ++t) {
         const int q = jacobi_partner<M>(j, t);
-        double y[P];
-#pragma unroll
-        for (int i = 0; i < P; ++i) y[i] = __shfl(x[i], q, kGroup);
-        const double ny = __shfl(nx, q, kGroup);
+        double y[P], ny;
+        exchange_column<P>(GX + g * (M * kExchangeLd<P>), j, q, x, nx, y, ny);
         if (jacobi_update<P>(x, y, nx, ny, j, q)) rotated = true;
       }
       if (!__any(rotated)) break;
     }
-    condition_of<P>(x, own, go0, pd, a.cond_max, cond, ill, ok);
+    condition_of<P>(x, factor, own, go0, pd, a.cond_max, cond, ill, ok);
   }
+  // ---- L^-1, column j by forward substitution
+  double y[P];
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < i; ++k) s = fma(Ls[g][k][i], y[k], s);   // y_k = 0 for k < j
+    const double inv_ii = Ls[g][i][i];
+    y[i] = i < j ? 0.0 : i == j ? inv_ii : -s * inv_ii;
+  }
+  if (j < P) {
+#pragma unroll
+    for (int k = 0; k < P; ++k) Gs[g][j][k] = y[k];
+  }
+  __syncthreads();
+
+  // ---- C_ij for i <= j, undone normalisation, both triangles into LDS
+  // (a matrix the SVD has inverted has its covariance there already)
+  if (j < P && !svd_done) {
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      double s = 0.0;
+#pragma unroll
+      for (int k = i; k < P; ++k) s = fma(Gs[g][i][k], y[k], s);   // zero terms for k < j
+      if (i <= j) {
+        const double cij = s / (Ls[g][i][P] * dj);
+        Ls[g][j][i] = cij;
+        Ls[g][i][j] = cij;
+      }
+    }
+  }
+  __syncthreads();
+
   // ---- double-double Cholesky (method 4): normalisation, factorisation,
   // L^-1 and C = L^-T L^-1 again in double-double arithmetic (~106 bits), so
   // the covariance of the FP64 matrix comes out to about kappa 2^-104 before
