@@ -413,38 +413,6 @@ __host__ __device__ inline void adjoint_point_setup(const EventC& ec, const AdjE
   }
 }
 
-// What a site's trigonometry and noise weight take from its constants.
-struct SiteHead {
-  double cdl, sdl, k1, k1t, k0t, x2_fac, xpS0, m5S0, k111S0;
-};
-
-__host__ __device__ inline SiteHead site_head(const SiteC& sc) {
-  return SiteHead{sc.cdl, sc.sdl, sc.k1, sc.k1t, sc.k0t, sc.x2_fac, sc.xpS0, sc.m5S0, sc.k111S0};
-}
-
-// The constants read before this line are asked for here, ahead of the work
-// behind it: scalar loads complete out of order, so a use waits for every load
-// in flight, and left alone the compiler puts each group right before its use.
-__host__ __device__ inline void loads_ahead() {
-#if defined(__HIP_DEVICE_COMPILE__)
-  __asm__ volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-#endif
-}
-
-struct Poly4 {
-  double c[4][5];
-};
-
-__host__ __device__ inline Poly4 poly4(const double (&p)[4][5]) {
-  Poly4 r;
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int k = 0; k < 5; ++k) r.c[q][k] = p[q][k];
-  return r;
-}
-
 // The sites' contributions at NQ points, out(s, t[kAdjN]) for each.  The basis
 // carries the root weight (trig_basis), as in the forward pass.
 template <int NQ, bool TAB, bool AHEAD, class OUT>
@@ -467,8 +435,7 @@ __host__ __device__ inline void adjoint_sites(const AdjEventC& ae, const SiteC* 
       const Point& q = ap[i].q;
       const double cH = q.cth * hd.cdl - q.sth * hd.sdl;
       const double sH = q.sth * hd.cdl + q.cth * hd.sdl;
-      const double r = TAB ? psd_root_weight<TAB>(sc, q) : psd_root_of(hd.x2_fac, hd.xpS0, hd.m5S0, hd.k111S0, q);
-      trig_basis(cH, sH, r, sp[i]);
+      trig_basis(cH, sH, site_root<false, TAB>(sc, hd, q), sp[i]);
       tc[i] = q.tf * cH;
       ts[i] = q.tf * sH;
       sp[i].u = -hd.k1 * ts[i];
