@@ -72,7 +72,14 @@ __global__ __launch_bounds__(kWBlock) void waveform_kernel(WaveformArgs a) {
   const int64_t row = a.total;
   // point 0 sits sh places past a 128-byte line of the rows
   const int sh = (int)(a.offsets[e] & 7);
-  for (int k = (int)blockIdx.y * kWBlock + tid - sh; k < ec.n; k += kWBlock * (int)gridDim.y) {
+  // A workgroup takes one stretch of whole runs of kWBlock points.  With runs
+  // dealt out in turn the line that two of them share was completed by
+  // workgroups on two XCDs wherever a row is not line-aligned (packed rows of
+  // odd length): 3000 packed pairs 726 -> 609 us, 10^4 1.89 -> 1.75 ms.
+  const int parts = (int)gridDim.y, runs = (ec.n + sh + kWBlock - 1) / kWBlock;
+  const int len = (runs + parts - 1) / parts * kWBlock;
+  const int k1 = min(ec.n, len * ((int)blockIdx.y + 1) - sh);
+  for (int k = len * (int)blockIdx.y + tid - sh; k < k1; k += kWBlock) {
     if (k < 0) continue;
     // explicit grids: ln v = (ln(pi M) + ln f)/3 from the given frequency
     const double L = EXPL ? (ec.lnpiM + log(ec.fx[k])) / 3.0 : fma((double)k, ec.dlnv, ec.lnv0);

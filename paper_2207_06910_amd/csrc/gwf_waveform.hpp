@@ -11,21 +11,19 @@ namespace gwf {
 
 constexpr int kWBlock = 256;
 
-// Workgroups per event: a small catalogue's grids are shared out (workgroup y
-// of an event takes every gridDim.y-th run of kWBlock points), so that about
-// 2048 workgroups are there, and two up to 8192 events, whose longest grids
-// would otherwise end the launch alone.  Measured, one workgroup per event and
-// this: strain of 600 neutron-star pairs 183 and 124 us, derivatives of 64
-// events 347 and 148 us.
-// The runs start on a 128-byte line of the rows (eight complex values): a
-// wavefront's 1 KB store is then whole lines, where a run that starts inside
-// one leaves the shared line to be completed by the next run's workgroup, on
-// another XCD.  Strain of 4000 pairs (3.1 GB) 825 -> 697 us, derivatives of 300
-// (3.0 GB) 904 -> 616 us.  Stores past the caches (non-temporal) were slower:
-// 948 and 881 us.
+// Workgroups per event: a small catalogue's grids are shared out, so that about
+// 2048 workgroups are there, and two in a large one, whose longest grids would
+// otherwise end the launch alone.  Measured, one workgroup per event and this:
+// strain of 600 neutron-star pairs 183 and 124 us, derivatives of 64 events 347
+// and 148 us.
+// A workgroup's points start on a 128-byte line of the first row (eight complex
+// values): where the row length is a multiple of eight, a wavefront's 1 KB store
+// is then whole lines, while a run that starts inside one leaves the shared
+// line to be completed by the next run.  Strain of 4000 pairs (3.1 GB) 825 ->
+// 697 us, derivatives of 300 (3.0 GB) 904 -> 616 us.  Stores past the caches
+// (non-temporal) were slower: 948 and 881 us.
 inline unsigned wave_parts(int64_t n) {
-  const int64_t y = (2048 + n - 1) / n;
-  return n >= 8192 ? 1u : (unsigned)std::min<int64_t>(64, std::max<int64_t>(y, 2));
+  return (unsigned)std::min<int64_t>(64, std::max<int64_t>((2048 + n - 1) / n, 2));
 }
 
 // Event e's inputs: the 13 parameters (no tidal rows without tides), e0 and

@@ -158,7 +158,7 @@ void launch_deriv_t(const WaveformArgs& a, int npi, bool rot, dim3 grid, dim3 bl
 
 hipError_t launch_waveform_deriv(const WaveformArgs& a0, int npi, bool rot, hipStream_t stream) {
   return launch_slices(a0, a0.n, 1, kWBlock, [&](const WaveformArgs& a, dim3 grid, dim3 block) {
-    grid.y = wave_parts(a.n);
+    grid.y = a.n >= 8192 ? 1u : wave_parts(a.n);
     if (a.gf) launch_deriv_t<true>(a, npi, rot, grid, block, stream);
     else launch_deriv_t<false>(a, npi, rot, grid, block, stream);
   });
