@@ -89,7 +89,15 @@ __global__ __launch_bounds__(kWBlock) void waveform_deriv_kernel(WaveformArgs a)
   const int64_t prow = (int64_t)a.net.n_ifo * row;     // one parameter's block of rows
   // point 0 sits sh places past a 128-byte line of the rows
   const int sh = (int)(a.offsets[e] & 7);
-  for (int k = (int)blockIdx.y * kWBlock + tid - sh; k < ec.n; k += kWBlock * (int)gridDim.y) {
+  // one stretch of whole runs a workgroup, the runs shared out evenly: dealt
+  // out in turn, two XCDs completed a shared line wherever a row is not
+  // line-aligned.  Derivatives of 1000 packed pairs 3.13 -> 2.87 ms, of 64
+  // events 149 -> 141 us.
+  const int part = (int)blockIdx.y, parts = (int)gridDim.y, runs = (ec.n + sh + kWBlock - 1) / kWBlock;
+  const int each = runs / parts, more = runs - each * parts;
+  const int r0 = part * each + min(part, more), r1 = r0 + each + (part < more ? 1 : 0);
+  const int k1 = min(ec.n, r1 * kWBlock - sh);
+  for (int k = r0 * kWBlock + tid - sh; k < k1; k += kWBlock) {
     if (k < 0) continue;
     // the event and site constants are re-read from LDS (uniform broadcast
     // reads) rather than held in registers across iterations
