@@ -46,9 +46,9 @@ MEASURED_TRAFFIC = {
 # clock is 4 x SQ_INSTS_VALU / (1024 SIMDs x 2.4 GHz x kernel time).  Set an
 # entry to None when its kernel changes.
 MEASURED_VALU_INSTS = {
-    "items_kernel<tidal,rot>": 1.2594e9,
-    "items_kernel<tidal,rot,mixed>": 1.2592e9,
-    "fisher_kernel<tidal,rot>": 1.3111e9,
+    "items_kernel<tidal,rot>": 9.47e8,
+    "items_kernel<tidal,rot,mixed>": 9.53e8,
+    "fisher_kernel<tidal,rot>": 1.013e9,
 }
 N_SIMD, CLOCK_HZ = 1024, 2.4e9
 
@@ -80,25 +80,26 @@ def log(msg):
 # instantiation the benchmarks run: tides, Earth rotation, analytic PSDs.
 # Split by where the work sits: once per point, per site, per effective
 # interferometer (n_eff = 1 per L site, 2 per closed triangle).
-#   items_kernel (FP64)   point 223 (grid, amplitude, PN series, sidereal
-#                         sin/cos, phase-only coefficients, staging),
-#                         site 57 (hour angle, root of the PSD weight and the
+#   items_kernel (FP64)   point 300 (grid, amplitude, PN series, sidereal
+#                         sin/cos, phase-only coefficients, the point's share
+#                         of the Gram from its network sums, staging),
+#                         site 43 (hour angle, root of the PSD weight and the
 #                         weighted trigonometric basis, arrival-time
-#                         derivatives), interferometer 213 (six pattern
-#                         polynomials, derivative vectors, 5x5 rank-2 update,
-#                         moments); MFMA 128 (16 per 64 points)
+#                         derivatives), interferometer 98 (six pattern
+#                         polynomials, Q, Z, Y and 14 network sums); MFMA 128
+#                         (16 per 64 points)
 #   items_kernel (mixed)  the same with the PSD's rational part in FP32:
-#                         site 35 FP64 (+ 14 FP32)
-#   adjoint_items_kernel  point 412 (the point set-up and the Gbar inner
-#                         products of the point's vectors), site 115, interferometer 294
+#                         site 24 FP64 (+ 14 FP32)
+#   adjoint_items_kernel  point 394 (the point set-up and the 14 coefficients
+#                         of its quadratic form), site 59, interferometer 320
 #                         (two points per lane and iteration; points past an item's
 #                         end run at zero weight and are not in the model)
 # The counter passes (SQ_INSTS_VALU_FLOPS_FP64 x 64 lanes and
 # SQ_INSTS_VALU_MFMA_MOPS_F64 x 512) confirm these per launch.
 KERNEL_FLOPS = {
-    "items": {"point": 223, "site": 57, "ifo": 213, "mfma": 128},
-    "items_mixed": {"point": 223, "site": 35, "ifo": 213, "mfma": 128},
-    "adjoint": {"point": 412, "site": 115, "ifo": 294, "mfma": 0},
+    "items": {"point": 300, "site": 43, "ifo": 98, "mfma": 128},
+    "items_mixed": {"point": 300, "site": 24, "ifo": 98, "mfma": 128},
+    "adjoint": {"point": 394, "site": 59, "ifo": 320, "mfma": 0},
 }
 # A dense per-(point, interferometer) count (Gram 2P(P+1), weighting 2P,
 # SNR 4, derivative assembly 8P, projection 120, PN 200 per point): the work

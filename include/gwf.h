@@ -614,13 +614,13 @@ gwf_status gwf_plan_destroy(gwf_plan* plan);
  *   chunk     points per work item, a positive multiple of 256
  *   npts_max  an upper bound of the catalogue's grid lengths; an event with a
  *             longer grid gets GWF_EV_INVALID_PARAM and a zero Fisher matrix
- * The workspace needs, in 256-byte aligned parts, n x 1048 bytes of event
- * constants, n x n_site x 512 of site constants, 4 (n + 1) of item offsets,
+ * The workspace needs, in 256-byte aligned parts, n x 1160 bytes of event
+ * constants, n x n_site x 608 of site constants, 4 (n + 1) of item offsets,
  * and 16 + 8 NACC bytes per work item (NACC = 91 with GWF_TIDAL, else 69)
  * for n ceil(npts_max / chunk) items, plus 256; a call needing more than
  * GWF_STATIC_SCRATCH_BYTES returns GWF_E_INVALID_ARG before any launch (the
  * 10^4 neutron-star binaries of 2000-20000 points on three sites need
- * about 41 MB with chunk 16384).  Every call on a device uses the same
+ * about 45 MB with chunk 16384).  Every call on a device uses the same
  * array: calls that overlap on one device (different streams, or threads)
  * race and must be serialised by the caller; each call rewrites everything
  * it reads. */

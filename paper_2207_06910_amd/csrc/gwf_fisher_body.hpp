@@ -24,7 +24,7 @@
 //
 // What bounds it: FP64 issue.  On the BNS catalogue (9.7e7 points, three
 // sites, four effective interferometers, P = 13) the work-item kernel takes
-// 2.09 ms where the rank-2 update of five derivative rows per interferometer,
+// 2.10 ms where the rank-2 update of five derivative rows per interferometer,
 // one point per lane, took 2.81 ms.
 #pragma once
 

@@ -10,7 +10,8 @@
 //
 // What bounds it: FP64 issue, about 80 instructions per point and 25 per site
 // and 14 per arm.  On 3000 neutron-star binaries (2.9e7 points, three sites,
-// five interferometers) one workgroup per event takes 0.38 ms, where an
+// five interferometers) one workgroup per event takes 0.38 ms (0.24 with each
+// event shared out over workgroups, see gwf_split.hip), where an
 // exponential per point and site, patterns from frame products and Horner
 // series took 0.58 ms.
 #pragma once
