@@ -259,7 +259,7 @@ class DeviceWorkload:
         self.n_ifo = n_ifo(self.sites)
         # the catalogue's longest grid and all its points, by which the plain
         # calls choose how they split the work (never what they compute)
-        self.points_max, self.points = int(np.max(wl.npts)), int(np.sum(wl.npts, dtype=np.int64))
+        self.points_max, self.points = int(np.max(wl.npts, initial=0)), int(np.sum(wl.npts, dtype=np.int64))
 
     def with_sites(self, sites) -> "DeviceWorkload":
         """The same device arrays with another network of the same shapes
