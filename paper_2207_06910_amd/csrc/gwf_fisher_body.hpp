@@ -100,11 +100,15 @@ struct FisherLds {
 };
 
 // A double that is the same in every lane, in scalar registers.
-__device__ inline double uniform_d(double x) {
+__host__ __device__ inline double uniform_d(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
   const int64_t b = __double_as_longlong(x);
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
   return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
+#else
+  return x;
+#endif
 }
 
 // Load an event's inputs: the 13 parameters (missing tidal rows read as

@@ -1,0 +1,44 @@
+"""The SNR kernels' grid walk on the host build of their code: a lane's sums
+over a grid of any length against the same points evaluated directly.
+
+Every term is positive, so the sums differ by no more than the largest relative
+difference of a term.  A walked value is at most 2 m + 1 = 31 u off (m = 15 steps
+from its anchor), and a term is a product of powers of the three values, with
+an exponent of at most 20 in all (v^-4 from the amplitude, v^12 and v^-6 v^6
+within the noise curve's shape): 20 x 31 u = 6.9e-14, whatever the length."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2207_06910_amd import synth
+
+HERE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "model_host")
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("snr") / "libsnr_host.so")
+    subprocess.check_call(["/opt/rocm/bin/hipcc", "-O2", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
+                           os.path.join(HERE, "snr_host.hip"), "-o", lib], stderr=subprocess.DEVNULL)
+    return ctypes.CDLL(lib)
+
+
+@pytest.mark.parametrize("npts", [2, 300, 4096, 4097, 20000, 1000000, 4000000])
+def test_walk_does_not_drift(host, npts):
+    wl = synth.bns1e4(n=3, seed=5)
+    sites = np.ascontiguousarray(wl.site_array())
+    P = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
+    for e, tid in ((0, 0), (1, 131), (2, 255)):
+        par = np.zeros(15)
+        par[:13] = wl.par[:, e]
+        got, ref = np.zeros(3 * len(sites)), np.zeros(3 * len(sites))
+        for direct, out in ((0, got), (1, ref)):
+            assert host.snr_lane_host(P(par), ctypes.c_double(2.0), ctypes.c_double(0.0), ctypes.c_int32(npts),
+                                      len(sites), P(sites), tid, direct, P(out)) == 0
+        assert np.array_equal(ref == 0.0, got == 0.0)
+        on = ref > 0.0
+        assert on.any() == (tid < npts)
+        assert np.all(np.abs(got[on] / ref[on] - 1.0) <= 6.9e-14), np.max(np.abs(got[on] / ref[on] - 1.0))
