@@ -39,6 +39,18 @@ __host__ __device__ inline double rsqrt_d(double x) {
 #endif
 }
 
+// rsqrt_d, and 0 for an infinite x (the estimate is 0 there, and the step's
+// x y^2 has to be a number).
+__host__ __device__ inline double rsqrt_inf_d(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-fmin(x, 1.7976931348623157e308) * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+#else
+  return 1.0 / sqrt(x);
+#endif
+}
+
 // sqrt(x) in FP32 from the hardware square root (about an ulp); the host
 // build calls sqrtf.
 __host__ __device__ inline float sqrtf_hw(float x) {

@@ -1068,10 +1068,10 @@ __host__ __device__ inline bool table_psd(const SiteC& sc, const Point& q, doubl
 }
 
 // The square root of the weight 4 w A^2 / S_n(f) with a sampled curve; zero
-// outside the sampled range.
+// outside the sampled range and where the curve is infinite.
 __host__ __device__ inline double table_root_weight(const SiteC& sc, const Point& q) {
   double S;
-  return table_psd(sc, q, S) ? (q.rw * sc.rS0inv) * rsqrt_d(S) : 0.0;
+  return table_psd(sc, q, S) ? (q.rw * sc.rS0inv) * rsqrt_inf_d(S) : 0.0;
 }
 
 // The square root of the weight, r = sqrt(4 w A^2 / S_n(f)), which the
@@ -1097,6 +1097,22 @@ __host__ __device__ inline double psd_root_weight(const SiteC& sc, const Point& 
   if (TAB && sc.tab_kind)
     return table_root_weight(sc, q);
   return psd_root_of(sc.x2_fac, sc.xpS0, sc.m5S0, sc.k111S0, q);
+}
+
+// The weight w / S_n(f) itself, for w = 4 w A^2, as the SNR kernels take it: it
+// enters their sums as it is, so that a sampled value that is zero, negative or
+// infinite gives an infinite, negative or no contribution.
+template <bool TAB = true>
+__host__ __device__ inline double psd_weight(const SiteC& sc, const Point& q, double w) {
+  if (TAB && sc.tab_kind) {
+    double S;
+    return table_psd(sc, q, S) ? w * (sc.rS0inv * sc.rS0inv) / S : 0.0;
+  }
+  const double x2 = sc.x2_fac * q.v6;
+  const double num = fma(fma(0.5, x2, -1.0), x2, 1.0);
+  const double den = fma(0.5, x2, 1.0);
+  const double topS = fma(fma(sc.m5S0, q.iv6, sc.xpS0 * q.vpsd), den, sc.k111S0 * num);
+  return w * den * recip(topS);
 }
 
 // The same root with the PSD shape in FP32 (mixed form).  The weight is a

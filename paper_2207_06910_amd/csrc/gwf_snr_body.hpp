@@ -2,9 +2,8 @@
 // one-event-per-workgroup kernel (gwf_fisher.hip).
 //
 // Every lane walks its grid points two at a time as the Fisher kernels do
-// (GridWalk; the site's noise weight enters as its square root, which scales
-// the trigonometric basis of the patterns) and adds the squared response of
-// each arm to its own sums.  The sites' constants are those of site_setup with
+// (GridWalk) and adds the weighted squared response of each arm to its own
+// sums.  The sites' constants are those of site_setup with
 // the arms themselves as effective interferometers (kArmsPlain): an L's one
 // arm, a triangle's first two, whose third response is minus their sum.
 //
@@ -58,22 +57,28 @@ __host__ __device__ inline void snr_lane(const EventC& ec, const SiteC* sc, int 
         asm volatile("" ::: "memory");
         const SiteC& st = sc[s];
         SiteTrigR sp[NQ];
+        double om[NQ];
 #pragma unroll
-        for (int i = 0; i < NQ; ++i) site_trig_root<false, TAB>(st, q[i], sp[i]);
+        for (int i = 0; i < NQ; ++i) {
+          const double cH = fma(q[i].cth, st.cdl, -(q[i].sth * st.sdl));
+          const double sH = fma(q[i].sth, st.cdl, q[i].cth * st.sdl);
+          trig_basis(cH, sH, 1.0, sp[i]);
+          om[i] = psd_weight<TAB>(st, q[i], EXPL ? q[i].w4A2 : q[i].rw * q[i].rw);
+        }
         double p0[NQ], x0[NQ];
 #pragma unroll
         for (int i = 0; i < NQ; ++i) {
           p0[i] = cplus * trig_val_r(st.jk[0][0], sp[i]);
           x0[i] = ccross * trig_val_r(st.jk[0][1], sp[i]);
-          acc[3 * s] = fma(p0[i], p0[i], fma(x0[i], x0[i], acc[3 * s]));
+          acc[3 * s] = fma(om[i], fma(p0[i], p0[i], x0[i] * x0[i]), acc[3 * s]);
         }
         if (st.n_arm == 3) {
 #pragma unroll
           for (int i = 0; i < NQ; ++i) {
             const double p1 = cplus * trig_val_r(st.jk[1][0], sp[i]), x1 = ccross * trig_val_r(st.jk[1][1], sp[i]);
             const double p2 = p0[i] + p1, x2 = x0[i] + x1;     // minus the third arm
-            acc[3 * s + 1] = fma(p1, p1, fma(x1, x1, acc[3 * s + 1]));
-            acc[3 * s + 2] = fma(p2, p2, fma(x2, x2, acc[3 * s + 2]));
+            acc[3 * s + 1] = fma(om[i], fma(p1, p1, x1 * x1), acc[3 * s + 1]);
+            acc[3 * s + 2] = fma(om[i], fma(p2, p2, x2 * x2), acc[3 * s + 2]);
           }
         }
       }

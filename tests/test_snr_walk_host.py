@@ -26,19 +26,44 @@ def host(tmp_path_factory):
     return ctypes.CDLL(lib)
 
 
+def _lane(host, wl, e, npts, tid, direct=0, curve=None, kind=1):
+    sites = np.ascontiguousarray(wl.site_array())
+    P = lambda a: None if a is None else a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
+    par = np.zeros(15)
+    par[:13] = wl.par[:, e]
+    out = np.zeros(3 * len(sites))
+    f, S = (None, None) if curve is None else [np.ascontiguousarray(x) for x in curve]
+    assert host.snr_lane_host(P(par), ctypes.c_double(2.0), ctypes.c_double(0.0), ctypes.c_int32(npts), len(sites),
+                              P(sites), tid, direct, ctypes.c_int64(0 if f is None else len(f)), P(f), P(S), kind,
+                              P(out)) == 0
+    return out
+
+
 @pytest.mark.parametrize("npts", [2, 300, 4096, 4097, 20000, 1000000, 4000000])
 def test_walk_does_not_drift(host, npts):
     wl = synth.bns1e4(n=3, seed=5)
-    sites = np.ascontiguousarray(wl.site_array())
-    P = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
     for e, tid in ((0, 0), (1, 131), (2, 255)):
-        par = np.zeros(15)
-        par[:13] = wl.par[:, e]
-        got, ref = np.zeros(3 * len(sites)), np.zeros(3 * len(sites))
-        for direct, out in ((0, got), (1, ref)):
-            assert host.snr_lane_host(P(par), ctypes.c_double(2.0), ctypes.c_double(0.0), ctypes.c_int32(npts),
-                                      len(sites), P(sites), tid, direct, P(out)) == 0
+        got, ref = _lane(host, wl, e, npts, tid), _lane(host, wl, e, npts, tid, direct=1)
         assert np.array_equal(ref == 0.0, got == 0.0)
         on = ref > 0.0
         assert on.any() == (tid < npts)
         assert np.all(np.abs(got[on] / ref[on] - 1.0) <= 6.9e-14), np.max(np.abs(got[on] / ref[on] - 1.0))
+
+
+def test_sampled_values_without_a_root(host):
+    """The weight enters the sums as it is: a curve of the other sign gives the
+    sums of the other sign, a zero an infinite sum, an infinite last sample the
+    sums of the curve without its last interval."""
+    wl = synth.bns1e4(n=1, seed=5)
+    f = np.geomspace(2.0, 3000.0, 500)
+    S = (f / 15.0) ** -4 + 1.0 + (f / 250.0) ** 2
+    ref = _lane(host, wl, 0, 3000, 7, curve=(f, S))
+    assert np.array_equal(_lane(host, wl, 0, 3000, 7, curve=(f, -S)), -ref) and ref.max() > 0.0
+    zero = S.copy()
+    zero[200:300] = 0.0                          # a few of the lane's twelve points
+    assert np.array_equal(_lane(host, wl, 0, 3000, 7, curve=(f, zero)) == np.inf, ref > 0.0)
+    cut = f < 700.0
+    inf = S[cut].copy()
+    inf[-1] = np.inf
+    assert np.array_equal(_lane(host, wl, 0, 3000, 7, curve=(f[cut], inf)),
+                          _lane(host, wl, 0, 3000, 7, curve=(f[cut][:-1], S[cut][:-1])))
