@@ -311,8 +311,6 @@ def _split(dw: DeviceWorkload, net, what, stream):
     if dw.grid_f is not None or (dw.points_max <= short and dw.points <= 1 << 20 and
                                  (what != SPLIT_IFOS or dw.n_ifo == 1)):
         return None
-    if what == SPLIT_SNR_FISHER and dw.flags & ECCENTRIC:
-        return None             # an event whose e0 is invalid keeps the SNR of its circular form there
     # parts of about 1/2048 of the work (the chip runs 512 workgroups at a time)
     # in whole iterations of a workgroup (512 points), 2 to 16 of them: 600
     # pairs' matrices 258 us with 1/8192, 234 with 1/4096, 210 with 1/2048

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(64) void setup_kernel(SetupArgs a) {
     EventC& ec = a.evc[e];
     event_grid_setup(p, a.fmin[e], a.fmax ? a.fmax[e] : 0.0, a.npts[e], a.flags, ec);
     if (!ec.status && (a.npts[e] != a.npts_plan[e] || a.npts[e] > a.npts_max))
-      ec.status = kEvInvalid;   // grid changed since the items were built, or longer than they allow
+      ec.status = ec.status_circ = kEvInvalid;   // grid changed since the items were built, or longer than they allow
     if (a.status) a.status[e] = ec.status;
   } else if (row == 1) {
     if (!a.no_phase) event_phase_setup(p, a.flags, a.evc[e]);
@@ -159,8 +159,7 @@ __global__ void combine_kernel(CombineArgs a) {
   }
   int r, c;
   slot_position(slot, NPI, r, c);
-  // an event skipped by the threshold keeps the SNR of the pass that skipped it
-  if (r == 8 && c == 8 && a.snr && st0 != kEvSkipped) a.snr[e] = sqrt(s);
+  if (r == 8 && c == 8 && a.snr && !(st0 && a.keep_snr)) a.snr[e] = sqrt(s);
   if (!rows_in(event_rows(a.par_mask, e), r, c)) s = 0.0;   // not one of the event's rows
   double* F = a.fisher + mat * ((int64_t)P * P * a.n);
   F[((int64_t)r * P + c) * a.n + e] = s;
@@ -302,7 +301,7 @@ __global__ __launch_bounds__(kBlock, 2) void snr_parts_kernel(SnrPartsArgs a) {
   const EventC& ec = *(const EventC*)((CEventC*)(a.evc) + e);
   const SiteC* sc = (const SiteC*)((CSiteC*)(a.sic) + (int64_t)e * a.n_set + a.set0);
   const int32_t len = part_length(ec.n, a.parts), k0 = part * len;
-  if (ec.status || k0 >= ec.n) return;             // its sums are not read
+  if (ec.status_circ || k0 >= ec.n) return;        // its sums are not read
   double acc[kSnrSlots];
 #pragma unroll
   for (int i = 0; i < kSnrSlots; ++i) acc[i] = 0.0;
@@ -315,7 +314,7 @@ __global__ __launch_bounds__(kBlock, 2) void snr_parts_kernel(SnrPartsArgs a) {
 __global__ __launch_bounds__(64) void snr_combine_kernel(SnrCombineArgs a) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= a.n) return;
-  const int32_t st0 = a.evc[e].status;
+  const int32_t st0 = a.evc[e].status_circ;
   const int32_t parts = st0 ? 0 : (a.evc[e].n - 1) / part_length(a.evc[e].n, a.parts) + 1;
   double tot = 0.0;
   for (int i = 0; i < a.n_ifo; ++i) {
@@ -327,15 +326,13 @@ __global__ __launch_bounds__(64) void snr_combine_kernel(SnrCombineArgs a) {
   }
   const double snr = sqrt(tot);
   a.snr[e] = snr;
-  if (st0) {
-    if (a.status) a.status[e] = st0;
-  } else if (a.snr_th > 0.0) {                     // the pass before the matrices
-    if (!(snr > a.snr_th)) {
+  if (a.snr_th > 0.0) {                            // the pass before the matrices
+    if (!a.evc[e].status && !(snr > a.snr_th)) {
       a.evc[e].status = kEvSkipped;
       if (a.status) a.status[e] = kEvSkipped;
     }
   } else if (a.status) {
-    a.status[e] = finite(tot) ? 0 : kEvNonFinite;
+    a.status[e] = st0 ? st0 : finite(tot) ? 0 : kEvNonFinite;
   }
 }
 

@@ -68,6 +68,7 @@ struct CombineArgs {
   const int32_t* item_first;  // [n+1]: items of event e are item_first[e] .. item_first[e+1]-1
   const double* partial;
   int32_t parts, n_mat;       // split form (item_first NULL), see ItemsArgs
+  int32_t keep_snr;           // nonzero: events with a status keep the SNR of the pass that skipped them
   double* fisher;             // [n_mat][P][P][n]
   double* snr;                // [n] or NULL
   int32_t* status;            // [n]

@@ -101,7 +101,7 @@ struct EventC {
   const double* fx;
   double lnpiM;
   int32_t n;
-  int32_t status;
+  int32_t status;              // of the event; status_circ: with e0 left out of it
   // amplitude: A^2 = KA v^-7 (factor 4 of the inner product included)
   double KA4;
   double dlnA_dMc, inv_dL;
@@ -121,7 +121,7 @@ struct EventC {
   // r = (v_ref/v)^{19/3} = exp((19/3)(ecc_lnvr - ln v)); ecc_mc v^-5 r joins
   // dPsi/dMc and ecc_e0 v^-5 r is dPsi/de0 (eta does not enter at fixed Mc)
   double ecc_lnvr, ecc_psi, ecc_mc, ecc_e0, ecc_cyc;
-  int32_t ecc, pad_ecc;
+  int32_t ecc, status_circ;
 };
 
 struct SiteC {
@@ -353,8 +353,10 @@ __host__ __device__ inline void event_grid_setup(const double* p, double fmin, d
   if (!(fmax > 0.0)) fmax = cut_frequency_of(Ms);
   ec.n = n;
   ec.fx = nullptr;
-  ec.status = check_event(p, (flags & kFlagTidal) != 0, fmin, fmax, n, (flags & kFlagEcc) != 0);
-  if (ec.status) return;
+  // the SNR does not know e0: it is there for an event whose e0 alone is refused
+  ec.status = ec.status_circ = check_event(p, (flags & kFlagTidal) != 0, fmin, fmax, n);
+  if (flags & kFlagEcc) ec.status = check_event(p, (flags & kFlagTidal) != 0, fmin, fmax, n, true);
+  if (ec.status_circ) return;
   // grid
   const double D = log(fmax / fmin) / (double)(n - 1);
   ec.piM = kPi * Ms;

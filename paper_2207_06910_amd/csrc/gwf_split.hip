@@ -89,8 +89,7 @@ gwf_status run(const gwf_events* ev, const gwf_grid* grid, uint32_t flags, doubl
   sa.fmin = grid->fmin; sa.fmax = grid->fmax; sa.npts = grid->npts; sa.npts_plan = grid->npts;
   sa.npts_max = 0x7fffffff;
   sa.ecc = ev->ecc; sa.fref = ev->f_ref_ecc;
-  if (!l.n_mat) sa.flags = flags & ~(uint32_t)GWF_ECCENTRIC;   // e0 does not enter the SNR
-  else sa.flags = flags;
+  sa.flags = flags;
   sa.net = nd; sa.evc = evc; sa.sic = sic; sa.status = status; sa.active = ev->active;
   sa.sets = l.sets; sa.n_set = l.n_set; sa.no_phase = l.n_mat == 0;
   hipError_t err = launch_setup(sa, s);
@@ -116,6 +115,7 @@ gwf_status run(const gwf_events* ev, const gwf_grid* grid, uint32_t flags, doubl
       CombineArgs ca{};
       ca.n = ev->n; ca.evc = evc; ca.partial = partial; ca.parts = parts; ca.n_mat = l.n_mat;
       ca.fisher = fisher; ca.snr = snr; ca.status = status; ca.par_mask = ev->par_mask;
+      ca.keep_snr = snr_th > 0.0;
       err = launch_combine(ca, npi, s);
     }
   }
