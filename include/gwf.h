@@ -478,13 +478,17 @@ gwf_status gwf_fisher_basis(int32_t P, int64_t n, const double* fisher, const gw
 /* -------------------------------------------------------- split form */
 /* gwf_snr, gwf_fisher and gwf_fisher_ifo with each event's grid split over
  * several workgroups, in a workspace the caller gives for the call: the same
- * outputs, statuses and thresholds (a split sum differs in its last bits), for
- * log grids.  For few events, long grids or uneven ones, where one workgroup
+ * outputs, statuses and thresholds, for log grids.  Both forms sum an event's
+ * grid in stretches of GWF_FISHER_STRETCH or GWF_SNR_STRETCH points (times the
+ * smallest whole number that leaves no more than GWF_SPLIT_PARTS_MAX of them),
+ * so with as many parts as that the results are those of the plain calls bit
+ * for bit, whatever the other events.  For few events, long grids or uneven ones, where one workgroup
  * per event leaves the chip idle; the set-up, part and combine kernels are
  * ordinary launches on `stream`, nothing is allocated or read back.
  *   parts      1..GWF_SPLIT_PARTS_MAX, the most parts of one event's grid: a
- *              grid of n points has parts of ceil(n / parts) points, rounded up
- *              to a multiple of 512
+ *              part is a stretch; a grid of more stretches has longer parts, of
+ *              ceil(n / parts) points rounded up to a multiple of 512 (its sums
+ *              then differ in their last bits)
  *   work       device, 256-byte aligned, of at least gwf_split_bytes bytes; used
  *              until the stream has passed the call; contents need not be set
  *   gwf_split_bytes   the workspace of n events (-1 and gwf_last_error if the
@@ -493,6 +497,8 @@ gwf_status gwf_fisher_basis(int32_t P, int64_t n, const double* fisher, const gw
  * Other arguments as for the plain calls; explicit grids return
  * GWF_E_UNSUPPORTED. */
 #define GWF_SPLIT_PARTS_MAX 64
+#define GWF_FISHER_STRETCH 3072
+#define GWF_SNR_STRETCH 4096
 
 int64_t gwf_split_bytes(int64_t n, const gwf_network* net, uint32_t flags, int32_t what, int32_t parts);
 

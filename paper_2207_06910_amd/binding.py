@@ -293,30 +293,30 @@ class DeviceWorkload:
 
 
 SPLIT_SNR, SPLIT_FISHER, SPLIT_SNR_FISHER, SPLIT_IFOS = 0, 1, 2, 3
+FISHER_STRETCH, SNR_STRETCH = 3072, 4096        # GWF_FISHER_STRETCH, GWF_SNR_STRETCH
 SPLIT_WORK_MAX = 256 << 20      # bytes of workspace a plain call may take
 
 
 def _split(dw: DeviceWorkload, net, what, stream):
     """(parts, workspace) of a plain call in the split form (gwf_*_split), or
-    None where one workgroup per event is the better form.  That is: explicit
-    grids, which the split form does not take; catalogues whose constants would
-    need more than SPLIT_WORK_MAX, which fill the chip by themselves; and few
-    events with short grids, where one launch beats three.  Measured, plain and
-    split, us: Fisher of 400 events of 1800 points 38 and 44, of 1500 events of
-    1000 points 67 and 59, of one event of 3000 points 36 and 32; SNR of 100
-    events of 4000 points 26 and 33, of one event of 10^4 points 71 and 36."""
+    None where one workgroup per event is the better form: explicit grids, which
+    the split form does not take; catalogues whose constants would need more
+    than SPLIT_WORK_MAX, which fill the chip by themselves; and short grids of
+    no more events than the chip runs workgroups at once (512), where one launch
+    beats three.  The form changes no result.  Measured, plain and split, us:
+    Fisher of one event of 1000 and 2000 neutron-star points 31 and 33, 43 and
+    39, of 400 events 38 and 41, 54 and 52, of 800 events of 500 points 48 and
+    46 and of 100 points 40 and 46; SNR of 400 events of 4000 and 6000 points 40
+    and 41, 52 and 45, of 800 events of 500 points 33 and 30; the matrices of
+    five interferometers of one event of 100 points 87 and 32."""
     import torch
     n = dw.n
-    short = 6144 if what == SPLIT_SNR else 2048
-    if dw.grid_f is not None or (dw.points_max <= short and dw.points <= 1 << 20 and
-                                 (what != SPLIT_IFOS or dw.n_ifo == 1)):
+    few = n <= 512 or (what != SPLIT_SNR and dw.points <= 1 << 18)
+    short = SNR_STRETCH if what == SPLIT_SNR else 2048
+    if dw.grid_f is not None or (few and dw.points_max <= short and (what != SPLIT_IFOS or dw.n_ifo == 1)):
         return None
-    # parts of about 1/2048 of the work (the chip runs 512 workgroups at a time)
-    # in whole iterations of a workgroup (512 points), 2 to 16 of them: 600
-    # pairs' matrices 258 us with 1/8192, 234 with 1/4096, 210 with 1/2048
-    per = dw.points * (dw.n_ifo if what == SPLIT_IFOS else 1) // 2048
-    length = 512 * min(16, max(2, -(-per // 512)))
-    parts = min(64, -(-dw.points_max // length))
+    # as many parts as the longest grid has stretches (gwf_*_split)
+    parts = min(64, -(-dw.points_max // (SNR_STRETCH if what == SPLIT_SNR else FISHER_STRETCH)))
     size = load().gwf_split_bytes(n, ctypes.byref(net), dw.flags, what, parts)
     if size < 0 or size > SPLIT_WORK_MAX:
         return None

@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kBlock, 2) void items_kernel(ItemsArgs a) {
     const uint32_t row = u / n, mat = row / (uint32_t)a.parts;
     const int32_t part = (int32_t)(row - mat * (uint32_t)a.parts);
     w.e = (int32_t)(u - row * n);
-    const int32_t ne = a.evc[w.e].n, len = part_length(ne, a.parts);
+    const int32_t ne = a.evc[w.e].n, len = part_length(ne, a.parts, kFisherStretch);
     w.k0 = part * len;
     w.k1 = min(ne, w.k0 + len);
     if (a.evc[w.e].status || w.k0 >= ne) return;   // its sums are not read
@@ -153,7 +153,7 @@ __global__ void combine_kernel(CombineArgs a) {
     } else {
       const int32_t ne = a.evc[e].n;
       i0 = u * a.parts;
-      i1 = i0 + (ne - 1) / part_length(ne, a.parts) + 1;
+      i1 = i0 + (ne - 1) / part_length(ne, a.parts, kFisherStretch) + 1;
     }
     for (int64_t i = i0; i < i1; ++i) s += a.partial[i * NACC + slot];
   }
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kBlock, 2) void snr_parts_kernel(SnrPartsArgs a) {
   typedef const __attribute__((address_space(4))) SiteC CSiteC;
   const EventC& ec = *(const EventC*)((CEventC*)(a.evc) + e);
   const SiteC* sc = (const SiteC*)((CSiteC*)(a.sic) + (int64_t)e * a.n_set + a.set0);
-  const int32_t len = part_length(ec.n, a.parts), k0 = part * len;
+  const int32_t len = part_length(ec.n, a.parts, kSnrStretch), k0 = part * len;
   if (ec.status_circ || k0 >= ec.n) return;        // its sums are not read
   double acc[kSnrSlots];
 #pragma unroll
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(64) void snr_combine_kernel(SnrCombineArgs a) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= a.n) return;
   const int32_t st0 = a.evc[e].status_circ;
-  const int32_t parts = st0 ? 0 : (a.evc[e].n - 1) / part_length(a.evc[e].n, a.parts) + 1;
+  const int32_t parts = st0 ? 0 : (a.evc[e].n - 1) / part_length(a.evc[e].n, a.parts, kSnrStretch) + 1;
   double tot = 0.0;
   for (int i = 0; i < a.n_ifo; ++i) {
     double t = 0.0;

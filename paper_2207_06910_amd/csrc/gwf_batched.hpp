@@ -18,12 +18,12 @@ enum SiteSets {
   kSetsIfos = 3       // one per interferometer: that one alone (duty factor applied)
 };
 
-// An event's grid of n points in at most `parts` parts of part_length points,
-// a multiple of what a workgroup takes in one iteration.
-constexpr int kPartUnit = 512;
-__host__ __device__ inline int32_t part_length(int32_t n, int32_t parts) {
-  const int32_t len = (n - 1) / parts + 1;
-  return ((len - 1) / kPartUnit + 1) * kPartUnit;
+// An event's grid of n points in at most `parts` parts of part_length points:
+// its stretches, or longer parts where there are too few.
+__host__ __device__ inline int32_t part_length(int32_t n, int32_t parts, int32_t unit) {
+  const int32_t len = stretch_length(n, unit);
+  if ((n - 1) / len < parts) return len;
+  return (((n - 1) / parts) / kPartUnit + 1) * kPartUnit;
 }
 
 struct SetupArgs {

@@ -76,7 +76,20 @@ __global__ __launch_bounds__(kBlock, 2) void fisher_kernel(FisherArgs a) {
   }
 
   double t = 0.0;
-  fisher_sums<NPI, 1, ROT, false, EXPL, TAB>(ec, sc, n_site, 0, ec.n, L, &t);
+  const int len = EXPL ? ec.n : stretch_length(ec.n, kFisherStretch);     // an explicit grid has one form only
+  if (ec.n <= len) {
+    double x = 0.0;
+    fisher_sums<NPI, 1, ROT, false, EXPL, TAB>(ec, sc, n_site, 0, ec.n, L, &x);
+    t += x;
+  } else if (!EXPL) {                    // on its own: a loop around it costs short grids 2 %
+    for (int k0 = 0;; k0 += len) {
+      double x = 0.0;
+      fisher_sums<NPI, 1, ROT, false, EXPL, TAB>(ec, sc, n_site, k0, k0 + min(ec.n - k0, len), L, &x);
+      t += x;
+      if (ec.n - k0 <= len) break;
+      __syncthreads();                   // the next stretch's sums take the same LDS
+    }
+  }
   if (tid < NACC) {
     int r, c;
     slot_position(tid, NPI, r, c);
@@ -126,12 +139,19 @@ __global__ __launch_bounds__(kBlock) void snr_kernel(SnrArgs a) {
       for (int i = tid; i < n_ifo; i += kBlock) a.snr_ifo[(int64_t)i * a.n + e] = 0.0;
     return;
   }
-  double acc[kSnrSlots];
-#pragma unroll
-  for (int i = 0; i < kSnrSlots; ++i) acc[i] = 0.0;
-  snr_sums<ROT, EXPL, true>(ec, sc, n_site, 0, ec.n, acc);
+  const uint32_t shapes = site_shapes(a.net);
   double t = 0.0;
-  snr_reduce(acc, n_site, n_ifo, site_shapes(a.net), red, &t);
+  const int len = EXPL ? ec.n : stretch_length(ec.n, kSnrStretch);
+  for (int k0 = 0;; k0 += len) {
+    double acc[kSnrSlots], x = 0.0;
+#pragma unroll
+    for (int i = 0; i < kSnrSlots; ++i) acc[i] = 0.0;
+    snr_sums<ROT, EXPL, true>(ec, sc, n_site, k0, k0 + min(ec.n - k0, len), acc);
+    snr_reduce(acc, n_site, n_ifo, shapes, red, &x);
+    t += x;
+    if (EXPL || ec.n - k0 <= len) break;
+    __syncthreads();                     // the next stretch's sums take the same LDS
+  }
   if (tid < n_ifo) {
     if (a.active && !a.active[(int64_t)tid * a.ld + e]) t = 0.0;   // off for this event
     if (a.snr_ifo) a.snr_ifo[(int64_t)tid * a.n + e] = sqrt(t);

@@ -176,6 +176,11 @@ __host__ __device__ inline bool net_has_tables(const NetDesc& nd) {
   return false;
 }
 
+// The set-up below is compiled into many kernels, and an event has to get the
+// same constants, bit for bit, in all of them: products and sums are fused by
+// how they are written here, not as each kernel's code generation finds best.
+#pragma clang fp contract(on)
+
 // ------------------------------------------------ per-event coefficients
 // Coefficients a_k (k = 0..7), b_5, b_6 (ln v parts) and tidal a_10, a_12 of
 // the TaylorF2 phase Psi_PN = 3/(128 eta) v^-5 sum_k (a_k + b_k ln v) v^k,
@@ -736,6 +741,8 @@ __host__ __device__ inline uint32_t select_ifo(uint32_t arms, const NetDesc& net
   return (k >= 0 && k < na) ? (arms & (1u << k)) : 0u;
 }
 
+#pragma clang fp contract(fast)
+
 // ---------------------------------------------------------- sin and cos
 // sin and cos of a moderate angle (|x| < 1e5): Cody-Waite reduction by pi/2
 // with a three-part constant, then the Taylor series of sin (to x^17) and
@@ -1150,6 +1157,15 @@ struct SiteTrigR {
   double u, w;                  // 2 pi f dDelta/dH, 2 pi f dDelta/dtheta
 };
 
+// cos and sin of the hour angle from a site's (cos, sin) of its longitude less
+// phi, every product's rounding written out: left to the compiler, which of the
+// two products of a sum is fused changes from kernel to kernel, and the same
+// point would have other bits in each.
+__host__ __device__ inline void hour_angle(const Point& q, double cdl, double sdl, double& cH, double& sH) {
+  cH = fma(q.cth, cdl, -(q.sth * sdl));
+  sH = fma(q.sth, cdl, q.cth * sdl);
+}
+
 __host__ __device__ inline void trig_basis(double cH, double sH, double r, SiteTrigR& sp) {
   sp.r = r;
   sp.rc = r * cH;
@@ -1161,8 +1177,8 @@ __host__ __device__ inline void trig_basis(double cH, double sH, double r, SiteT
 
 template <bool MIXED = false, bool TAB = true>
 __host__ __device__ inline void site_trig_root(const SiteC& sc, const Point& q, SiteTrigR& sp) {
-  const double cH = q.cth * sc.cdl - q.sth * sc.sdl;
-  const double sH = q.sth * sc.cdl + q.cth * sc.sdl;
+  double cH, sH;
+  hour_angle(q, sc.cdl, sc.sdl, cH, sH);
   trig_basis(cH, sH, MIXED ? psd_root_weight_f32<TAB>(sc, q) : psd_root_weight<TAB>(sc, q), sp);
   sp.u = q.tf * (-sc.k1 * sH);
   sp.w = fma(q.tf, sc.k1t * cH, q.tf * sc.k0t);
@@ -1278,8 +1294,8 @@ __host__ __device__ inline void site_sums(const AmpFactors& am, const Point (&q)
     loads_ahead();
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
-      const double cH = q[i].cth * hd.cdl - q[i].sth * hd.sdl;
-      const double sH = q[i].sth * hd.cdl + q[i].cth * hd.sdl;
+      double cH, sH;
+      hour_angle(q[i], hd.cdl, hd.sdl, cH, sH);
       trig_basis(cH, sH, site_root<MIXED, TAB>(st, hd, q[i]), sp[i]);
       sp[i].u = q[i].tf * (-hd.k1 * sH);
       sp[i].w = fma(q[i].tf, hd.k1t * cH, q[i].tf * hd.k0t);

@@ -60,8 +60,8 @@ __host__ __device__ inline void snr_lane(const EventC& ec, const SiteC* sc, int 
         double om[NQ];
 #pragma unroll
         for (int i = 0; i < NQ; ++i) {
-          const double cH = fma(q[i].cth, st.cdl, -(q[i].sth * st.sdl));
-          const double sH = fma(q[i].sth, st.cdl, q[i].cth * st.sdl);
+          double cH, sH;
+          hour_angle(q[i], st.cdl, st.sdl, cH, sH);
           trig_basis(cH, sH, 1.0, sp[i]);
           om[i] = psd_weight<TAB>(st, q[i], EXPL ? q[i].w4A2 : q[i].rw * q[i].rw);
         }

@@ -25,6 +25,9 @@
 
 using namespace gwf;
 
+static_assert(kFisherStretch == GWF_FISHER_STRETCH && kSnrStretch == GWF_SNR_STRETCH &&
+              kMaxStretches == GWF_SPLIT_PARTS_MAX, "stretches as declared");
+
 namespace {
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
