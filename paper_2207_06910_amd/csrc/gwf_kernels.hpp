@@ -143,6 +143,7 @@ struct WaveformArgs {
   int32_t* status;          // [n] or NULL
   double* dh;               // derivative kernel: [P][n_ifo][total] complex
   const uint32_t* par_mask; // derivative kernel: [n] or NULL, rows outside an event's set are 0
+  int32_t share, longest;   // parts of a short grid, and the most runs of a part of a long one (wave_part)
   int64_t base;             // first event of the launch (set by the launcher)
 };
 

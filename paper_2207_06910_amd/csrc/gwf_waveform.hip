@@ -10,7 +10,7 @@
 // multiply-add), and only the final fraction in [-1/2, 1/2] goes through
 // sin/cos.
 //
-// One or several workgroups per event (wave_parts), lanes over grid points:
+// One or several workgroups per event (wave_part), lanes over grid points:
 // each interferometer's output row is written with consecutive lanes on
 // consecutive 16-byte complex values.
 // What bounds it: the output's writes, 4.5 TB/s on 3.1 GB (a fill of 4 GiB
@@ -47,7 +47,8 @@ __global__ __launch_bounds__(kWBlock) void waveform_kernel(WaveformArgs a) {
   const int n_site = a.net.n_site;
   // a site: its hour angle and delay, and its computed arms' patterns (the arms
   // themselves, kArmsPlain) times the inclination factors; pi M does not enter
-  const bool some = wave_setup(a, e, TIDAL, flags | a.ecc_flag, ec, ok, [&](int s, const double* p) {
+  int32_t k0 = 0, k1 = 0;
+  const bool some = wave_setup(a, e, TIDAL, flags | a.ecc_flag, ec, ok, k0, k1, [&](int s, const double* p) {
     SiteC sc;
     SiteDesc sd = a.net.site[s];
     sd.psd_kind = 0;                     // the noise curve plays no part
@@ -70,16 +71,9 @@ __global__ __launch_bounds__(kWBlock) void waveform_kernel(WaveformArgs a) {
   const double amp0 = exp(ec.lnA);
   double2* __restrict__ out = reinterpret_cast<double2*>(a.h) + base;
   const int64_t row = a.total;
-  // point 0 sits sh places past a 128-byte line of the rows
-  const int sh = (int)(a.offsets[e] & 7);
-  // A workgroup takes one stretch of whole runs of kWBlock points.  With runs
-  // dealt out in turn the line that two of them share was completed by
-  // workgroups on two XCDs wherever a row is not line-aligned (packed rows of
-  // odd length): 3000 packed pairs 726 -> 609 us, 10^4 1.89 -> 1.75 ms.
-  const int parts = (int)gridDim.y, runs = (ec.n + sh + kWBlock - 1) / kWBlock;
-  const int len = (runs + parts - 1) / parts * kWBlock;
-  const int k1 = min(ec.n, len * ((int)blockIdx.y + 1) - sh);
-  for (int k = len * (int)blockIdx.y + tid - sh; k < k1; k += kWBlock) {
+  // (counted in 32 bits without a sign: a grid may end within a run of 2^31)
+  for (uint32_t u = tid, end = (uint32_t)k1 - (uint32_t)k0; u < end; u += kWBlock) {
+    const int k = (int)((uint32_t)k0 + u);
     if (k < 0) continue;
     // explicit grids: ln v = (ln(pi M) + ln f)/3 from the given frequency
     const double L = EXPL ? (ec.lnpiM + log(ec.fx[k])) / 3.0 : fma((double)k, ec.dlnv, ec.lnv0);
@@ -153,9 +147,12 @@ void launch_waveform_t(const WaveformArgs& a, bool tidal, bool rot, dim3 grid, d
 }
 
 // An explicit grid (a.gf set) selects the instantiations that read it.
-hipError_t launch_waveform(const WaveformArgs& a0, bool tidal, bool rot, bool mixed, hipStream_t stream) {
+hipError_t launch_waveform(const WaveformArgs& args, bool tidal, bool rot, bool mixed, hipStream_t stream) {
+  WaveformArgs a0 = args;
+  a0.share = wave_share(a0.n, 1024);
+  a0.longest = 16;
   return launch_slices(a0, a0.n, 1, kWBlock, [&](const WaveformArgs& a, dim3 grid, dim3 block) {
-    grid.y = wave_parts(a.n);
+    grid.y = (unsigned)std::min<int64_t>(64, std::max<int64_t>({2, a.share, (4096 + a.n - 1) / a.n}));
     if (a.gf) {
       if (mixed) launch_waveform_t<true, true>(a, tidal, rot, grid, block, stream);
       else launch_waveform_t<false, true>(a, tidal, rot, grid, block, stream);

@@ -11,19 +11,59 @@ namespace gwf {
 
 constexpr int kWBlock = 256;
 
-// Workgroups per event: a small catalogue's grids are shared out, so that about
-// 2048 workgroups are there, and two in a large one, whose longest grids would
-// otherwise end the launch alone.  Measured, one workgroup per event and this:
-// strain of 600 neutron-star pairs 183 and 124 us, derivatives of 64 events 347
-// and 148 us.
-// A workgroup's points start on a 128-byte line of the first row (eight complex
-// values): where the row length is a multiple of eight, a wavefront's 1 KB store
-// is then whole lines, while a run that starts inside one leaves the shared
-// line to be completed by the next run.  Strain of 4000 pairs (3.1 GB) 825 ->
-// 697 us, derivatives of 300 (3.0 GB) 904 -> 616 us.  Stores past the caches
-// (non-temporal) were slower: 948 and 881 us.
-inline unsigned wave_parts(int64_t n) {
-  return (unsigned)std::min<int64_t>(64, std::max<int64_t>((2048 + n - 1) / n, 2));
+// A workgroup takes one part of an event's grid, whole runs of kWBlock points.
+// The first point sits sh = offset mod 8 places past a 128-byte line of the rows
+// and runs start on lines (eight complex values): where the row length is a
+// multiple of eight, a wavefront's 1 KB store is then whole lines, while a run
+// that starts inside one leaves the shared line to be completed by the next
+// run.  Strain of 4000 pairs (3.1 GB) 825 -> 697 us, derivatives of 300 (3.0 GB)
+// 904 -> 616 us.  Stores past the caches (non-temporal) were slower: 948 and
+// 881 us.  Parts are stretches, not runs dealt out in turn, whose shared lines
+// two XCDs complete wherever a row is not line-aligned: strain of 10^4 packed
+// pairs 1.89 -> 1.75 ms, derivatives of 1000 3.13 -> 2.87 ms.
+//
+// How many (wave_part): a part pays for a set-up, that of about 1000 points.  A
+// grid is cut into `share` parts, which share the idle chip out while the events
+// alone do not fill it, and beyond that only into parts of `longest` runs, so
+// that no long grid ends the launch alone.  The launchers choose:
+//   strain       share 1024 / n (the workgroups that run at once), longest 16
+//   derivatives  share 2048 / n below 512 events, else 1; longest 4: they write
+//                11 to 14 times as much per point, so a set-up weighs less;
+//                above 8192 events one part each
+// Measured with one part, two and this: strain of 20000 black-hole pairs of
+// 1000 points 374, 424 and 273 us (short grids, one part), of 300 and of 10^4
+// neutron-star pairs 148, 95 and 68 us, 1.87, 1.70 and 1.70 ms; derivatives of
+// 2000 pairs of 300 points 54, 79 and 50 us, of 64 ragged events 347 (one part)
+// and 146 us, of 10^4 pairs of 2000 points 643 and 748 us with one and two.
+inline int32_t wave_share(int64_t n, int64_t full) {
+  return (int32_t)std::min<int64_t>(64, std::max<int64_t>(full / n, 1));
+}
+
+// Part `part` of at most `parts` of a grid of n points whose first sits sh places
+// past a line: its points [k0, k1), k0 below 0 where the first run starts before
+// the grid; false where it has none.
+__host__ __device__ inline bool wave_part(int32_t n, int32_t sh, int32_t part, int32_t parts, int32_t share,
+                                          int32_t longest, int32_t& k0, int32_t& k1) {
+  const int32_t runs = (int32_t)(((int64_t)n + sh + kWBlock - 1) / kWBlock);
+  int32_t m = runs < share ? runs : share;                 // the parts taken, of even length
+  if (m * longest < runs) m = (runs - 1) / longest + 1;
+  if (m > parts) m = parts;
+  if (m <= 1) {
+    k0 = -sh;
+    k1 = n;
+    return part == 0;
+  }
+  if (part >= m) return false;
+  const int32_t each = runs / m, more = runs - each * m;
+  const int32_t r0 = part * each + (part < more ? part : more), r1 = r0 + each + (part < more ? 1 : 0);
+  k0 = (int32_t)((int64_t)r0 * kWBlock - sh);
+  k1 = r1 == runs ? n : (int32_t)((int64_t)r1 * kWBlock - sh);
+  return true;
+}
+
+// Whether wave_part has nothing for the part, without its divisions.
+__host__ __device__ inline bool wave_part_empty(int32_t n, int32_t sh, int32_t part, int32_t share, int32_t longest) {
+  return (int64_t)part * (part < share ? 1 : longest) * kWBlock >= (int64_t)n + sh;
 }
 
 // Event e's inputs: the 13 parameters (no tidal rows without tides), e0 and
@@ -38,13 +78,16 @@ __device__ inline void load_event(const WaveformArgs& a, int64_t e, bool tidal, 
 // the grid, with the check that the event's columns [b, b + npts) lie inside
 // a row of the output, and the status; wavefront 1 calls site(s, p) on one lane
 // per site; wavefronts 2 and 3 the phase and angle series.  False (for the
-// whole workgroup) if there is nothing to write; a workgroup beyond the
-// event's points leaves before any of it.
+// whole workgroup) if there is nothing to write; a workgroup that can have
+// no points of the event leaves before any of it.
 template <class Site>
 __device__ inline bool wave_setup(const WaveformArgs& a, int64_t e, bool tidal, uint32_t flags, EventC& ec,
-                                  int32_t& ok, const Site& site) {
+                                  int32_t& ok, int32_t& k0, int32_t& k1, const Site& site) {
   const int tid = threadIdx.x;
-  if (blockIdx.y > 0 && (int64_t)blockIdx.y * kWBlock >= a.npts[e] + (int64_t)(a.offsets[e] & 7)) return false;
+  const int32_t part = (int32_t)blockIdx.y;
+  // (the first workgroup stays for the status, and does not wait for the grid's
+  // length)
+  if (part > 0 && wave_part_empty(a.npts[e], (int32_t)(a.offsets[e] & 7), part, a.share, a.longest)) return false;
   double p[kNparIn];
   load_event(a, e, tidal, p);
   if (tid == 0) {
@@ -63,7 +106,8 @@ __device__ inline bool wave_setup(const WaveformArgs& a, int64_t e, bool tidal, 
     event_setup_grid(p, a.fmin, a.fmax, a.npts, a.goff, a.gf, e, flags, ec, kSetupAngle);
   }
   __syncthreads();
-  return ok != 0;
+  return ok != 0 &&
+         wave_part(ec.n, (int32_t)(a.offsets[e] & 7), part, (int32_t)gridDim.y, a.share, a.longest, k0, k1);
 }
 
 // x reduced to [-1/2, 1/2] by subtracting the nearest integer (exact).

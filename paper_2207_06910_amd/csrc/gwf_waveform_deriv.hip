@@ -16,7 +16,7 @@ namespace {
 // (Phic, chi1z, chi2z[, Lambda1, Lambda2][, e0]); the phase in cycles exactly as
 // for the strain.  D is a combination of Q, iQ, Z and Y (NetSums), so a point
 // turns those three complex numbers by the phase and the rows follow by real
-// coefficients.  One or several workgroups per event (wave_parts), lanes over
+// coefficients.  One or several workgroups per event (wave_part), lanes over
 // grid points; row (a, i) of dh holds parameter a at interferometer i,
 // consecutive lanes on consecutive complex values.  FP64 only.
 // What bounds it: the output's writes, 4.9 TB/s on 3.0 GB of 300 neutron-star
@@ -73,7 +73,8 @@ __global__ __launch_bounds__(kWBlock) void waveform_deriv_kernel(WaveformArgs a)
   const int64_t e = a.base + blockIdx.x;
   const int tid = threadIdx.x;
   const int n_site = a.net.n_site;
-  const bool some = wave_setup(a, e, TIDAL, flags, ec, ok, [&](int s, const double* p) {
+  int32_t k0 = 0, k1 = 0;
+  const bool some = wave_setup(a, e, TIDAL, flags, ec, ok, k0, k1, [&](int s, const double* p) {
     SiteDesc sd = a.net.site[s];
     sd.psd_kind = 0;                     // the noise curve plays no part, nor does pi M
     site_setup(p, sd, 1.0, sc[s], kArmsPlain);
@@ -87,17 +88,9 @@ __global__ __launch_bounds__(kWBlock) void waveform_deriv_kernel(WaveformArgs a)
   double2* __restrict__ out = reinterpret_cast<double2*>(a.dh) + a.offsets[e];
   const int64_t row = a.total;
   const int64_t prow = (int64_t)a.net.n_ifo * row;     // one parameter's block of rows
-  // point 0 sits sh places past a 128-byte line of the rows
-  const int sh = (int)(a.offsets[e] & 7);
-  // one stretch of whole runs a workgroup, the runs shared out evenly: dealt
-  // out in turn, two XCDs completed a shared line wherever a row is not
-  // line-aligned.  Derivatives of 1000 packed pairs 3.13 -> 2.87 ms, of 64
-  // events 149 -> 141 us.
-  const int part = (int)blockIdx.y, parts = (int)gridDim.y, runs = (ec.n + sh + kWBlock - 1) / kWBlock;
-  const int each = runs / parts, more = runs - each * parts;
-  const int r0 = part * each + min(part, more), r1 = r0 + each + (part < more ? 1 : 0);
-  const int k1 = min(ec.n, r1 * kWBlock - sh);
-  for (int k = r0 * kWBlock + tid - sh; k < k1; k += kWBlock) {
+  // (counted in 32 bits without a sign: a grid may end within a run of 2^31)
+  for (uint32_t u = tid, end = (uint32_t)k1 - (uint32_t)k0; u < end; u += kWBlock) {
+    const int k = (int)((uint32_t)k0 + u);
     if (k < 0) continue;
     // the event and site constants are re-read from LDS (uniform broadcast
     // reads) rather than held in registers across iterations
@@ -164,9 +157,12 @@ void launch_deriv_t(const WaveformArgs& a, int npi, bool rot, dim3 grid, dim3 bl
   }
 }
 
-hipError_t launch_waveform_deriv(const WaveformArgs& a0, int npi, bool rot, hipStream_t stream) {
+hipError_t launch_waveform_deriv(const WaveformArgs& args, int npi, bool rot, hipStream_t stream) {
+  WaveformArgs a0 = args;
+  a0.share = a0.n < 512 ? wave_share(a0.n, 2048) : 1;
+  a0.longest = 4;
   return launch_slices(a0, a0.n, 1, kWBlock, [&](const WaveformArgs& a, dim3 grid, dim3 block) {
-    grid.y = a.n >= 8192 ? 1u : wave_parts(a.n);
+    grid.y = a.n < 512 ? (unsigned)a.share : (unsigned)((8192 + a.n - 1) / a.n);
     if (a.gf) launch_deriv_t<true>(a, npi, rot, grid, block, stream);
     else launch_deriv_t<false>(a, npi, rot, grid, block, stream);
   });
