@@ -12,8 +12,9 @@
 //
 // Condition number.  The eigenvalues of a positive definite normalised matrix
 // G^ = L L^T are the squares of the singular values of L (its Cholesky factor,
-// formed for the inversion); of any other matrix, and where singular vectors
-// are wanted, the |eigenvalues| are the matrix's own singular values.  Either
+// formed for the inversion); of any other matrix, and where the inverse is taken
+// from the singular vectors, the |eigenvalues| are the matrix's own singular
+// values.  Either
 // are found by one-sided (Hestenes) Jacobi: at each step the columns are
 // paired by a round-robin schedule, each lane fetches its partner's column
 // (exchange_column), and both lanes of a pair compute the same rotation from
@@ -257,16 +258,16 @@ __global__ __launch_bounds__(kInvBlock, 3) void invert_kernel(InvertArgs a) {
   __syncthreads();
 
   // ---- condition number: one-sided Jacobi on the columns of the Cholesky
-  // factor, or of the normalised matrix where it has none.  A wavefront that
-  // holds a matrix the SVD below inverts, or whose eigen-decomposition is
-  // wanted, accumulates the rotations V as well (H V = X), so that the SVD
-  // needs no second Jacobi; X and the condition number come out the same
-  // either way.
+  // factor, or of the normalised matrix where it has none (and for the inverses
+  // by SVD alone).  A wavefront that holds a matrix the SVD below inverts, or
+  // whose eigen-decomposition is wanted, accumulates the rotations V as well
+  // (H V = X), so that the SVD needs no second Jacobi; X and the condition number
+  // come out the same either way.
   const bool want_eig = a.eigval != nullptr || a.eigvec != nullptr;
   const bool need_v =
       __any(go0 && (a.method == 2 || a.method == 3 || (a.method == 1 && !pd))) || want_eig;
   double x[P];
-  const bool factor = go0 && pd && a.method != 2 && a.method != 3 && !want_eig;
+  const bool factor = go0 && pd && a.method != 2 && a.method != 3;
 #pragma unroll
   for (int i = 0; i < P; ++i) x[i] = !factor ? h[i] : i < j || j >= P ? 0.0 : i == j ? ljj : l[i];
   double cond;
@@ -308,7 +309,9 @@ __global__ __launch_bounds__(kInvBlock, 3) void invert_kernel(InvertArgs a) {
     // above with the rotations V accumulated: H V = X = U diag(s) with
     // orthonormal U and V; then H^-1 = V diag(w) U^T with w = 1/s (or the
     // paper's truncated or dropped small singular values), and eigenvalue
-    // j = sign(u_j . v_j) s_j with eigenvector v_j.  Only wavefronts holding
+    // j = sign(u_j . v_j) s_j with eigenvector v_j (of a factor's Jacobi, s_j^2
+    // with u_j: the condition number is then the same as without the
+    // eigen-decomposition).  Only wavefronts holding
     // such a matrix run it (need_v held for them).
     const bool svd_grp = go0 && !ill && (a.method == 2 || a.method == 3 || (a.method == 1 && !pd));
     if (__any(svd_grp) || want_eig) {
@@ -327,7 +330,7 @@ __global__ __launch_bounds__(kInvBlock, 3) void invert_kernel(InvertArgs a) {
       const double inv_s = sj > 0.0 ? 1.0 / sj : 0.0;
 #pragma unroll
       for (int i = 0; i < P; ++i) x[i] *= inv_s;                    // u_j
-      const double lam = col_dot<P>(x, vs) >= 0.0 ? sj : -sj;
+      const double lam = factor ? sj * sj : col_dot<P>(x, vs) >= 0.0 ? sj : -sj;
 
       if (want_eig) {
         // ascending position of this eigenvalue; eigenvector signed so that
@@ -338,10 +341,13 @@ __global__ __launch_bounds__(kInvBlock, 3) void invert_kernel(InvertArgs a) {
           const double lm = __shfl(lam, m, kGroup);
           if (lm < lam || (lm == lam && m < j)) ++rank;
         }
+        // the factor's left singular vectors u_j are the matrix's eigenvectors
         double bv = -1.0, bs = 1.0;
 #pragma unroll
-        for (int i = 0; i < P; ++i)
+        for (int i = 0; i < P; ++i) {
+          if (factor) vs[i] = x[i];
           if (fabs(vs[i]) > bv) { bv = fabs(vs[i]); bs = vs[i]; }
+        }
         const double fl = bs < 0.0 ? -1.0 : 1.0;
         if (live && j < P) {
           if (a.eigval) a.eigval[(int64_t)rank * a.n + e] = go0 ? lam : nan;
