@@ -483,7 +483,9 @@ def fom_terms(snr, inv, P, w_snr, w_logdet, want_gbar=True, stream=None):
     n, dev = snr.shape[0], snr.device
     full = len(inv["out"]) == P
     gbar = torch.empty((P, P, n), dtype=torch.float64, device=dev) if want_gbar and not full else None
-    work = torch.empty(FOM_WORK, dtype=torch.float64, device=dev)
+    # freed on return: it belongs to the call's stream, which may still be using it
+    with torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext():
+        work = torch.empty(FOM_WORK, dtype=torch.float64, device=dev)
     J = torch.empty((), dtype=torch.float64, device=dev)
     _check(load().gwf_fom(P, n, sum(1 << i for i in inv["out"]), _ptr(snr), _ptr(inv["logdet"]),
                           _ptr(inv["status"]), _ptr(inv["cov"]) if gbar is not None else None, w_snr, w_logdet,
