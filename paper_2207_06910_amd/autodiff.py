@@ -54,7 +54,13 @@ def _forward(dw, xi, w_snr, w_logdet, rows, cond_max, plan=None, want_gbar=False
     # parameter set (par_mask) is honoured by the inversion
     fixed = () if rows is None else [i for i in range(P) if i not in set(int(k) for k in rows)]
     inv = binding.covariance(F, r["status"], fixed=fixed, cond_max=cond_max, par_mask=dwx.par_mask)
-    J, gbar = binding.fom_terms(r["snr"], inv, P, float(w_snr), float(w_logdet), want_gbar)
+    import torch
+    if torch.is_tensor(w_snr) or torch.is_tensor(w_logdet):     # weights with a shape or a gradient of their own
+        ok = inv["status"] == 0
+        J = (w_snr * torch.log(r["snr"][ok]).sum() + w_logdet * inv["logdet"][ok].sum()).to(torch.float64)
+        gbar = binding.fom_terms(r["snr"], inv, P, 1.0, 1.0)[1] if want_gbar else None
+    else:
+        J, gbar = binding.fom_terms(r["snr"], inv, P, float(w_snr), float(w_logdet), want_gbar)
     return dwx, inv, J, gbar
 
 
@@ -91,6 +97,7 @@ def network_fom(xi, dw, w_snr=1.0, w_logdet=1.0, rows=None, cond_max=1e13, plan=
 
 
 def network_fom_value(xi, dw, w_snr=1.0, w_logdet=1.0, rows=None, cond_max=1e13):
-    """J(xi) without gradient bookkeeping, and the mask of events that entered."""
+    """J(xi) without gradient bookkeeping along xi, and the mask of events that
+    entered.  The weights may be tensors: J then has their shape and gradient."""
     _, inv, J, _ = _forward(dw, xi, w_snr, w_logdet, None if rows is None else tuple(rows), float(cond_max))
     return J, inv["status"] == 0
