@@ -585,8 +585,9 @@ gwf_status gwf_plan_fisher(gwf_plan* plan, double* fisher, double* snr, int32_t*
  * (one stream, or synchronised).  The first call on a plan allocates the
  * adjoint's constants (the contractions of each event's Gbar, about 1 KB per
  * event, and each site's pattern-derivative polynomials, about 0.7 KB per
- * event and site), and shorter work items of the adjoint's own where the
- * plan's would leave it few, kept with the plan until gwf_plan_destroy and
+ * event and site), and, the first time outside a capture, shorter work items of
+ * the adjoint's own where the plan's would leave it few (their upload waits for
+ * the device), kept with the plan until gwf_plan_destroy and
  * counted in gwf_plan_info's workspace_bytes; later calls allocate nothing.
  * Returns GWF_E_NOMEM if the constants cannot be allocated (without memory for
  * its own items it takes the plan's). */

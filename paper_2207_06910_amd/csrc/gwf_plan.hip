@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -48,6 +49,7 @@ struct gwf_plan {
   int32_t* adj_first = nullptr;
   double* adj_partial = nullptr;
   int adj_n_items = 0;
+  bool adj_split = false;           // split_adjoint has been called
   int64_t workspace_bytes = 0;
   // graph cache, keyed by the output pointers of the last replay
   hipStream_t cap = nullptr;
@@ -122,9 +124,10 @@ gwf_status set_items(gwf_plan* p, int chunk) {
 // 1.20 / 0.88 ms; units of 512 points 0.18 ms at 100 events; two or six rounds
 // 0.66 and 0.65 ms at 1000.  From about 5e7 points on (10^4 events) the plan's
 // items are short enough and are taken as they are.
-// Without memory for its own items the adjoint takes the plan's.
+// Without memory for its own items, and while the stream is being captured (the
+// upload would end the capture), the adjoint takes the plan's.
 constexpr int64_t kAdjointGroups = 3072, kAdjointUnit = 1024;
-void split_adjoint(gwf_plan* p) {
+void split_adjoint(gwf_plan* p) try {
   int64_t points = 0;
   for (int32_t n : p->npts_host) points += n >= 2 ? n : 2;
   const int64_t len = (points / kAdjointGroups / kAdjointUnit + 1) * kAdjointUnit;
@@ -150,6 +153,17 @@ void split_adjoint(gwf_plan* p) {
   p->adj_items = nullptr;
   p->adj_first = nullptr;
   p->adj_partial = nullptr;
+} catch (const std::bad_alloc&) {   // no host memory for the list
+}
+
+// Whether a capture runs on s.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
 }
 
 struct Outs {
@@ -405,6 +419,9 @@ gwf_status gwf_plan_adjoint(gwf_plan* p, const double* gbar, const int32_t* stat
       return api_fail(GWF_E_NOMEM, "adjoint constants of %lld events", (long long)p->n);
     }
     p->workspace_bytes += (int64_t)((size_t)p->n * (adjoint_event_bytes() + p->n_site_alloc * adjoint_site_bytes()));
+  }
+  if (!p->adj_split && !capturing(s)) {
+    p->adj_split = true;
     split_adjoint(p);
   }
   err = launch_setup(sa, s);
