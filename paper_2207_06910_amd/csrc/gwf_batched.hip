@@ -105,8 +105,8 @@ __global__ __launch_bounds__(kBlock, 2) void items_kernel(ItemsArgs a) {
     w.e = (int32_t)(u - row * n);
     const int32_t ne = a.evc[w.e].n, len = part_length(ne, a.parts, kFisherStretch);
     w.k0 = part * len;
-    w.k1 = min(ne, w.k0 + len);
     if (a.evc[w.e].status || w.k0 >= ne) return;   // its sums are not read
+    w.k1 = w.k0 + min(ne - w.k0, len);
     w.slot = ((int32_t)mat * a.n + w.e) * a.parts + part;
     n_set = a.n_set;
     if (a.n_mat > 1) set0 = (int32_t)mat;
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(kBlock, 2) void snr_parts_kernel(SnrPartsArgs a) {
   double acc[kSnrSlots];
 #pragma unroll
   for (int i = 0; i < kSnrSlots; ++i) acc[i] = 0.0;
-  snr_sums<ROT, false, TAB>(ec, sc, a.net.n_site, k0, min(ec.n, k0 + len), acc);
+  snr_sums<ROT, false, TAB>(ec, sc, a.net.n_site, k0, k0 + min(ec.n - k0, len), acc);
   double t;
   snr_reduce(acc, a.net.n_site, a.net.n_ifo, site_shapes(a.net), red, &t);
   if ((int)threadIdx.x < a.net.n_ifo) a.partial[((int64_t)e * a.parts + part) * a.net.n_ifo + threadIdx.x] = t;

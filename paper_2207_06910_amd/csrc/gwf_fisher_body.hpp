@@ -169,7 +169,7 @@ __device__ inline void fisher_sums(const EventC& ec, const SiteC* sc, int n_site
   // on a log grid, v, 1/v and v^-12.42 walk from point to point (GridWalk)
   GridWalk gw;
   if (!EXPL) {
-    gw.start(ec, k0 + tid < k1 ? k0 + tid : k1 - 1, kBlock);
+    gw.start(ec, point_past(k0, tid, k1) ? k1 - 1 : k0 + tid, kBlock);
 #pragma unroll
     for (int i = 0; i < 3; ++i) gw.ratio[i] = uniform_d(gw.ratio[i]);   // the same step in every lane
   }
@@ -210,12 +210,12 @@ __device__ inline void fisher_sums(const EventC& ec, const SiteC* sc, int n_site
   act.list = (uint32_t)__builtin_amdgcn_readfirstlane((int)act.list);
   act.n = __builtin_amdgcn_readfirstlane(act.n);
 #pragma unroll 1
-  for (int kb = k0; kb < k1; kb += NQ * kBlock) {
+  for (uint32_t kb = k0; kb < (uint32_t)k1; kb += NQ * kBlock) {
     // The per-event constants are re-read every iteration (uniform reads);
     // hoisting them out of the loop would need more registers than a lane has.
     __asm__ volatile("" ::: "memory");
-    const int k = kb + tid;
-    const bool inner = kb > 0 && kb + NQ * kBlock < k1;
+    const int k = (int)(kb + tid);
+    const bool inner = kb > 0 && kb + NQ * kBlock < (uint32_t)k1;
     double vv[NQ][3];
     if (!EXPL) walk_points<NQ>(ec, gw, k, kBlock, k1, inner, vv);
     Point q[NQ];

@@ -1455,6 +1455,12 @@ __host__ __device__ inline ActiveSites active_sites(const SiteC* sc, int n_site)
   return a;
 }
 
+// Whether the point k + d is kend or past it, without a sign: a grid may end
+// within a workgroup's points of 2^31.
+__host__ __device__ inline bool point_past(int32_t k, int32_t d, int32_t kend) {
+  return (uint32_t)k + (uint32_t)d >= (uint32_t)kend;
+}
+
 // The grid values, weights and sidereal angles of NQ points k, k + stride, ...
 // of an event, from vrec[NQ][3] (GridWalk; NULL: evaluated directly).  Points
 // at or past kend stand for the point kend - 1 (whose grid values the caller
@@ -1465,15 +1471,16 @@ __host__ __device__ inline void point_block(const EventC& ec, int32_t k, int32_t
                                             const double (*vrec)[3], Point (&q)[NQ]) {
 #pragma unroll
   for (int i = 0; i < NQ; ++i) {
-    int32_t ki = k + i * stride;
+    const bool past = !inner && point_past(k, i * stride, kend);
+    int32_t ki = (int32_t)((uint32_t)k + (uint32_t)(i * stride));
     if (!inner) {
       keep_branch();
-      if (ki >= kend) ki = kend - 1;
+      if (past) ki = kend - 1;
     }
     point_setup<EXPL, ECC>(ec, ki, false, ROT, q[i], MIXED ? kPsdF32 : kPsdF64, vrec ? vrec[i] : nullptr, inner);
     if (!inner) {
       keep_branch();
-      if (k + i * stride >= kend) q[i].rw = q[i].w4A2 = 0.0;
+      if (past) q[i].rw = q[i].w4A2 = 0.0;
     }
   }
 }
@@ -1493,7 +1500,7 @@ __host__ __device__ inline void walk_points(const EventC& ec, GridWalk& gw, int3
     keep_branch();
 #pragma unroll
     for (int i = 0; i < NQ; ++i)
-      if (k + i * stride >= k1) grid_values(ec, k1 - 1, vv[i]);
+      if (point_past(k, i * stride, k1)) grid_values(ec, k1 - 1, vv[i]);
   }
 }
 

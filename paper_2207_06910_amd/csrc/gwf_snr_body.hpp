@@ -37,19 +37,21 @@ __host__ __device__ inline void snr_lane(const EventC& ec, const SiteC* sc, int 
   constexpr int NQ = 2;
   GridWalk gw;
   if (!EXPL) {
-    gw.start(ec, k0 + tid < k1 ? k0 + tid : k1 - 1, kBlock);
+    gw.start(ec, point_past(k0, tid, k1) ? k1 - 1 : k0 + tid, kBlock);
 #pragma unroll
     for (int i = 0; i < 3; ++i) gw.ratio[i] = uniform_d(gw.ratio[i]);
   }
 #pragma unroll 1
-  for (int kb = k0; kb < k1; kb += NQ * kBlock) {
+  for (uint32_t kb = k0; kb < (uint32_t)k1; kb += NQ * kBlock) {
     asm volatile("" ::: "memory");       // constants are re-read rather than held in registers
-    const bool inner = kb > 0 && kb + NQ * kBlock < k1;
-    if (!EXPL && kb > k0 && (kb - k0) % kSnrWalk == 0) gw.anchor(ec, kb + tid < k1 ? kb + tid : k1 - 1);
+    const int k = (int)(kb + tid);
+    const bool inner = kb > 0 && kb + NQ * kBlock < (uint32_t)k1;
+    if (!EXPL && kb > (uint32_t)k0 && (kb - (uint32_t)k0) % kSnrWalk == 0)
+      gw.anchor(ec, point_past(k, 0, k1) ? k1 - 1 : k);
     double vv[NQ][3];
-    if (!EXPL) walk_points<NQ>(ec, gw, kb + tid, kBlock, k1, inner, vv);
+    if (!EXPL) walk_points<NQ>(ec, gw, k, kBlock, k1, inner, vv);
     Point q[NQ];
-    point_block<NQ, false, ROT, false, EXPL>(ec, kb + tid, kBlock, k1, inner, EXPL ? nullptr : vv, q);
+    point_block<NQ, false, ROT, false, EXPL>(ec, k, kBlock, k1, inner, EXPL ? nullptr : vv, q);
     const double cplus = ec.cplus, ccross = ec.ccross;
 #pragma unroll
     for (int s = 0; s < kMaxSites; ++s) {

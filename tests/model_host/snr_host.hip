@@ -4,13 +4,13 @@
 
 using namespace gwf;
 
-// SNR^2 sums [3 n_site] of the points lane tid takes of an event's whole grid,
-// walked (direct = 0), or of the same points one by one, each evaluated
+// SNR^2 sums [3 n_site] of the points lane tid takes of an event's grid from point
+// k0 on, walked (direct = 0), or of the same points one by one, each evaluated
 // directly; sites[s][7] = lat, lon, gamma, zeta, shape, S0, f0; tab_n > 0: every
 // site has the sampled curve (tab_f, tab_S) of that kind, scaled by its S0.
 extern "C" int snr_lane_host(const double* par, double fmin, double fmax, int32_t n, int n_site, const double* sites,
-                             int tid, int direct, int64_t tab_n, const double* tab_f, const double* tab_S, int kind,
-                             double* out) {
+                             int tid, int direct, int32_t k0, int64_t tab_n, const double* tab_f, const double* tab_S,
+                             int kind, double* out) {
   EventC ec;
   event_setup(par, fmin, fmax, n, kFlagRot, ec);
   if (ec.status) return ec.status;
@@ -28,9 +28,10 @@ extern "C" int snr_lane_host(const double* par, double fmin, double fmax, int32_
   }
   double acc[kSnrSlots] = {};
   if (!direct) {
-    snr_lane<true, false, true>(ec, sc, n_site, 0, ec.n, tid, acc);
+    snr_lane<true, false, true>(ec, sc, n_site, k0, ec.n, tid, acc);
   } else {
-    for (int32_t k = tid; k < ec.n; k += kBlock) snr_lane<true, false, true>(ec, sc, n_site, k, k + 1, 0, acc);
+    for (int64_t k = (int64_t)k0 + tid; k < ec.n; k += kBlock)
+      snr_lane<true, false, true>(ec, sc, n_site, (int)k, (int)k + 1, 0, acc);
   }
   for (int i = 0; i < 3 * n_site; ++i) out[i] = acc[i];
   return 0;

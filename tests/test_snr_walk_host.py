@@ -26,7 +26,7 @@ def host(tmp_path_factory):
     return ctypes.CDLL(lib)
 
 
-def _lane(host, wl, e, npts, tid, direct=0, curve=None, kind=1):
+def _lane(host, wl, e, npts, tid, direct=0, curve=None, kind=1, k0=0):
     sites = np.ascontiguousarray(wl.site_array())
     P = lambda a: None if a is None else a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
     par = np.zeros(15)
@@ -34,8 +34,8 @@ def _lane(host, wl, e, npts, tid, direct=0, curve=None, kind=1):
     out = np.zeros(3 * len(sites))
     f, S = (None, None) if curve is None else [np.ascontiguousarray(x) for x in curve]
     assert host.snr_lane_host(P(par), ctypes.c_double(2.0), ctypes.c_double(0.0), ctypes.c_int32(npts), len(sites),
-                              P(sites), tid, direct, ctypes.c_int64(0 if f is None else len(f)), P(f), P(S), kind,
-                              P(out)) == 0
+                              P(sites), tid, direct, k0, ctypes.c_int64(0 if f is None else len(f)), P(f), P(S),
+                              kind, P(out)) == 0
     return out
 
 
@@ -67,3 +67,16 @@ def test_sampled_values_without_a_root(host):
     inf[-1] = np.inf
     assert np.array_equal(_lane(host, wl, 0, 3000, 7, curve=(f[cut], inf)),
                           _lane(host, wl, 0, 3000, 7, curve=(f[cut][:-1], S[cut][:-1])))
+
+
+@pytest.mark.parametrize("npts", [2 ** 31 - 1, 2 ** 31 - 200, 2 ** 31 - 256, 2 ** 31 - 512, 2 ** 31 - 600])
+@pytest.mark.parametrize("left", [1, 200, 257, 1300])
+def test_the_longest_grids_end(host, npts, left):
+    """A range that ends within a workgroup's points of 2^31: the lanes past the
+    end have no points, and the loop stops."""
+    wl = synth.bns1e4(n=1, seed=5)
+    for tid in (0, 199, 255):
+        got, ref = (_lane(host, wl, 0, npts, tid, direct=d, k0=npts - left) for d in (0, 1))
+        on = ref > 0.0
+        assert on.any() == (tid < left)
+        assert np.array_equal(on, got > 0.0) and np.all(np.abs(got[on] / ref[on] - 1.0) <= 6.9e-14)
