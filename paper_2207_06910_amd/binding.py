@@ -173,6 +173,17 @@ def _stream(stream):
     return ctypes.c_void_p(s.cuda_stream)
 
 
+def _memory_of(stream):
+    """A context whose allocations belong to the call's stream (any object with
+    a ``cuda_stream``, None: the current stream)."""
+    import torch
+    if stream is None:
+        return contextlib.nullcontext()
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream or 0)
+    return torch.cuda.stream(stream)
+
+
 def _dev_f64(t):
     import torch
     if not (t.is_cuda and t.dtype == torch.float64 and t.is_contiguous()):
@@ -323,7 +334,7 @@ def _split(dw: DeviceWorkload, net, what, stream):
     # the workspace belongs to the call's stream: the allocator may hand it out
     # again once the stream has passed the call.  Under graph capture, and
     # without memory for it, the call runs as before it could be split.
-    with torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext():
+    with _memory_of(stream):
         if torch.cuda.is_current_stream_capturing():
             return None
         try:
@@ -484,7 +495,7 @@ def fom_terms(snr, inv, P, w_snr, w_logdet, want_gbar=True, stream=None):
     full = len(inv["out"]) == P
     gbar = torch.empty((P, P, n), dtype=torch.float64, device=dev) if want_gbar and not full else None
     # freed on return: it belongs to the call's stream, which may still be using it
-    with torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext():
+    with _memory_of(stream):
         work = torch.empty(FOM_WORK, dtype=torch.float64, device=dev)
     J = torch.empty((), dtype=torch.float64, device=dev)
     _check(load().gwf_fom(P, n, sum(1 << i for i in inv["out"]), _ptr(snr), _ptr(inv["logdet"]),
