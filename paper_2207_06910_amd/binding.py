@@ -246,7 +246,8 @@ class DeviceWorkload:
         self.fmin = torch.as_tensor(np.ascontiguousarray(wl.fmin), dtype=torch.float64, device=device)
         self.fmax = None if wl.fmax is None else torch.as_tensor(
             np.ascontiguousarray(wl.fmax), dtype=torch.float64, device=device)
-        self.npts = torch.as_tensor(np.ascontiguousarray(wl.npts), dtype=torch.int32, device=device)
+        npts = np.ascontiguousarray(wl.npts)
+        self.npts = torch.as_tensor(npts, dtype=torch.int32, device=device)
         self.tc_s = None if wl.tc_s is None else torch.as_tensor(
             np.ascontiguousarray(wl.tc_s), dtype=torch.float64, device=device)
         act = getattr(wl, "active", None)
@@ -270,7 +271,7 @@ class DeviceWorkload:
         self.n_ifo = n_ifo(self.sites)
         # the catalogue's longest grid and all its points, by which the plain
         # calls choose how they split the work (never what they compute)
-        self.points_max, self.points = int(np.max(wl.npts, initial=0)), int(np.sum(wl.npts, dtype=np.int64))
+        self.points_max, self.points = int(np.max(npts, initial=0)), int(np.sum(npts, dtype=np.int64))
 
     def with_sites(self, sites) -> "DeviceWorkload":
         """The same device arrays with another network of the same shapes
