@@ -479,9 +479,9 @@ gwf_status gwf_fisher_basis(int32_t P, int64_t n, const double* fisher, const gw
 /* gwf_snr, gwf_fisher and gwf_fisher_ifo with each event's grid split over
  * several workgroups, in a workspace the caller gives for the call: the same
  * outputs, statuses and thresholds, for log grids.  Both forms sum an event's
- * grid in stretches of GWF_FISHER_STRETCH or GWF_SNR_STRETCH points (times the
- * smallest whole number that leaves no more than GWF_SPLIT_PARTS_MAX of them),
- * so with as many parts as that the results are those of the plain calls bit
+ * grid in stretches of GWF_FISHER_STRETCH, GWF_SNR_STRETCH or (one matrix per
+ * interferometer) GWF_IFO_STRETCH points (times the smallest whole number that
+ * leaves no more than GWF_SPLIT_PARTS_MAX of them), so with as many parts as that the results are those of the plain calls bit
  * for bit, whatever the other events.  For few events, long grids or uneven ones, where one workgroup
  * per event leaves the chip idle; the set-up, part and combine kernels are
  * ordinary launches on `stream`, nothing is allocated or read back.
@@ -499,6 +499,7 @@ gwf_status gwf_fisher_basis(int32_t P, int64_t n, const double* fisher, const gw
 #define GWF_SPLIT_PARTS_MAX 64
 #define GWF_FISHER_STRETCH 3072
 #define GWF_SNR_STRETCH 4096
+#define GWF_IFO_STRETCH 4096
 
 int64_t gwf_split_bytes(int64_t n, const gwf_network* net, uint32_t flags, int32_t what, int32_t parts);
 

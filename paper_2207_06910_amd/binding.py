@@ -305,7 +305,7 @@ class DeviceWorkload:
 
 
 SPLIT_SNR, SPLIT_FISHER, SPLIT_SNR_FISHER, SPLIT_IFOS = 0, 1, 2, 3
-FISHER_STRETCH, SNR_STRETCH = 3072, 4096        # GWF_FISHER_STRETCH, GWF_SNR_STRETCH
+FISHER_STRETCH, SNR_STRETCH, IFO_STRETCH = 3072, 4096, 4096     # GWF_FISHER_STRETCH, ...
 SPLIT_WORK_MAX = 256 << 20      # bytes of workspace a plain call may take
 
 
@@ -328,7 +328,8 @@ def _split(dw: DeviceWorkload, net, what, stream):
     if dw.grid_f is not None or (few and dw.points_max <= short and (what != SPLIT_IFOS or dw.n_ifo == 1)):
         return None
     # as many parts as the longest grid has stretches (gwf_*_split)
-    parts = min(64, -(-dw.points_max // (SNR_STRETCH if what == SPLIT_SNR else FISHER_STRETCH)))
+    stretch = {SPLIT_SNR: SNR_STRETCH, SPLIT_IFOS: IFO_STRETCH}.get(what, FISHER_STRETCH)
+    parts = min(64, -(-dw.points_max // stretch))
     size = load().gwf_split_bytes(n, ctypes.byref(net), dw.flags, what, parts)
     if size < 0 or size > SPLIT_WORK_MAX:
         return None

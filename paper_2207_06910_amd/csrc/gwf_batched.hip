@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kBlock, 2) void items_kernel(ItemsArgs a) {
     const uint32_t row = u / n, mat = row / (uint32_t)a.parts;
     const int32_t part = (int32_t)(row - mat * (uint32_t)a.parts);
     w.e = (int32_t)(u - row * n);
-    const int32_t ne = a.evc[w.e].n, len = part_length(ne, a.parts, kFisherStretch);
+    const int32_t ne = a.evc[w.e].n, len = part_length(ne, a.parts, a.unit);
     w.k0 = part * len;
     if (a.evc[w.e].status || w.k0 >= ne) return;   // its sums are not read
     w.k1 = w.k0 + min(ne - w.k0, len);
@@ -153,7 +153,7 @@ __global__ void combine_kernel(CombineArgs a) {
     } else {
       const int32_t ne = a.evc[e].n;
       i0 = u * a.parts;
-      i1 = i0 + (ne - 1) / part_length(ne, a.parts, kFisherStretch) + 1;
+      i1 = i0 + (ne - 1) / part_length(ne, a.parts, a.unit) + 1;
     }
     for (int64_t i = i0; i < i1; ++i) s += a.partial[i * NACC + slot];
   }

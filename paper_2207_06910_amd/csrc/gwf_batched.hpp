@@ -58,7 +58,7 @@ struct ItemsArgs {
   // split form: a workgroup for each of `parts` parts of n events (those a short
   // grid does not fill leave at once), for each of n_mat matrices per event;
   // n_set: SiteC per event, matrix m of several taking the m-th alone
-  int32_t parts, n, n_mat, n_set;
+  int32_t parts, unit, n, n_mat, n_set;   // unit: points of a stretch (stretch_length)
   int64_t base;               // first item of the launch (set by the launcher)
 };
 
@@ -67,7 +67,7 @@ struct CombineArgs {
   const EventC* evc;
   const int32_t* item_first;  // [n+1]: items of event e are item_first[e] .. item_first[e+1]-1
   const double* partial;
-  int32_t parts, n_mat;       // split form (item_first NULL), see ItemsArgs
+  int32_t parts, unit, n_mat; // split form (item_first NULL), see ItemsArgs
   int32_t keep_snr;           // nonzero: events with a status keep the SNR of the pass that skipped them
   double* fisher;             // [n_mat][P][P][n]
   double* snr;                // [n] or NULL

@@ -76,7 +76,8 @@ __global__ __launch_bounds__(kBlock, 2) void fisher_kernel(FisherArgs a) {
   }
 
   double t = 0.0;
-  const int len = EXPL ? ec.n : stretch_length(ec.n, kFisherStretch);     // an explicit grid has one form only
+  // an explicit grid has one form only
+  const int len = EXPL ? ec.n : stretch_length(ec.n, a.ifo_sel > 0 ? kIfoStretch : kFisherStretch);
   if (ec.n <= len) {
     double x = 0.0;
     fisher_sums<NPI, 1, ROT, false, EXPL, TAB>(ec, sc, n_site, 0, ec.n, L, &x);

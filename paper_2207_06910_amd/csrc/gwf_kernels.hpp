@@ -29,12 +29,14 @@ hipError_t launch_slices(Args a, int64_t units, int64_t units_per_wg, unsigned b
 // same bits whatever the other events of its catalogue, by which the form is
 // chosen, and whatever memory there is for the split one.
 // The lengths weigh the reductions of a full chip against the latency of a few
-// events.  Matrices in stretches of 2048, 3072 and 4096 points: 500 pairs' of
-// five interferometers 511, 476 and 458 us, 1501 events with their threshold
-// 536, 503 and 488, 100 pairs 61, 59 and 69, one pair 38, 45 and 49; SNR in 2048,
-// 3072 and 4096: 3000 pairs 273, 253 and 244 us, one pair 31, 31 and 33.
+// events.  In stretches of 2048, 3072 and 4096 points: matrices of 1501 events
+// with their threshold 536, 503 and 488 us, of 100 pairs 61, 59 and 69, of one pair
+// 38, 45 and 49; of five interferometers of 500 pairs 511, 476 and 458, of four
+// pairs 35, 38 and 43; SNR of 3000 pairs 273, 253 and 244, of one pair 31, 31 and
+// 33.
 constexpr int32_t kPartUnit = 512;      // what a workgroup takes in one iteration
 constexpr int32_t kFisherStretch = 6 * kPartUnit, kSnrStretch = 8 * kPartUnit, kMaxStretches = 64;
+constexpr int32_t kIfoStretch = 8 * kPartUnit;     // per-interferometer matrices: many workgroups an event
 __host__ __device__ inline int32_t stretch_length(int32_t n, int32_t unit) {
   return n <= unit * kMaxStretches ? unit : ((n - 1) / (unit * kMaxStretches) + 1) * unit;
 }

@@ -25,7 +25,7 @@
 
 using namespace gwf;
 
-static_assert(kFisherStretch == GWF_FISHER_STRETCH && kSnrStretch == GWF_SNR_STRETCH &&
+static_assert(kFisherStretch == GWF_FISHER_STRETCH && kSnrStretch == GWF_SNR_STRETCH && kIfoStretch == GWF_IFO_STRETCH &&
               kMaxStretches == GWF_SPLIT_PARTS_MAX, "stretches as declared");
 
 namespace {
@@ -110,13 +110,14 @@ gwf_status run(const gwf_events* ev, const gwf_grid* grid, uint32_t flags, doubl
     }
   }
   if (err == hipSuccess && l.n_mat) {
+    const int32_t unit = l.sets == kSetsIfos ? kIfoStretch : kFisherStretch;
     ItemsArgs ia{};
     ia.evc = evc; ia.sic = sic; ia.n_site = l.n_mat > 1 || l.sets == kSetsIfos ? 1 : nd.n_site;
-    ia.partial = partial; ia.parts = parts; ia.n = (int32_t)ev->n; ia.n_mat = l.n_mat; ia.n_set = l.n_set;
+    ia.partial = partial; ia.parts = parts; ia.unit = unit; ia.n = (int32_t)ev->n; ia.n_mat = l.n_mat; ia.n_set = l.n_set;
     err = launch_items(ia, npi, rot, false, tab, ev->n * parts * l.n_mat, s);
     if (err == hipSuccess) {
       CombineArgs ca{};
-      ca.n = ev->n; ca.evc = evc; ca.partial = partial; ca.parts = parts; ca.n_mat = l.n_mat;
+      ca.n = ev->n; ca.evc = evc; ca.partial = partial; ca.parts = parts; ca.unit = unit; ca.n_mat = l.n_mat;
       ca.fisher = fisher; ca.snr = snr; ca.status = status; ca.par_mask = ev->par_mask;
       ca.keep_snr = snr_th > 0.0;
       err = launch_combine(ca, npi, s);

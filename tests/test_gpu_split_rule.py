@@ -29,7 +29,7 @@ SNR, FISHER, BOTH, IFOS = 0, 1, 2, 3
     (1, 4096, SNR, "bns", None), (1, 4097, SNR, "bns", 2), (1, 8193, SNR, "bns", 3),
     (512, 600, FISHER, "bbh", None), (513, 600, FISHER, "bbh", 1), (513, 500, FISHER, "bbh", None),
     (512, 4096, SNR, "bbh", None), (513, 100, SNR, "bbh", 1),
-    (1, 100, IFOS, "bns", 1), (1, 100, IFOS, "bbh", None), (1, 20000, IFOS, "bbh", 7),
+    (1, 100, IFOS, "bns", 1), (1, 100, IFOS, "bbh", None), (1, 20000, IFOS, "bbh", 5),
     (2, 64 * 3072, FISHER, "bbh", 64), (2, 64 * 3072 + 1, FISHER, "bbh", 64), (2, 2, SNR, "bbh", None)])
 def test_rule(lib, monkeypatch, n, npts, what, pop, parts):
     wl = synth.bns1e4(n=n, seed=3).with_npts(npts) if pop == "bns" else synth.bbh100(n=n, npts=npts, seed=3)
