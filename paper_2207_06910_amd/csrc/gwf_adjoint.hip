@@ -19,7 +19,7 @@
 //
 // The batched form (gwf_plan_adjoint) runs the same per-point mathematics
 // over a plan's work items:
-//   adj_setup_kernel        one lane per event (AdjEventC from Gbar) and one
+//   adj_setup_kernel        16 lanes per event (AdjEventC from Gbar) and one
 //                   per (event, site) (AdjSiteC), into the plan's adjoint
 //                   workspace (the plan's set-up kernel has written EventC
 //                   and SiteC);
@@ -29,8 +29,8 @@
 //                   constant address space (scalar loads into SGPRs); the
 //                   item's per-site sums go to its slot (deterministic:
 //                   fixed reduction order, slots in event order);
-//   adjoint_combine_kernel  one lane per event sums its items' slots in item
-//                   order and forms the event's gradient terms; the
+//   adjoint_combine_kernel  one lane per (event, site) sums its items' slots in
+//                   item order and forms the site's gradient terms; the
 //                   reduce_kernel then sums the events.
 #include <algorithm>
 

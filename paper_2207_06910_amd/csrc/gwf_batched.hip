@@ -1,9 +1,9 @@
 // gwf_batched.hip -- batched form of the Fisher/SNR path for catalogues with
 // uneven grid lengths.
 //
-//   setup_kernel    one lane per event and one per event x site: the
-//                   per-event and per-site constants, written once to a
-//                   workspace.
+//   setup_kernel    three lanes per event (the parts of its constants) and one
+//                   per event x site, each on a row of workgroups of its own:
+//                   written once to a workspace.
 //   items_kernel    one workgroup per work item (event, point range [k0, k1),
 //                   at most `chunk` points), dispatched in the plan's
 //                   longest-first order, writes the item's partial sums to its

@@ -108,8 +108,9 @@ hipError_t launch_snr_combine(const SnrCombineArgs& a, hipStream_t s);
 struct AdjEventC;
 struct AdjSiteC;
 
-// One lane per event: the contractions of its Gbar and its sites' pattern
-// derivatives, after the plan's set-up kernel (EventC, SiteC).
+// The contractions of each event's Gbar (16 lanes an event) and its sites'
+// pattern derivatives (a lane each), after the plan's set-up kernel (EventC,
+// SiteC).
 struct AdjSetupArgs {
   const double* par;          // [13][ld]: theta and psi of each event
   int64_t ld, n;

@@ -2,12 +2,15 @@
 //
 // One workgroup of 256 lanes per event.  The workgroup first builds the
 // event's constants (PN-series coefficients, grid, amplitude) and each
-// site's constants (pattern maps, delay and PSD factors) in LDS; every lane
-// then walks the event's frequency grid with stride 256, evaluates the
-// derivative vectors of all interferometers at its frequency in registers
-// and accumulates the noise-weighted Gram matrix; a fixed-order wavefront +
-// LDS reduction produces the event's matrix.  Nothing is atomically added,
-// so results are bitwise reproducible.
+// site's constants (pattern polynomials, delay and PSD factors) in LDS, three
+// parts of the event and the sites side by side; every lane then walks a stretch
+// of the event's frequency grid with stride 256, sums the products of all
+// interferometers' response vectors at its frequency in registers (NetSums) and
+// adds the point's share of the noise-weighted Gram matrix; a fixed-order
+// wavefront + LDS reduction produces the stretch's matrix, and the stretches
+// are added in order.  Nothing is atomically added, so results are bitwise
+// reproducible, and the split form (gwf_split.hip), a workgroup per stretch,
+// gives the same bits.
 //
 // The accumulation itself (gwf_fisher_body.hpp) is shared with the batched
 // work-item form (gwf_batched.hip).
@@ -18,18 +21,19 @@
 // from per-frequency network sums W = sum_i w_i |Q_i|^2 and
 // U_b = sum_i w_i Re(i Q_i D_b,i^*):
 //   Gamma_ab += W c_a c_b   (a, b phase-only),   Gamma_ba += U_b c_a,
-// and only the 8x8 block of (Mc, eta, dL, theta, phi, iota, psi, tc) needs a
-// per-interferometer rank-2 update.
+// and the 8x8 block of (Mc, eta, dL, theta, phi, iota, psi, tc) follows from the
+// same point's 14 sums by coefficients that no interferometer changes
+// (accumulate_sums).
 #include "gwf_fisher_body.hpp"
 #include "gwf_snr_body.hpp"
 
 namespace gwf {
 
-// Two workgroups per compute unit (256 registers; 45 KB of LDS each with
-// tides: 37 KB of FisherLds, the event's 1.1 KB of constants and 6.9 KB for
+// Two workgroups per compute unit (256 registers; 43 KB of LDS each with
+// tides: 37 KB of FisherLds, the event's 1.2 KB of constants and 4.9 KB for
 // eight sites) hide the latency of the LDS constant reads and of the
 // transcendental sequences.
-static_assert(64 + kMaxSites <= kBlock, "site set-up lanes in the second wavefront");
+static_assert(64 + kMaxSites <= 128, "site set-up lanes in the second wavefront");
 
 template <int NPI_, bool ROT, bool EXPL, bool TAB>
 __global__ __launch_bounds__(kBlock, 2) void fisher_kernel(FisherArgs a) {

@@ -31,8 +31,9 @@
 // What bounds it: 10^4 matrices are 2500 wavefronts, 2 or 3 to a SIMD, each a
 // chain of about 94 steps; the LDS pipe carried the columns 73 % of the time
 // as 28 four-byte permutes a step, and as 14 sixteen-byte accesses 63 % of a
-// shorter time.  10^4 13 x 13 matrices: covariance and condition 179 us
-// before, 142 us in this form; one matrix 79 and 67 us.
+// shorter time.  10^4 13 x 13 matrices (condition numbers 20 to 6e4): covariance
+// and condition 166 us before, 133 us in this form; one matrix 86 and 73 us; with
+// the eigen-decomposition, on the factor too, 280 and 237 us.
 //
 // Inversion.  The Cholesky factorisation is right-looking over columns: at
 // step k the pivot lane's column is broadcast and every later column updates

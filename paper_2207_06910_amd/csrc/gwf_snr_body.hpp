@@ -7,12 +7,11 @@
 // the arms themselves as effective interferometers (kArmsPlain): an L's one
 // arm, a triangle's first two, whose third response is minus their sum.
 //
-// What bounds it: FP64 issue, about 80 instructions per point and 25 per site
-// and 14 per arm.  On 3000 neutron-star binaries (2.9e7 points, three sites,
-// five interferometers) one workgroup per event takes 0.38 ms (0.24 with each
-// event shared out over workgroups, see gwf_split.hip), where an
-// exponential per point and site, patterns from frame products and Horner
-// series took 0.58 ms.
+// What bounds it: FP64 issue, about 80 instructions per point, 25 per site
+// and 15 per arm.  On 3000 neutron-star binaries (2.9e7 points, three sites,
+// five interferometers), a workgroup per stretch (gwf_split.hip): 0.245 ms, where
+// an exponential per point and site, patterns from frame products and Horner
+// series with one workgroup per event took 0.58 ms.
 #pragma once
 
 #include "gwf_fisher_body.hpp"

@@ -9,10 +9,12 @@
 // writes every event's constants once, the work-item kernel (gwf_batched.hip)
 // takes (event, part, matrix) from its workgroup's number -- no item table,
 // so nothing is read back or built -- with scalar loads of the constants, and
-// the parts' sums are combined in order.  Measured, one workgroup per event
-// and split: one neutron-star pair 188 and 41 us, 600 pairs 358 and 210 us,
-// 1501 events with their SNR threshold 816 and 535 us, 500 pairs' matrices of
-// five interferometers 892 and 468 us, SNR of 3000 pairs 372 and 247 us.
+// the parts' sums are combined in order.  A part is a stretch of the grid that
+// the one-workgroup form sums on its own as well (stretch_length), so both
+// forms give the same bits.  Measured before there was a split form and now: one
+// neutron-star pair 165 and 45 us, 1000 pairs 512 and 289 us, 1501 events with
+// their SNR threshold 1043 and 502 us, 500 pairs' matrices of five
+// interferometers 945 and 462 us, SNR of 3000 pairs 578 and 245 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
