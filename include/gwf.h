@@ -497,9 +497,9 @@ gwf_status gwf_fisher_basis(int32_t P, int64_t n, const double* fisher, const gw
  * Other arguments as for the plain calls; explicit grids return
  * GWF_E_UNSUPPORTED. */
 #define GWF_SPLIT_PARTS_MAX 64
-#define GWF_FISHER_STRETCH 3072
+#define GWF_FISHER_STRETCH 2560
 #define GWF_SNR_STRETCH 4096
-#define GWF_IFO_STRETCH 4096
+#define GWF_IFO_STRETCH 3072
 
 int64_t gwf_split_bytes(int64_t n, const gwf_network* net, uint32_t flags, int32_t what, int32_t parts);
 

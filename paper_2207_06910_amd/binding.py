@@ -305,7 +305,7 @@ class DeviceWorkload:
 
 
 SPLIT_SNR, SPLIT_FISHER, SPLIT_SNR_FISHER, SPLIT_IFOS = 0, 1, 2, 3
-FISHER_STRETCH, SNR_STRETCH, IFO_STRETCH = 3072, 4096, 4096     # GWF_FISHER_STRETCH, ...
+FISHER_STRETCH, SNR_STRETCH, IFO_STRETCH = 2560, 4096, 3072     # GWF_FISHER_STRETCH, ...
 SPLIT_WORK_MAX = 256 << 20      # bytes of workspace a plain call may take
 
 

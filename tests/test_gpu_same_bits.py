@@ -12,7 +12,7 @@ from paper_2207_06910_amd import synth
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-LENGTHS = [2, 511, 513, 3071, 3072, 3073, 4096, 4097, 6145, 8193, 20000, 64 * 3072 + 5]
+LENGTHS = [2, 511, 513, 2560, 2561, 3072, 3073, 4096, 4097, 8193, 20000, 64 * 3072 + 5]
 
 
 @pytest.fixture(scope="module")

@@ -25,12 +25,12 @@ SNR, FISHER, BOTH, IFOS = 0, 1, 2, 3
 
 
 @pytest.mark.parametrize("n,npts,what,pop,parts", [
-    (1, 2048, FISHER, "bns", None), (1, 2049, FISHER, "bns", 1), (1, 3072, BOTH, "bns", 1), (1, 3073, BOTH, "bns", 2),
+    (1, 2048, FISHER, "bns", None), (1, 2049, FISHER, "bns", 1), (1, 2560, BOTH, "bns", 1), (1, 2561, BOTH, "bns", 2),
     (1, 4096, SNR, "bns", None), (1, 4097, SNR, "bns", 2), (1, 8193, SNR, "bns", 3),
     (512, 600, FISHER, "bbh", None), (513, 600, FISHER, "bbh", 1), (513, 500, FISHER, "bbh", None),
     (512, 4096, SNR, "bbh", None), (513, 100, SNR, "bbh", 1),
-    (1, 100, IFOS, "bns", 1), (1, 100, IFOS, "bbh", None), (1, 20000, IFOS, "bbh", 5),
-    (2, 64 * 3072, FISHER, "bbh", 64), (2, 64 * 3072 + 1, FISHER, "bbh", 64), (2, 2, SNR, "bbh", None)])
+    (1, 100, IFOS, "bns", 1), (1, 100, IFOS, "bbh", None), (1, 20000, IFOS, "bbh", 7),
+    (2, 64 * 2560, FISHER, "bbh", 64), (2, 64 * 2560 + 1, FISHER, "bbh", 64), (2, 2, SNR, "bbh", None)])
 def test_rule(lib, monkeypatch, n, npts, what, pop, parts):
     wl = synth.bns1e4(n=n, seed=3).with_npts(npts) if pop == "bns" else synth.bbh100(n=n, npts=npts, seed=3)
     dw = lib.DeviceWorkload(wl)
