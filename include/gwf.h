@@ -481,22 +481,27 @@ gwf_status gwf_fisher_basis(int32_t P, int64_t n, const double* fisher, const gw
  * outputs, statuses and thresholds, for log grids.  Both forms sum an event's
  * grid in stretches of GWF_FISHER_STRETCH, GWF_SNR_STRETCH or (one matrix per
  * interferometer) GWF_IFO_STRETCH points (times the smallest whole number that
- * leaves no more than GWF_SPLIT_PARTS_MAX of them), so with as many parts as that the results are those of the plain calls bit
- * for bit, whatever the other events.  For few events, long grids or uneven ones, where one workgroup
- * per event leaves the chip idle; the set-up, part and combine kernels are
- * ordinary launches on `stream`, nothing is allocated or read back.
+ * leaves no more than GWF_SPLIT_PARTS_MAX of them), so with as many parts as that
+ * the results are those of the plain calls bit for bit, whatever the other events.
+ * For few events, long grids or uneven ones, where one workgroup per event leaves
+ * the chip idle; the set-up, part and combine kernels are ordinary launches on
+ * `stream`, nothing is allocated or read back.
  *   parts      1..GWF_SPLIT_PARTS_MAX, the most parts of one event's grid: a
  *              part is a stretch; a grid of more stretches has longer parts, of
  *              ceil(n / parts) points rounded up to a multiple of 512 (its sums
  *              then differ in their last bits)
  *   work       device, 256-byte aligned, of at least gwf_split_bytes bytes; used
- *              until the stream has passed the call; contents need not be set
- *   gwf_split_bytes   the workspace of n events (-1 and gwf_last_error if the
- *              arguments are invalid); what: 0 gwf_snr_split, 1 gwf_fisher_split,
+ *              until the stream has passed the call; contents need not be set.
+ *              More events than it holds at once are taken in slices, one after
+ *              the other on the stream, with the same results
+ *   gwf_split_bytes   the workspace of n events, no more than
+ *              GWF_SPLIT_SLICE_BYTES however many they are (-1 and gwf_last_error
+ *              if the arguments are invalid); what: 0 gwf_snr_split, 1 gwf_fisher_split,
  *              2 the same with snr_th > 0 or snr_ifo, 3 gwf_fisher_ifo_split
  * Other arguments as for the plain calls; explicit grids return
  * GWF_E_UNSUPPORTED. */
 #define GWF_SPLIT_PARTS_MAX 64
+#define GWF_SPLIT_SLICE_BYTES (256 << 20)
 #define GWF_FISHER_STRETCH 2560
 #define GWF_SNR_STRETCH 4096
 #define GWF_IFO_STRETCH 3072

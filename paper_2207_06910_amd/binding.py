@@ -306,16 +306,16 @@ class DeviceWorkload:
 
 SPLIT_SNR, SPLIT_FISHER, SPLIT_SNR_FISHER, SPLIT_IFOS = 0, 1, 2, 3
 FISHER_STRETCH, SNR_STRETCH, IFO_STRETCH = 2560, 4096, 3072     # GWF_FISHER_STRETCH, ...
-SPLIT_WORK_MAX = 256 << 20      # bytes of workspace a plain call may take
+SPLIT_WORK_MAX = 256 << 20      # bytes of workspace a plain call may take (GWF_SPLIT_SLICE_BYTES)
 
 
 def _split(dw: DeviceWorkload, net, what, stream):
     """(parts, workspace) of a plain call in the split form (gwf_*_split), or
     None where one workgroup per event is the better form: explicit grids, which
-    the split form does not take; catalogues whose constants would need more
-    than SPLIT_WORK_MAX, which fill the chip by themselves; and short grids of
-    no more events than the chip runs workgroups at once (512), where one launch
-    beats three.  The form changes no result.  Measured, plain and split, us:
+    the split form does not take, and short grids of no more events than the chip
+    runs workgroups at once (512), where one launch beats three.  The form changes
+    no result, nor does the workspace, of at most SPLIT_WORK_MAX bytes, in which
+    larger catalogues are taken in slices.  Measured, plain and split, us:
     Fisher of one event of 1000 and 2000 neutron-star points 31 and 33, 43 and
     39, of 400 events 38 and 41, 54 and 52, of 800 events of 500 points 48 and
     46 and of 100 points 40 and 46; SNR of 400 events of 4000 and 6000 points 40

@@ -161,9 +161,9 @@ __global__ void combine_kernel(CombineArgs a) {
   slot_position(slot, NPI, r, c);
   if (r == 8 && c == 8 && a.snr && !(st0 && a.keep_snr)) a.snr[e] = sqrt(s);
   if (!rows_in(event_rows(a.par_mask, e), r, c)) s = 0.0;   // not one of the event's rows
-  double* F = a.fisher + mat * ((int64_t)P * P * a.n);
-  F[((int64_t)r * P + c) * a.n + e] = s;
-  F[((int64_t)c * P + r) * a.n + e] = s;
+  double* F = a.fisher + mat * ((int64_t)P * P * a.ldo);
+  F[((int64_t)r * P + c) * a.ldo + e] = s;
+  F[((int64_t)c * P + r) * a.ldo + e] = s;
   // the set-up kernel wrote the parameter status; a non-finite sum adds its bit
   if (!st0 && !finite(s)) atomicOr(a.status + e, (int32_t)kEvNonFinite);
 }
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(64) void snr_combine_kernel(SnrCombineArgs a) {
     for (int32_t q = 0; q < parts; ++q) t += a.partial[(e * a.parts + q) * a.n_ifo + i];
     if (a.active && !a.active[(int64_t)i * a.ld + e]) t = 0.0;   // off for this event
     tot += t;
-    if (a.snr_ifo) a.snr_ifo[(int64_t)i * a.n + e] = sqrt(t);
+    if (a.snr_ifo) a.snr_ifo[(int64_t)i * a.ldo + e] = sqrt(t);
   }
   const double snr = sqrt(tot);
   a.snr[e] = snr;

@@ -63,13 +63,13 @@ struct ItemsArgs {
 };
 
 struct CombineArgs {
-  int64_t n;
+  int64_t n, ldo;             // events, and the length of the output rows (n or, of a slice, more)
   const EventC* evc;
   const int32_t* item_first;  // [n+1]: items of event e are item_first[e] .. item_first[e+1]-1
   const double* partial;
   int32_t parts, unit, n_mat; // split form (item_first NULL), see ItemsArgs
   int32_t keep_snr;           // nonzero: events with a status keep the SNR of the pass that skipped them
-  double* fisher;             // [n_mat][P][P][n]
+  double* fisher;             // [n_mat][P][P][ldo]
   double* snr;                // [n] or NULL
   int32_t* status;            // [n]
   const uint32_t* par_mask;   // [n] or NULL: rows of each event's Fisher matrix (others 0)
@@ -89,14 +89,14 @@ struct SnrPartsArgs {
 };
 
 struct SnrCombineArgs {
-  int64_t n, ld;
+  int64_t n, ld, ldo;         // ldo: length of snr_ifo's rows
   int32_t parts, n_ifo;
   const uint8_t* active;      // [n_ifo][ld] or NULL
   EventC* evc;                // an event below the threshold gets its status here
   const double* partial;
   double snr_th;              // > 0: events whose SNR does not exceed it are skipped
   double* snr;                // [n]
-  double* snr_ifo;            // [n_ifo][n] or NULL
+  double* snr_ifo;            // [n_ifo][ldo] or NULL
   int32_t* status;            // [n] or NULL
 };
 

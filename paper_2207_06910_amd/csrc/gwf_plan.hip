@@ -195,7 +195,7 @@ gwf_status enqueue(gwf_plan* p, const Outs& o, hipStream_t s) {
   }
   if (err == hipSuccess) {
     CombineArgs ca{};
-    ca.n = p->n; ca.evc = p->evc; ca.item_first = p->item_first; ca.partial = p->partial;
+    ca.n = ca.ldo = p->n; ca.evc = p->evc; ca.item_first = p->item_first; ca.partial = p->partial;
     ca.fisher = o.fisher; ca.snr = o.snr; ca.status = o.status; ca.par_mask = p->ev.par_mask;
     err = launch_combine(ca, p->npi, s);
   }

@@ -123,7 +123,7 @@ gwf_status gwf_fisher_static(const gwf_events* ev, const gwf_network* net, const
   }
   if (err == hipSuccess) {
     CombineArgs ca{};
-    ca.n = n; ca.evc = evc; ca.item_first = first; ca.partial = partial;
+    ca.n = ca.ldo = n; ca.evc = evc; ca.item_first = first; ca.partial = partial;
     ca.fisher = fisher; ca.snr = snr; ca.status = status; ca.par_mask = ev->par_mask;
     err = launch_combine(ca, npi, s);
   }
