@@ -53,6 +53,7 @@ __global__ __launch_bounds__(64) void setup_kernel(SetupArgs a) {
   if (row == 0) {
     EventC& ec = a.evc[e];
     event_grid_setup(p, a.fmin[e], a.fmax ? a.fmax[e] : 0.0, a.npts[e], a.flags, ec);
+    if (!ec.status_circ) GridWalk::keep_ratios(ec, kBlock);
     if (!ec.status && (a.npts[e] != a.npts_plan[e] || a.npts[e] > a.npts_max))
       ec.status = ec.status_circ = kEvInvalid;   // grid changed since the items were built, or longer than they allow
     if (a.status) a.status[e] = ec.status;
@@ -305,7 +306,7 @@ __global__ __launch_bounds__(kBlock, 2) void snr_parts_kernel(SnrPartsArgs a) {
   double acc[kSnrSlots];
 #pragma unroll
   for (int i = 0; i < kSnrSlots; ++i) acc[i] = 0.0;
-  snr_sums<ROT, false, TAB>(ec, sc, a.net.n_site, k0, k0 + min(ec.n - k0, len), acc);
+  snr_sums<ROT, false, TAB, true>(ec, sc, a.net.n_site, k0, k0 + min(ec.n - k0, len), acc);
   double t;
   snr_reduce(acc, a.net.n_site, a.net.n_ifo, site_shapes(a.net), red, &t);
   if ((int)threadIdx.x < a.net.n_ifo) a.partial[((int64_t)e * a.parts + part) * a.net.n_ifo + threadIdx.x] = t;

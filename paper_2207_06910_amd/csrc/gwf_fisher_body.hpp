@@ -169,7 +169,9 @@ __device__ inline void fisher_sums(const EventC& ec, const SiteC* sc, int n_site
   // on a log grid, v, 1/v and v^-12.42 walk from point to point (GridWalk)
   GridWalk gw;
   if (!EXPL) {
-    gw.start(ec, point_past(k0, tid, k1) ? k1 - 1 : k0 + tid, kBlock);
+    const int k = point_past(k0, tid, k1) ? k1 - 1 : k0 + tid;
+    if (NQ == 2) gw.start_kept(ec, k);     // the work-item kernels: the set-up kernel left the ratios
+    else gw.start(ec, k, kBlock);
 #pragma unroll
     for (int i = 0; i < 3; ++i) gw.ratio[i] = uniform_d(gw.ratio[i]);   // the same step in every lane
   }

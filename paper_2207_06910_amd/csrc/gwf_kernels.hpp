@@ -30,11 +30,12 @@ hipError_t launch_slices(Args a, int64_t units, int64_t units_per_wg, unsigned b
 // chosen, and whatever memory there is for the split one.
 // The lengths weigh what a workgroup costs a full chip besides its points (its
 // start, the walk's, the reduction) against the latency of a few events.  In
-// stretches of 2048, 2560, 3072 and 4096 points: matrices of 1501 events with
-// their threshold 536, 516, 503 and 488 us, of 100 pairs 61, 53, 59 and 69, of
-// one pair 38, 42, 45 and 49; of five interferometers of 500 pairs 511, 490, 476
-// and 458, of four pairs 35, 37, 38 and 43; SNR of 3000 pairs 273, 259, 253 and
-// 244, of one pair 31, 32, 31 and 33.
+// stretches of 2048, 2560, 3072 and 4096 points (before the walk's ratios came
+// with the constants, 1 to 3 % more): matrices of 1501 events with their
+// threshold 536, 516, 503 and 488 us, of 100 pairs 61, 53, 59 and 69, of one pair
+// 38, 42, 45 and 49; of five interferometers of 500 pairs 511, 490, 476 and 458,
+// of four pairs 35, 37, 38 and 43; SNR of 3000 pairs 273, 259, 253 and 244, of
+// one pair 31, 32, 31 and 33.
 constexpr int32_t kPartUnit = 512;      // what a workgroup takes in one iteration
 constexpr int32_t kFisherStretch = 5 * kPartUnit, kSnrStretch = 8 * kPartUnit;
 constexpr int32_t kIfoStretch = 6 * kPartUnit;     // per-interferometer matrices: more workgroups an event

@@ -29,14 +29,16 @@ constexpr int kSnrSlots = 3 * kMaxSites;     // slot 3 s + k: arm k of site s
 constexpr int kSnrWalk = 16 * kBlock;
 
 // Adds the points of [k0, k1) that lane tid of a workgroup takes to its
-// acc[kSnrSlots].
-template <bool ROT, bool EXPL, bool TAB>
+// acc[kSnrSlots].  KEPT: the set-up kernel left the walk's ratios.
+template <bool ROT, bool EXPL, bool TAB, bool KEPT = false>
 __host__ __device__ inline void snr_lane(const EventC& ec, const SiteC* sc, int n_site, int k0, int k1, int tid,
                                          double* acc) {
   constexpr int NQ = 2;
   GridWalk gw;
   if (!EXPL) {
-    gw.start(ec, point_past(k0, tid, k1) ? k1 - 1 : k0 + tid, kBlock);
+    const int k = point_past(k0, tid, k1) ? k1 - 1 : k0 + tid;
+    if (KEPT) gw.start_kept(ec, k);
+    else gw.start(ec, k, kBlock);
 #pragma unroll
     for (int i = 0; i < 3; ++i) gw.ratio[i] = uniform_d(gw.ratio[i]);
   }
@@ -87,9 +89,9 @@ __host__ __device__ inline void snr_lane(const EventC& ec, const SiteC* sc, int 
   }
 }
 
-template <bool ROT, bool EXPL, bool TAB>
+template <bool ROT, bool EXPL, bool TAB, bool KEPT = false>
 __device__ inline void snr_sums(const EventC& ec, const SiteC* sc, int n_site, int k0, int k1, double* acc) {
-  snr_lane<ROT, EXPL, TAB>(ec, sc, n_site, k0, k1, threadIdx.x, acc);
+  snr_lane<ROT, EXPL, TAB, KEPT>(ec, sc, n_site, k0, k1, threadIdx.x, acc);
 }
 
 // The workgroup's sums of every interferometer: on return (after a workgroup
