@@ -33,7 +33,7 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 MEASURED_TRAFFIC = {
     "items_kernel<tidal,rot>": 58.1e6,
     "items_kernel<tidal,rot,mixed>": 60.1e6,
-    "items_kernel<tidal,rot,parts>": 146.1e6,
+    "items_kernel<tidal,rot,parts>": 145.8e6,
     "waveform_kernel<rot,tidal>": 7848.9e6,
     "waveform_kernel<rot,tidal,mixed>": 7862.9e6,
     "waveform_deriv_kernel<rot,tidal>": 10301.7e6,
@@ -46,9 +46,9 @@ MEASURED_TRAFFIC = {
 # clock is 4 x SQ_INSTS_VALU / (1024 SIMDs x 2.4 GHz x kernel time).  Set an
 # entry to None when its kernel changes.
 MEASURED_VALU_INSTS = {
-    "items_kernel<tidal,rot>": 9.45e8,
-    "items_kernel<tidal,rot,mixed>": 9.51e8,
-    "items_kernel<tidal,rot,parts>": 1.047e9,
+    "items_kernel<tidal,rot>": 9.40e8,
+    "items_kernel<tidal,rot,mixed>": 9.48e8,
+    "items_kernel<tidal,rot,parts>": 1.032e9,
 }
 N_SIMD, CLOCK_HZ = 1024, 2.4e9
 

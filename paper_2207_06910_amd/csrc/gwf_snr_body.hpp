@@ -9,7 +9,7 @@
 //
 // What bounds it: FP64 issue, about 80 instructions per point, 25 per site
 // and 15 per arm.  On 3000 neutron-star binaries (2.9e7 points, three sites,
-// five interferometers), a workgroup per stretch (gwf_split.hip): 0.245 ms, where
+// five interferometers), a workgroup per stretch (gwf_split.hip): 0.237 ms, where
 // an exponential per point and site, patterns from frame products and Horner
 // series with one workgroup per event took 0.58 ms.
 #pragma once

@@ -13,9 +13,9 @@
 // are taken in slices, one after the other on the stream.  A part is a stretch of the grid that
 // the one-workgroup form sums on its own as well (stretch_length), so both
 // forms give the same bits.  Measured before there was a split form and now: one
-// neutron-star pair 165 and 41 us, 1000 pairs 512 and 291 us, 1501 events with
-// their SNR threshold 1043 and 494 us, 500 pairs' matrices of five
-// interferometers 945 and 470 us, SNR of 3000 pairs 578 and 242 us.
+// neutron-star pair 165 and 41 us, 1000 pairs 512 and 290 us, 1501 events with
+// their SNR threshold 1043 and 487 us, 500 pairs' matrices of five
+// interferometers 945 and 468 us, SNR of 3000 pairs 578 and 237 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
